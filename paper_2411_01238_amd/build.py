@@ -8,7 +8,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libsdrop.so")
-SOURCES = ["sdrop_mask.hip", "sdrop_bias_grad.hip", "sdrop_gemm.hip", "sdrop_gemm_f16.hip", "sdrop_gemm_bf16.hip"]
+# (source, object, defines): the GEMM kernels are one source, compiled per operand type and group of kernels.
+# The longest units come first.
+UNITS = [("sdrop_gemm_inst.hip", "sdrop_gemm_%s_%d.o" % (t.lower(), part), ["-DSDROP_T=" + t, "-DSDROP_PART=%d" % part])
+         for part in (1, 0, 3, 2) for t in ("F16", "BF16")]
+UNITS += [(src, os.path.splitext(src)[0] + ".o", []) for src in ("sdrop_gemm.hip", "sdrop_mask.hip", "sdrop_bias_grad.hip")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -23,9 +27,10 @@ def _hipcc():
     return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-def _compile(src):
-    obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc()] + HIPCC_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit):
+    src, obj, defines = unit
+    obj = os.path.join(CSRC, obj)
+    cmd = [_hipcc()] + HIPCC_FLAGS + defines + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
@@ -37,8 +42,8 @@ def _compile(src):
 
 def build(verbose=True):
     """Compiles every HIP source and links libsdrop.so; always rebuilds."""
-    with ThreadPoolExecutor(max_workers=min(5, len(SOURCES))) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with ThreadPoolExecutor(max_workers=min(8, len(UNITS))) as ex:
+        objs = list(ex.map(_compile, UNITS))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.check_call(cmd)
     if verbose:

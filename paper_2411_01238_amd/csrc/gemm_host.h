@@ -1,7 +1,6 @@
 // Host-side declarations shared by the GEMM translation units: the launch heuristics and knobs (defined in
-// sdrop_gemm.hip) and the two entry functions that each typed translation unit (sdrop_gemm_f16.hip,
-// sdrop_gemm_bf16.hip) instantiates for its operand type.  The kernels are compiled per operand type in
-// separate files so that they build in parallel.
+// sdrop_gemm.hip) and the entry functions that sdrop_gemm_inst.hip instantiates, once per operand type and group of
+// kernels, so that the kernels build in parallel.
 #ifndef SDROP_GEMM_HOST_H
 #define SDROP_GEMM_HOST_H
 #include "gemm_device_common.h"
@@ -51,7 +50,7 @@ constexpr int kTNNK = 129;
 
 // One of the three products for operands of type T: picks tile shapes and kernel form, launches.
 // o32: fp32 output instead of the operands' type.
-template <class T> int dispatch_typed(int op, bool o32, GemmParams &P, hipStream_t stream);
+template <int OP, class T> int dispatch_typed(bool o32, GemmParams &P, hipStream_t stream);
 // Both gradients in one launch, in the given form; dw_f32: dW's launch writes fp32 planes (a split reduction).
 // Returns -1 when the device does not grant the LDS the launch needs.
 template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, const GemmParams &Pdx, const GemmParams &Pdw,
@@ -59,12 +58,15 @@ template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, 
 // The forward product by the kernel that draws its own mask and writes the mask object (see gemm_seeded_grid.h).
 // Returns -1 when the device does not grant the LDS the launch needs.
 template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream_t stream);
-extern template int fwd_seeded_typed<F16>(bool, const GemmParams &, hipStream_t);
-extern template int fwd_seeded_typed<BF16>(bool, const GemmParams &, hipStream_t);
-extern template int dispatch_typed<F16>(int, bool, GemmParams &, hipStream_t);
-extern template int dispatch_typed<BF16>(int, bool, GemmParams &, hipStream_t);
-extern template int bwd_fused_typed<F16>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t);
-extern template int bwd_fused_typed<BF16>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t);
+#define SDROP_EXTERN(T)                                                                \
+    extern template int dispatch_typed<FWD, T>(bool, GemmParams &, hipStream_t);       \
+    extern template int dispatch_typed<DX, T>(bool, GemmParams &, hipStream_t);        \
+    extern template int dispatch_typed<DW, T>(bool, GemmParams &, hipStream_t);        \
+    extern template int fwd_seeded_typed<T>(bool, const GemmParams &, hipStream_t);    \
+    extern template int bwd_fused_typed<T>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t)
+SDROP_EXTERN(F16);
+SDROP_EXTERN(BF16);
+#undef SDROP_EXTERN
 
 }  // namespace sdrop
 #endif

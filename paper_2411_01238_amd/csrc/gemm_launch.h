@@ -1,4 +1,4 @@
-// Launch logic of the GEMM kernels for one operand type (included by the typed translation units only).
+// Launch logic of the GEMM kernels (included by sdrop_gemm_inst.hip only).
 #ifndef SDROP_GEMM_LAUNCH_H
 #define SDROP_GEMM_LAUNCH_H
 #include "gemm_host.h"
@@ -393,12 +393,9 @@ int launch_bwd_fused_tile64(const GemmParams &Pdx, const GemmParams &Pdw, int n_
 
 }  // namespace
 
-template <class T> int dispatch_typed(int op, bool o32, GemmParams &P, hipStream_t stream)
+template <int OP, class T> int dispatch_typed(bool o32, GemmParams &P, hipStream_t stream)
 {
-    using O16 = typename In<T>::out16;
-    if (op == FWD) return o32 ? dispatch_tile<FWD, T, float>(P, stream) : dispatch_tile<FWD, T, O16>(P, stream);
-    if (op == DX) return o32 ? dispatch_tile<DX, T, float>(P, stream) : dispatch_tile<DX, T, O16>(P, stream);
-    return o32 ? dispatch_tile<DW, T, float>(P, stream) : dispatch_tile<DW, T, O16>(P, stream);
+    return o32 ? dispatch_tile<OP, T, float>(P, stream) : dispatch_tile<OP, T, typename In<T>::out16>(P, stream);
 }
 
 template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream_t stream)

@@ -425,7 +425,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
             P.C = static_cast<char *>(ws);
             P.ldc = (nk_native ? K : N) * 4;            // the planes of partial sums are contiguous fp32, [K][N] or [N][K]
             P.scale = 1.0f;
-            const int rc1 = (dtype == SDROP_F16) ? dispatch_typed<F16>(OP, true, P, st) : dispatch_typed<BF16>(OP, true, P, st);
+            const int rc1 = (dtype == SDROP_F16) ? dispatch_typed<OP, F16>(true, P, st) : dispatch_typed<OP, BF16>(true, P, st);
             if (rc1 != SDROP_OK) return rc1;
             const int rc2 = launch_reduce(ws, out, K * N, P.splits, scale, dtype, out_dtype, st, nk_native ? K : N, ld_out, P);
             if (rc2 != SDROP_OK || !(w_nk && !nk_native)) return rc2;
@@ -433,7 +433,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
         }
     }
     const bool o32 = out_dtype == SDROP_F32;
-    const int rcg = dtype == SDROP_F16 ? dispatch_typed<F16>(OP, o32, P, st) : dispatch_typed<BF16>(OP, o32, P, st);
+    const int rcg = dtype == SDROP_F16 ? dispatch_typed<OP, F16>(o32, P, st) : dispatch_typed<OP, BF16>(o32, P, st);
     if (rcg != SDROP_OK || !(w_nk && !nk_native && OP == DW)) return rcg;
     return launch_transpose(out, final_out, K, N, N, final_ld, (int)esz_out, st);
 }

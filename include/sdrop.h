@@ -414,6 +414,26 @@ int sdrop_fwd_seeded_ex(const void *X, const void *W, void *mask, size_t mask_by
                         int dtype, int out_dtype, void *ws, size_t ws_bytes, void *stream,
                         const sdrop_epilogue_t *epi);
 
+/*
+ * sdrop_fwd_seeded_ex plus the layer's own bias:  Y = s (X . m') W + bias, the sum in fp32 before the one rounding.
+ *   bias   device pointer, N values of type `dtype`, 16-byte aligned
+ *   Y      has type `dtype`
+ * epi, ws and ws_bytes as for sdrop_fwd_seeded_ex (epi may be NULL: contiguous matrices, [K,N] weight).
+ */
+int sdrop_fwd_seeded_bias(const void *X, const void *W, const void *bias, void *mask, size_t mask_bytes, void *Y,
+                          int64_t M, int64_t K, int64_t N, int BM, int BK, double p, uint64_t seed, uint64_t rng_stream,
+                          int dtype, void *ws, size_t ws_bytes, void *stream, const sdrop_epilogue_t *epi);
+
+/*
+ * The gradient of that bias: db[n] = sum over all rows m of dY[m, n], accumulated in fp32, rounded once to `dtype`.
+ *   dY[M,N]   rows ld_dy elements apart (0 = N; else >= N, a multiple of 8); N a multiple of 8
+ *   db        N values of type `dtype`, 16-byte aligned
+ *   ws, ws_bytes  device workspace of at least sdrop_col_sum_workspace_bytes(M, N) bytes (fp32 rows that a second
+ *             launch adds in a fixed order: the result does not depend on scheduling)
+ */
+size_t sdrop_col_sum_workspace_bytes(int64_t M, int64_t N);
+int sdrop_col_sum(const void *dY, void *db, int64_t M, int64_t N, int dtype, int64_t ld_dy,
+                  void *ws, size_t ws_bytes, void *stream);
 
 /*
  * The layer before the dropout as an output-sparse product: only the blocks of X that the

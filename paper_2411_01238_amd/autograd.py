@@ -2,8 +2,8 @@
 
 Section 3.1 of arxiv 2411.01238: forward eq. (1), backward eq. (2) and (3), the block mask of
 Section 3.2 drawn once per call and shared by the three products.  Everything runs in libsdrop's
-kernels; this file only wires them into autograd (no arithmetic of its own besides the bias add
-and the seed bookkeeping).
+kernels; this file only wires them into autograd (no arithmetic of its own besides the add of a bias that is not of
+the operands' type, and the seed bookkeeping).
 """
 import torch
 
@@ -12,9 +12,10 @@ from . import sdrop
 
 class _SparseDropMatmul(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, w, p, BM, BK, seed, rng_stream, w_layout):
-        # the mask and eq. (1) in one call (one launch for block grids up to 128 x 64); m serves the backward
-        y, m = sdrop.sdrop_fwd_seeded(x, w, BM, BK, p, seed, rng_stream, w_layout=w_layout)
+    def forward(ctx, x, w, bias, p, BM, BK, seed, rng_stream, w_layout):
+        # the mask and eq. (1), plus the bias if there is one, in one call (one launch for block grids up to 128 x 64);
+        # m serves the backward
+        y, m = sdrop.sdrop_fwd_seeded(x, w, BM, BK, p, seed, rng_stream, w_layout=w_layout, bias=bias)
         ctx.save_for_backward(x, w)
         ctx.mask = m
         ctx.w_layout = w_layout
@@ -30,7 +31,11 @@ class _SparseDropMatmul(torch.autograd.Function):
         else:
             dx = sdrop.sdrop_bwd_dx_ex(dy, w, ctx.mask, w_layout=wl) if ctx.needs_input_grad[0] else None
             dw = sdrop.sdrop_bwd_dw_ex(x, dy, ctx.mask, w_layout=wl) if ctx.needs_input_grad[1] else None
-        return dx, dw, None, None, None, None, None, None
+        db = None
+        if ctx.needs_input_grad[2]:
+            # (as a torch operation where the caller differentiates the gradient once more: it is linear in dy)
+            db = dy.sum(0) if torch.is_grad_enabled() and dy.requires_grad else sdrop.sdrop_col_sum(dy)
+        return dx, dw, db, None, None, None, None, None, None
 
 
 def sparsedrop_matmul(x, w, p, BM=128, BK=128, seed=0, rng_stream=0, weight_layout="kn"):
@@ -41,7 +46,15 @@ def sparsedrop_matmul(x, w, p, BM=128, BK=128, seed=0, rng_stream=0, weight_layo
     its gradient.
     """
     wl = {"kn": sdrop.W_KN, "nk": sdrop.W_NK}[weight_layout]
-    return _SparseDropMatmul.apply(x, w, float(p), int(BM), int(BK), int(seed), int(rng_stream), wl)
+    return _SparseDropMatmul.apply(x, w, None, float(p), int(BM), int(BK), int(seed), int(rng_stream), wl)
+
+
+def _fusable_bias(bias, x, n):
+    """May the forward's kernel add this bias (and its gradient come from sdrop_col_sum)?  A plain vector of x's type, as the
+    kernel reads it.  Anything else, and a call under forward-mode differentiation, adds it as a torch operation."""
+    return (type(bias) in (torch.Tensor, torch.nn.Parameter) and bias.dtype == x.dtype and bias.device == x.device
+            and tuple(bias.shape) == (n,) and bias.is_contiguous() and bias.data_ptr() % 16 == 0
+            and torch.autograd.forward_ad._current_level < 0)
 
 
 _ACTS = {"relu": (sdrop.ACT_RELU, sdrop.GATE_RELU), "gelu_tanh": (sdrop.ACT_GELU_TANH, sdrop.GATE_GELU_TANH),
@@ -137,9 +150,14 @@ class SparseDropLinear(torch.nn.Module):
         lead = x.shape[:-1]
         x2 = x.reshape(-1, x.shape[-1]).contiguous()
         p = self.p if self.training else 0.0
-        y = sparsedrop_matmul(x2, self.weight, p, self.BM, self.BK, self.seed, self.calls, self.weight_layout)
+        nk = self.weight_layout == "nk"
+        bias = self.bias
+        if bias is not None and _fusable_bias(bias, x2, self.weight.shape[0 if nk else 1]):
+            y = _SparseDropMatmul.apply(x2, self.weight, bias, p, self.BM, self.BK, self.seed, self.calls, sdrop.W_NK if nk else sdrop.W_KN)
+        else:
+            y = sparsedrop_matmul(x2, self.weight, p, self.BM, self.BK, self.seed, self.calls, self.weight_layout)
+            if bias is not None:
+                y = y + bias
         if self.training:
             self.calls += 1
-        if self.bias is not None:
-            y = y + self.bias
         return y.reshape(*lead, y.shape[-1])

@@ -30,6 +30,7 @@ struct GemmParams {
     float scale;
     // optional element-wise tail of FWD and DX (see Tail below); all null / 0 for eq. (1)-(3) proper
     const float *bias;
+    const char *bias16; // FWD only: one value of the operands' type per output column (no other tail with it), or null
     const char *aux;
     int32_t act;
     int32_t gate_mode;  // how aux gates the output (SDROP_GATE_*)
@@ -121,6 +122,7 @@ __device__ __forceinline__ void store_out(char *p, uint4 v)
 //         that GELU at aux (the backward of a GELU, given its input).
 struct Tail {
     const float *bias;
+    const char *bias16; // the same in the operands' 16-bit type (the layer's own bias: kTailBias16)
     const char *aux;
     const char *c0;     // the output's origin
     int act;
@@ -129,14 +131,14 @@ struct Tail {
 __device__ __forceinline__ Tail make_tail(const GemmParams &P)
 {
     Tail t;
-    t.bias = P.bias; t.aux = P.aux; t.c0 = P.C; t.act = P.act; t.gate_mode = P.gate_mode;
+    t.bias = P.bias; t.bias16 = P.bias16; t.aux = P.aux; t.c0 = P.C; t.act = P.act; t.gate_mode = P.gate_mode;
     return t;
 }
 // The tail that writes the second output of the producing layer: bias, no activation, no gate.
 __device__ __forceinline__ Tail make_tail_preact(const GemmParams &P)
 {
     Tail t;
-    t.bias = P.bias; t.aux = nullptr; t.c0 = P.C2; t.act = SDROP_ACT_NONE; t.gate_mode = SDROP_GATE_RELU;
+    t.bias = P.bias; t.bias16 = nullptr; t.aux = nullptr; t.c0 = P.C2; t.act = SDROP_ACT_NONE; t.gate_mode = SDROP_GATE_RELU;
     return t;
 }
 // act4 / gate4 work on four consecutive columns of one output row (a register quad of the

@@ -19,7 +19,8 @@ enum TailMode {
     kTailReluGate,        // ReLU gate, no activation (bias allowed)
     kTailGeluErf,         // GELU (erf form), no gate
     kTailGeluErfGate,     // that GELU's derivative as the gate, no activation
-    kTailGeneric          // anything else (the tanh form, an activation together with a gate)
+    kTailGeneric,         // anything else (the tanh form, an activation together with a gate)
+    kTailBias16           // eq. (1) plus the layer's own 16-bit bias (GemmParams::bias16; chosen by it, not by tail_mode)
 };
 inline int tail_mode(const GemmParams &P)
 {

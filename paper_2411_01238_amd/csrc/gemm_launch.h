@@ -91,12 +91,13 @@ int launch_t(const GemmParams &P, int grid, bool ragged, hipStream_t stream, boo
 
 // The forward kernel that draws its own mask and writes the mask object (block grids of at most 128 x 64; whole
 // tiles or a ragged last tile column).  Returns -1 when the device does not grant the LDS.
-template <class T, class OutT, int TM>
+// BIAS: plus the 16-bit bias P.bias16.
+template <class T, class OutT, int TM, bool BIAS = false>
 int launch_fwd_seeded(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
-    auto k_whole = fwd_seeded_kernel<T, OutT, TM, false>;
-    auto k_edge = fwd_seeded_kernel<T, OutT, TM, true>;
+    auto k_whole = fwd_seeded_kernel<T, OutT, TM, false, BIAS>;
+    auto k_edge = fwd_seeded_kernel<T, OutT, TM, true, BIAS>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -116,13 +117,40 @@ int launch_fwd_seeded(const GemmParams &P, hipStream_t stream)
     return hip_status(hipGetLastError());
 }
 
-// eq. (1) with the weight as [N,K], read in place (N a multiple of 256, no tail); SEEDED: the mask drawn in the same
-// launch (block grids of at most 128 x 64).  Returns -1 when the device does not grant the LDS.
-template <class T, class OutT, int TM, bool SEEDED = false>
+// eq. (1) plus the 16-bit bias P.bias16, with a mask object and a [K,N] weight (whole tiles or a ragged last tile
+// column).  Returns -1 when the device does not grant the LDS.
+template <class T, class OutT, int TM>
+int launch_fwd_bias(const GemmParams &P, hipStream_t stream)
+{
+    constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
+    auto k_whole = gemm_persistent_kernel<FWD, T, OutT, TM, 256, 1, 4, kTailBias16, false>;
+    auto k_edge = gemm_persistent_kernel<FWD, T, OutT, TM, 256, 1, 4, kTailBias16, true>;
+    static int ok = -1;     // per instantiation: does the device grant that much LDS?
+    if (ok < 0) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        ok = (e == hipSuccess);
+        if (!ok) (void)hipGetLastError();
+    }
+    if (!ok) return -1;
+    GemmParams Q = P;
+    Q.n_tiles = (int)((P.N + 255) / 256);
+    Q.splits = 1;
+    Q.total_tiles = Q.MB * Q.n_tiles;
+    const int ncu = cu_count();
+    auto k = P.N % 256 != 0 ? k_edge : k_whole;
+    hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
+    return hip_status(hipGetLastError());
+}
+
+// eq. (1) with the weight as [N,K], read in place (N a multiple of 256, no tail but the 16-bit bias with BIAS); SEEDED:
+// the mask drawn in the same launch (block grids of at most 128 x 64).  Returns -1 when the device does not grant the LDS.
+template <class T, class OutT, int TM, bool SEEDED = false, bool BIAS = false>
 int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
-    auto k = fwd_nk_kernel<T, OutT, TM, SEEDED>;
+    auto k = fwd_nk_kernel<T, OutT, TM, SEEDED, BIAS>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -273,6 +301,16 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
         }
     }
     if constexpr (OP == FWD) {
+        if (P.bias16) {
+            if constexpr (sizeof(OutT) == 2) {
+                int rc;
+                if (P.w_nk) rc = P.BM == 128 ? launch_fwd_nk<T, OutT, 128, false, true>(P, stream) : launch_fwd_nk<T, OutT, 64, false, true>(P, stream);
+                else rc = P.BM == 128 ? launch_fwd_bias<T, OutT, 128>(P, stream) : launch_fwd_bias<T, OutT, 64>(P, stream);
+                return rc == -1 ? SDROP_EHIP : rc;
+            } else {
+                return SDROP_EDTYPE;         // (the output has the bias's type: checked at the entry point)
+            }
+        }
         if (P.w_nk) {
             const int rc = P.BM == 128 ? launch_fwd_nk<T, OutT, 128>(P, stream) : launch_fwd_nk<T, OutT, 64>(P, stream);
             return rc == -1 ? SDROP_EHIP : rc;       // (the [K,N] persistent form needs the same LDS)
@@ -401,6 +439,11 @@ template <int OP, class T> int dispatch_typed(bool o32, GemmParams &P, hipStream
 template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream_t stream)
 {
     using O16 = typename In<T>::out16;
+    if (P.bias16) {
+        if (o32) return SDROP_EDTYPE;
+        if (P.w_nk) return P.BM == 128 ? launch_fwd_nk<T, O16, 128, true, true>(P, stream) : launch_fwd_nk<T, O16, 64, true, true>(P, stream);
+        return P.BM == 128 ? launch_fwd_seeded<T, O16, 128, true>(P, stream) : launch_fwd_seeded<T, O16, 64, true>(P, stream);
+    }
     if (P.w_nk) {
         if (P.BM == 128) return o32 ? launch_fwd_nk<T, float, 128, true>(P, stream) : launch_fwd_nk<T, O16, 128, true>(P, stream);
         return o32 ? launch_fwd_nk<T, float, 64, true>(P, stream) : launch_fwd_nk<T, O16, 64, true>(P, stream);

@@ -94,6 +94,25 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     // a ReLU gate the gate values lie where the outputs go; store requests them a piece ahead.
     uint4 gate_q[MI * NJ][4];
     f32x4 bias_r[NJ][NIP * 4];
+    typedef __attribute__((__vector_size__(4 * sizeof(typename In<T>::out16)))) typename In<T>::out16 bias4;
+    bias4 bias16_r[NJ][NIP * 4];
+    // The 16-bit bias values of the wavefront's columns (8 bytes per lane and 8-column group), requested together.
+    // RAGN: lanes beyond the last column read the last four values instead (their results are not stored).
+    template <bool RAGN, class F> __device__ __forceinline__ void bias16_prefetch(const Tail &tl, F &&dst)
+    {
+        const int whalf = (threadIdx.x & 63) >> 5;
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj) {
+            int64_t gcol0 = 0;
+            (void)dst(0, nj, gcol0);
+#pragma unroll
+            for (int i = 0; i < NIP * 4; ++i) {
+                int64_t c = gcol0 + (i >> 2) * 32 + 8 * (i & 3) + 4 * whalf;
+                if (RAGN && c > ncols - 4) c = ncols - 4;
+                bias16_r[nj][i] = *reinterpret_cast<const bias4 *>(tl.bias16 + c * 2);
+            }
+        }
+    }
     template <int MI0 = 0, int MI1 = MI, int NJ0 = 0, int NJ1 = NJ, class F>
     __device__ __forceinline__ void tail_prefetch(int64_t ldc, const Tail &tl, F &&dst)
     {
@@ -179,7 +198,10 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                     for (int q = 0; q < 4; ++q) {
                         const f32x16 &a = acc[mi][nj * NIP + nl];
                         float v[4] = {a[4 * q] * scale, a[4 * q + 1] * scale, a[4 * q + 2] * scale, a[4 * q + 3] * scale};
-                        if constexpr (TAIL) {
+                        if constexpr (MODE == kTailBias16) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] += static_cast<float>(bias16_r[nj][nl * 4 + q][e]);
+                        } else if constexpr (TAIL) {
                             if (tl.bias) {
                                 const f32x4 bv = bias_r[nj][nl * 4 + q];
                                 v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
@@ -295,9 +317,16 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     // together do not fit the register file, those of a half do.
     template <int MODE, bool RAGN = false, class F> __device__ __forceinline__ void finish(char *reg, float scale, int64_t ldc, const Tail &tl, F &&dst)
     {
-        static_assert(!RAGN || MODE == kTailNone, "tiles that hang over the output's edge have no tail forms");
+        static_assert(!RAGN || MODE == kTailNone || MODE == kTailBias16, "tiles that hang over the output's edge have no other tail forms");
         if constexpr (MODE == kTailNone) {
             store<kTailNone, 0, MI, 0, NJ, RAGN>(reg, scale, ldc, tl, dst);
+        } else if constexpr (MODE == kTailBias16) {
+            // A layer's own bias, read as it is (16 bits) and added before the rounding, also on a ragged last tile column and
+            // with a drawn mask, where the other tails have no form: the pass over Y that adds it otherwise costs 48 us at
+            // 16384 x 3072 and 9 at 8192 x 1000, this epilogue 1-3.  16 registers of bias values for the whole sub-tile:
+            // the operand registers are free by now.
+            bias16_prefetch<RAGN>(tl, dst);
+            store<kTailBias16, 0, MI, 0, NJ, RAGN>(reg, scale, ldc, tl, dst);
         } else if constexpr (NJ >= 2) {
             constexpr int H = NJ / 2;
             tail_prefetch<0, MI, 0, H>(ldc, tl, dst);
@@ -359,7 +388,8 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
 {
     static_assert(OP == FWD || OP == DW, "output-sparse dX is not handled here");
     static_assert(!SEEDED || OP == FWD, "only the forward kernel draws its own mask");
-    static_assert(!W_NK || (!RAGN && TAIL == kTailNone), "[N,K] weights: the plain products on whole tiles");
+    static_assert(TAIL != kTailBias16 || OP == FWD, "the 16-bit bias belongs to the forward product");
+    static_assert(!W_NK || (!RAGN && (TAIL == kTailNone || TAIL == kTailBias16)), "[N,K] weights: the plain products on whole tiles");
     static_assert(!W_NK || OP == FWD || (TM / WM / 32) % (128 / (32 * (int)sizeof(OutT))) == 0, "the transposed tile's rows must fill 128-byte pieces");
     constexpr int NW = WM * WN;
     static_assert(NW == 4, "one computing and one loading wavefront per SIMD");
@@ -660,18 +690,18 @@ __global__ __launch_bounds__(512) void dw_nk_kernel(GemmParams P)
     gemm_persistent_body<DW, T, OutT, TM, 256, 1, 4, kTailNone, false, false, true>(P, gridDim.x, blockIdx.x);
 }
 
-// eq. (1) with the weight as [N,K] (see W_NK above); SEEDED: it draws its own mask as well.
-template <class T, class OutT, int TM, bool SEEDED>
+// eq. (1) with the weight as [N,K] (see W_NK above); SEEDED: it draws its own mask as well; BIAS: plus a 16-bit bias.
+template <class T, class OutT, int TM, bool SEEDED, bool BIAS>
 __global__ __launch_bounds__(512) void fwd_nk_kernel(GemmParams P)
 {
-    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, kTailNone, false, SEEDED, true>(P, gridDim.x, blockIdx.x);
+    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, BIAS ? kTailBias16 : kTailNone, false, SEEDED, true>(P, gridDim.x, blockIdx.x);
 }
 
 // The forward kernel that draws its own mask and writes the mask object as well (see SEEDED above).
-template <class T, class OutT, int TM, bool RAGN>
+template <class T, class OutT, int TM, bool RAGN, bool BIAS>
 __global__ __launch_bounds__(512) void fwd_seeded_kernel(GemmParams P)
 {
-    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, kTailNone, RAGN, true>(P, gridDim.x, blockIdx.x);
+    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, BIAS ? kTailBias16 : kTailNone, RAGN, true>(P, gridDim.x, blockIdx.x);
 }
 
 // a[i] for a uniform index i in 0..3, as selects (keeps everything in scalar registers)

@@ -297,7 +297,7 @@ GemmParams base_params(int op, const void *a, const void *b, const void *mask, v
     P.splits = 1;
     P.total_tiles = 0;
     P.scale = (p < 1.0) ? (float)(1.0 / (1.0 - p)) : 0.0f;
-    P.bias = nullptr; P.aux = nullptr; P.act = SDROP_ACT_NONE;
+    P.bias = nullptr; P.bias16 = nullptr; P.aux = nullptr; P.act = SDROP_ACT_NONE;
     P.gate_mode = SDROP_GATE_RELU; P.C2 = nullptr;
     P.p = p;
     P.key0 = P.key1 = P.ctr2 = P.ctr3 = 0;
@@ -333,7 +333,7 @@ template <int OP>
 int run(const void *a, const void *b, const void *mask, void *out,
         int64_t M, int64_t K, int64_t N, int BM, int BK, double p,
         int dtype, int out_dtype, void *ws, size_t ws_bytes, void *stream,
-        const sdrop_epilogue_t *epi = nullptr, void *out2 = nullptr)
+        const sdrop_epilogue_t *epi = nullptr, void *out2 = nullptr, const void *bias16 = nullptr)
 {
     const int rc = check_gemm_args(a, b, mask, out, M, K, N, BM, BK, p, dtype, out_dtype);
     if (rc != SDROP_OK) return rc;
@@ -416,6 +416,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
         P.gate_mode = epi->gate_mode;
     }
     if (out2) P.C2 = static_cast<char *>(out2);
+    P.bias16 = static_cast<const char *>(bias16);
     if constexpr (OP == DW) {
         P.splits = dw_splits(M, N, BM, BK, K);
         if (P.splits > 1) {
@@ -449,9 +450,11 @@ bool fwd_seeded_applies(const sdrop_mask_layout_t &L)
 }
 
 // epi: null, or the weight layout and the leading dimensions of X, W and Y (nothing else of it may be set)
+// bias16: null, or N values of the operands' type that are added before the rounding (output of that type only)
 int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, void *y,
                    int64_t M, int64_t K, int64_t N, int BM, int BK, double p, uint64_t seed, uint64_t rng_stream,
-                   int dtype, int out_dtype, void *stream, const sdrop_epilogue_t *epi = nullptr, void *ws = nullptr, size_t ws_bytes = 0)
+                   int dtype, int out_dtype, void *stream, const sdrop_epilogue_t *epi = nullptr, void *ws = nullptr, size_t ws_bytes = 0,
+                   const void *bias16 = nullptr)
 {
     // every argument check of both calls before anything is enqueued
     const int rc = check_gemm_args(x, w, mask, y, M, K, N, BM, BK, p, dtype, out_dtype);
@@ -484,6 +487,7 @@ int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, 
         P.key0 = (uint32_t)seed; P.key1 = (uint32_t)(seed >> 32);
         P.ctr2 = (uint32_t)rng_stream; P.ctr3 = (uint32_t)(rng_stream >> 32);
         P.threshold = (uint64_t)floor(p * 4294967296.0);
+        P.bias16 = static_cast<const char *>(bias16);
         hipStream_t st = static_cast<hipStream_t>(stream);
         const bool o32 = out_dtype == SDROP_F32;
         const int rs = dtype == SDROP_F16 ? fwd_seeded_typed<F16>(o32, P, st) : fwd_seeded_typed<BF16>(o32, P, st);
@@ -491,7 +495,7 @@ int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, 
     }
     const int rm = sdrop_mask(mask, mask_bytes, M, K, BM, BK, p, seed, rng_stream, stream);
     if (rm != SDROP_OK) return rm;
-    return run<FWD>(x, w, mask, y, M, K, N, BM, BK, p, dtype, out_dtype, ws, ws_bytes, stream, epi);
+    return run<FWD>(x, w, mask, y, M, K, N, BM, BK, p, dtype, out_dtype, ws, ws_bytes, stream, epi, nullptr, bias16);
 }
 
 // both gradients in one launch where bwd_fused_kernel or bwd_fused_tile_kernel applies (128 x 128
@@ -769,6 +773,16 @@ int sdrop_fwd_seeded_ex(const void *X, const void *W, void *mask, size_t mask_by
 {
     return sdrop::run_fwd_seeded(X, W, mask, mask_bytes, Y, M, K, N, BM, BK, p, seed, rng_stream, dtype, out_dtype, stream,
                                  epi, ws, ws_bytes);
+}
+
+int sdrop_fwd_seeded_bias(const void *X, const void *W, const void *bias, void *mask, size_t mask_bytes, void *Y,
+                          int64_t M, int64_t K, int64_t N, int BM, int BK, double p, uint64_t seed, uint64_t rng_stream,
+                          int dtype, void *ws, size_t ws_bytes, void *stream, const sdrop_epilogue_t *epi)
+{
+    if (!bias) return SDROP_EINVAL;
+    if (reinterpret_cast<uintptr_t>(bias) % 16) return SDROP_EALIGN;
+    return sdrop::run_fwd_seeded(X, W, mask, mask_bytes, Y, M, K, N, BM, BK, p, seed, rng_stream, dtype, dtype, stream,
+                                 epi, ws, ws_bytes, bias);
 }
 
 int sdrop_bwd_dx(const void *dY, const void *W, const void *mask, void *dX,

@@ -24,10 +24,10 @@ MASK_NUNITS_OFFSET = 80
 
 EXPORTS = ("sdrop_strerror", "sdrop_last_hip_error", "sdrop_status", "sdrop_set_tuning", "sdrop_mask_layout", "sdrop_mask_bytes",
            "sdrop_mask", "sdrop_mask_split", "sdrop_mask_from_bits", "sdrop_mask_bits", "sdrop_workspace_bytes",
-           "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
+           "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_fwd_seeded_bias", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
            "sdrop_bwd", "sdrop_bwd_ex", "sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex", "sdrop_workspace_bytes_ex",
            "sdrop_producer", "sdrop_producer_ex",
-           "sdrop_bias_grad_workspace_bytes", "sdrop_bias_grad")
+           "sdrop_bias_grad_workspace_bytes", "sdrop_bias_grad", "sdrop_col_sum_workspace_bytes", "sdrop_col_sum")
 
 SCALE_DROPOUT, SCALE_ONE = 0, 1
 ACT_NONE, ACT_RELU, ACT_GELU_TANH, ACT_GELU_ERF = 0, 1, 2, 3
@@ -102,6 +102,9 @@ def lib():
         L.sdrop_fwd_seeded_ex.argtypes = [vp, vp, vp, sz, vp, i64, i64, i64, ci, ci, dbl, u64, u64, ci, ci, vp, sz, vp,
                                           ctypes.POINTER(Epilogue)]
         L.sdrop_fwd_seeded_ex.restype = ci
+        L.sdrop_fwd_seeded_bias.argtypes = [vp, vp, vp, vp, sz, vp, i64, i64, i64, ci, ci, dbl, u64, u64, ci, vp, sz, vp,
+                                            ctypes.POINTER(Epilogue)]
+        L.sdrop_fwd_seeded_bias.restype = ci
         L.sdrop_bwd_dw_static.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, ci, vp]
         L.sdrop_bwd_dw_static.restype = ci
         for name in ("sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex"):
@@ -122,6 +125,10 @@ def lib():
         L.sdrop_bias_grad_workspace_bytes.restype = sz
         L.sdrop_bias_grad.argtypes = [vp, vp, vp, i64, i64, ci, ci, ci, i64, vp, sz, vp]
         L.sdrop_bias_grad.restype = ci
+        L.sdrop_col_sum_workspace_bytes.argtypes = [i64, i64]
+        L.sdrop_col_sum_workspace_bytes.restype = sz
+        L.sdrop_col_sum.argtypes = [vp, vp, i64, i64, ci, i64, vp, sz, vp]
+        L.sdrop_col_sum.restype = ci
         _lib = L
     return _lib
 
@@ -371,10 +378,12 @@ def sdrop_fwd(X, W, mask, out_dtype=None, out=None, ws=None):
     return _gemm("sdrop_fwd", OP_FWD, X, W, mask, (M, N), M, K, N, out_dtype, out, ws)
 
 
-def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=None, out=None, w_layout=W_KN, ws=None):
+def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=None, out=None, w_layout=W_KN, ws=None,
+                     bias=None):
     """The step's mask and eq. (1) in one call (one launch for small block grids): returns (Y, Mask).
     The Mask is the object sdrop_mask would have written; the backward calls of the step take it.
-    w_layout=W_NK: W is given as [N, K].  Row-strided X, W or out (column ranges of wider matrices) are taken in place."""
+    w_layout=W_NK: W is given as [N, K].  Row-strided X, W or out (column ranges of wider matrices) are taken in place.
+    bias: None, or N values of X's type that are added to Y before its rounding (Y of X's type)."""
     M, K = X.shape
     K2, N = W.shape if w_layout == W_KN else (W.shape[1], W.shape[0])
     if K2 != K:
@@ -391,8 +400,10 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
         out = torch.empty((M, N), dtype=out_dtype, device=X.device)
     elif tuple(out.shape) != (M, N) or out.dtype != out_dtype:
         raise ValueError("out has the wrong shape or dtype")
+    if bias is not None and (bias.dtype != dtype or out_dtype != dtype or tuple(bias.shape) != (N,)):
+        raise ValueError("bias must have one value of the operands' and the output's dtype per output column")
     (xp, ldx), (wp, ldw), (yp, ldy) = _mat(X, "X"), _mat(W, "W"), _mat(out, "Y")
-    if w_layout == W_KN and (ldx, ldw, ldy) == (K, N, N):
+    if w_layout == W_KN and bias is None and (ldx, ldw, ldy) == (K, N, N):
         rc = lib().sdrop_fwd_seeded(xp, wp, _dev(m.buf, "mask"), m.buf.numel(), yp,
                                     M, K, N, BM, BK, float(p), int(seed), int(rng_stream),
                                     _DTYPES[dtype], _DTYPES[out_dtype], _stream())
@@ -404,9 +415,14 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
             ws = torch.empty(need, dtype=torch.uint8, device=X.device)
         ws_ptr = ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0)
         ws_bytes = ws.numel() * ws.element_size() if ws is not None else 0
-        rc = lib().sdrop_fwd_seeded_ex(xp, wp, _dev(m.buf, "mask"), m.buf.numel(), yp,
-                                       M, K, N, BM, BK, float(p), int(seed), int(rng_stream),
-                                       _DTYPES[dtype], _DTYPES[out_dtype], ws_ptr, ws_bytes, _stream(), ctypes.byref(e))
+        if bias is not None:
+            rc = lib().sdrop_fwd_seeded_bias(xp, wp, _dev(bias, "bias"), _dev(m.buf, "mask"), m.buf.numel(), yp,
+                                             M, K, N, BM, BK, float(p), int(seed), int(rng_stream),
+                                             _DTYPES[dtype], ws_ptr, ws_bytes, _stream(), ctypes.byref(e))
+        else:
+            rc = lib().sdrop_fwd_seeded_ex(xp, wp, _dev(m.buf, "mask"), m.buf.numel(), yp,
+                                           M, K, N, BM, BK, float(p), int(seed), int(rng_stream),
+                                           _DTYPES[dtype], _DTYPES[out_dtype], ws_ptr, ws_bytes, _stream(), ctypes.byref(e))
     _check(rc, "sdrop_fwd_seeded")
     return out, m
 
@@ -596,4 +612,23 @@ def sdrop_bias_grad(dZ, mask, out=None, ws=None):
                                ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0),
                                ws.numel() * ws.element_size() if ws is not None else 0, _stream())
     _check(rc, "sdrop_bias_grad")
+    return out
+
+
+def sdrop_col_sum(dY, out=None, ws=None):
+    """db[n] = sum_m dY[m, n], accumulated in fp32, rounded once to dY's type: the gradient of a layer's own bias.
+    dY [M, N] fp16 / bf16 with contiguous rows (a leading dimension is allowed)."""
+    M, N = dY.shape
+    if dY.dtype not in (torch.float16, torch.bfloat16):
+        raise SdropError(EDTYPE, "sdrop_col_sum")
+    if out is None:
+        out = torch.empty(N, dtype=dY.dtype, device=dY.device)
+    elif tuple(out.shape) != (N,) or out.dtype != dY.dtype:
+        raise ValueError("out must have one value of dY's dtype per column")
+    ptr, ld = _mat(dY, "dY")
+    if ws is None:
+        ws = torch.empty(max(int(lib().sdrop_col_sum_workspace_bytes(M, N)), 16), dtype=torch.uint8, device=dY.device)
+    rc = lib().sdrop_col_sum(ptr, _dev(out, "out"), M, N, _DTYPES[dY.dtype], ld, ctypes.c_void_p(ws.data_ptr()),
+                             ws.numel() * ws.element_size(), _stream())
+    _check(rc, "sdrop_col_sum")
     return out

@@ -1,0 +1,93 @@
+"""A layer's own bias in the forward kernel's epilogue (sdrop_fwd_seeded_bias) and its gradient (sdrop_col_sum): arxiv
+2411.01238, eq. (1) with the bias of the linear layer behind the dropout, against float64 and against the plain calls."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sdrop_oracle as orc
+from paper_2411_01238_amd import sdrop
+from paper_2411_01238_amd.autograd import SparseDropLinear
+from paper_2411_01238_amd.workloads import make_custom
+from _util import f64
+
+pytestmark = pytest.mark.gpu
+
+# unit spacing of the type relative to a value at the bottom of its binade: one rounding moves a value by at most half of it
+EPS = {"bf16": 2.0 ** -7, "f16": 2.0 ** -10}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,K,N,BM,BK,nk", [
+    (128, 128, 8, 128, 128, False),          # one tile, eight valid columns
+    (256, 256, 256, 64, 64, False),
+    (256, 384, 264, 128, 64, False),         # the last tile column eight wide
+    (192, 256, 1000, 64, 128, False),
+    (256, 256, 512, 128, 128, True),         # the weight as [N,K], in place
+    (128, 256, 256, 64, 64, True),
+    (256, 256, 72, 128, 128, True),          # ... through a transposed copy
+    (129 * 64, 128, 256, 64, 64, False),     # a grid too tall for the seeded form: mask, then the product
+    (129 * 64, 128, 520, 64, 64, False),
+    (129 * 128, 128, 256, 128, 128, True),
+])
+def test_forward_with_bias(M, K, N, BM, BK, nk, dtype):
+    p = 0.4
+    print("bias case", M, K, N, BM, BK, nk, dtype, flush=True)
+    X, W, _ = make_custom(M, K, N, dtype, seed=7)
+    g = torch.Generator().manual_seed(1)
+    b = torch.randn(N, generator=g).to(X.dtype)
+    Wg = (W.t().contiguous() if nk else W).cuda()
+    lay = sdrop.W_NK if nk else sdrop.W_KN
+    guard = torch.full((M + 2, N), 7.0, dtype=X.dtype, device="cuda")
+    y, m = sdrop.sdrop_fwd_seeded(X.cuda(), Wg, BM, BK, p, 3, 1, w_layout=lay, bias=b.cuda(), out=guard[1:M + 1])
+    y0, m0 = sdrop.sdrop_fwd_seeded(X.cuda(), Wg, BM, BK, p, 3, 1, w_layout=lay, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert bool((guard[0] == 7).all()) and bool((guard[M + 1] == 7).all())
+    assert torch.equal(m.bits(), m0.bits())
+    # the fp32 output of the plain call plus the bias, rounded once.  The kernel scales and adds in one fused operation,
+    # so its fp32 sum lacks the rounding of the product (2^-24 of it) that y0 carries: half an ulp of the output plus that
+    s = y0.double() + b.cuda().double()
+    assert bool(((y.double() - s).abs() <= 0.5 * EPS[dtype] * s.abs() + 2.0 ** -23 * y0.double().abs() + 2.0 ** -25).all())
+    keep = orc.mask(M // BM, K // BK, p, 3, 1)
+    if M <= 256:
+        ref = orc.fwd(f64(X), f64(W), keep, BM, BK, p) + f64(b)
+        assert np.all(np.abs(f64(y) - ref) <= 0.5 * EPS[dtype] * np.abs(ref) + 2e-5 * np.max(np.abs(ref)))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("M,N,ld", [(1, 8, 8), (7, 64, 64), (64, 72, 72), (33, 128, 136), (300, 136, 136), (4096, 72, 72),
+                                    (1000, 1000, 1024), (2048, 264, 264), (16384, 3072, 3072)])
+def test_column_sums(M, N, ld, dtype):
+    print("col_sum case", M, N, ld, dtype, flush=True)
+    g = torch.Generator().manual_seed(M + N)
+    d = torch.randn(M, N, generator=g).to(dtype)
+    wide = torch.full((M, ld), float("nan"), dtype=dtype, device="cuda")
+    wide[:, :N] = d.cuda()
+    got = sdrop.sdrop_col_sum(wide[:, :N])
+    ref = d.to(torch.float64).sum(0)
+    # one rounding to the output type, plus fp32 sums in chains of at most M / 256 + 64 additions (rows of a thread, row
+    # groups of a workgroup, parts), each off by 2^-24 of a partial sum that the sum of the magnitudes bounds
+    eps = 0.5 * EPS["bf16" if dtype == torch.bfloat16 else "f16"]
+    bound = eps * ref.abs() + 2.0 ** -24 * (M / 256 + 64) * d.to(torch.float64).abs().sum(0)
+    assert bool(((got.cpu().to(torch.float64) - ref).abs() <= bound * 1.01).all())
+    assert torch.equal(got, sdrop.sdrop_col_sum(wide[:, :N]))
+
+
+@pytest.mark.parametrize("bias_dtype", [torch.bfloat16, torch.float32])
+def test_layer_gradients_and_the_forms_that_stay_torch(bias_dtype):
+    torch.manual_seed(0)
+    layer = SparseDropLinear(256, 72, p=0.5, BM=64, BK=64, bias=True, seed=2)
+    layer.bias.data = torch.randn(72, device="cuda").to(bias_dtype)         # fp32: added as a torch operation, the output is fp32
+    x = torch.randn(128, 256, device="cuda", dtype=torch.bfloat16, requires_grad=True)
+    y = layer(x)
+    assert y.dtype == bias_dtype
+    dy = torch.randn(128, 72, device="cuda", dtype=y.dtype)
+    dx, dw, db = torch.autograd.grad(y, [x, layer.weight, layer.bias], dy)
+    assert db.dtype == bias_dtype
+    ref = f64(dy).sum(0)
+    assert np.all(np.abs(f64(db) - ref) <= 0.5 * EPS["bf16"] * np.abs(ref) + 1e-5)
+    # the gradient of the bias is linear in dy and can be differentiated again
+    dy.requires_grad_(True)
+    layer.calls = 0
+    (db2,) = torch.autograd.grad(layer(x), [layer.bias], dy, create_graph=True)
+    (ddy,) = torch.autograd.grad(db2.float().sum(), [dy])
+    assert bool((ddy == 1).all())

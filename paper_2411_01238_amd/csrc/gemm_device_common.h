@@ -89,6 +89,9 @@ constexpr int kThreads = 256;    // 4 wavefronts per workgroup
 // LDS stages: three for tiles of 128 rows (one workgroup per CU; the deeper prefetch measured
 // faster than two co-resident workgroups with two stages: 93 vs 120 us for dX at 4096^3, p=0.5);
 // two for tiles of 64 rows, so that two or three workgroups share a CU (measured faster there).
+// The persistent kernels: three stages and 16 KB of output staging.  (A fourth stage, which 128 x 128 tiles have room for,
+// changed no time of theirs by more than 3 % either way, forward and dX, K or N of 512 to 4096.)
+constexpr int persistent_lds(int tm, int tn) { return 3 * (tm + tn) * TK * 2 + 4 * 4096; }
 constexpr int stages_for(int tm, int tn) { return (void)tn, tm <= 64 ? 2 : 3; }
 
 // A value that is the same in every lane, told to the compiler (it then lives in a scalar register

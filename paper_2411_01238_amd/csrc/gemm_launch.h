@@ -61,7 +61,7 @@ int launch_t(const GemmParams &P, int grid, bool ragged, hipStream_t stream, boo
         // the persistent form also has a variant for a ragged last tile column, without a tail
         if ((!ragged || !TAIL) && persistent_ok) {
             // persistent form: three operand stages plus 4 KiB of output staging per computing wavefront
-            constexpr int P_LDS = 3 * (TM + TN) * TK * 2 + WM * WN * 4096;
+            constexpr int P_LDS = persistent_lds(TM, TN);
             auto k_whole = gemm_persistent_kernel<OP, T, OutT, TM, TN, WM, WN, TMODE, false>;
             auto k_edge = gemm_persistent_kernel<OP, T, OutT, TM, TN, WM, WN, TMODE, !TAIL>;    // (the same kernel when there is a tail)
             static int pers_ok = -1;    // per instantiation: does the device grant that much LDS?
@@ -92,12 +92,12 @@ int launch_t(const GemmParams &P, int grid, bool ragged, hipStream_t stream, boo
 // The forward kernel that draws its own mask and writes the mask object (block grids of at most 128 x 64; whole
 // tiles or a ragged last tile column).  Returns -1 when the device does not grant the LDS.
 // BIAS: plus the 16-bit bias P.bias16.
-template <class T, class OutT, int TM, bool BIAS = false>
+template <class T, class OutT, int TM, int TN = 256, bool BIAS = false>
 int launch_fwd_seeded(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
-    auto k_whole = fwd_seeded_kernel<T, OutT, TM, false, BIAS>;
-    auto k_edge = fwd_seeded_kernel<T, OutT, TM, true, BIAS>;
+    constexpr int P_LDS = persistent_lds(TM, TN);
+    auto k_whole = fwd_seeded_kernel<T, OutT, TM, TN, false, BIAS>;
+    auto k_edge = fwd_seeded_kernel<T, OutT, TM, TN, true, BIAS>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -108,23 +108,23 @@ int launch_fwd_seeded(const GemmParams &P, hipStream_t stream)
     }
     if (!ok) return -1;
     GemmParams Q = P;
-    Q.n_tiles = (int)((P.N + 255) / 256);
+    Q.n_tiles = (int)((P.N + TN - 1) / TN);
     Q.splits = 1;
     Q.total_tiles = Q.MB * Q.n_tiles;
     const int ncu = cu_count();
-    auto k = P.N % 256 != 0 ? k_edge : k_whole;
+    auto k = P.N % TN != 0 ? k_edge : k_whole;
     hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
     return hip_status(hipGetLastError());
 }
 
-// eq. (1) plus the 16-bit bias P.bias16, with a mask object and a [K,N] weight (whole tiles or a ragged last tile
-// column).  Returns -1 when the device does not grant the LDS.
-template <class T, class OutT, int TM>
-int launch_fwd_bias(const GemmParams &P, hipStream_t stream)
+// eq. (1), plus the 16-bit bias P.bias16 with BIAS, with a mask object and a [K,N] weight (whole tiles or a ragged last
+// tile column).  Returns -1 when the device does not grant the LDS.
+template <class T, class OutT, int TM, int TN, bool BIAS>
+int launch_fwd_plain(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
-    auto k_whole = gemm_persistent_kernel<FWD, T, OutT, TM, 256, 1, 4, kTailBias16, false>;
-    auto k_edge = gemm_persistent_kernel<FWD, T, OutT, TM, 256, 1, 4, kTailBias16, true>;
+    constexpr int P_LDS = persistent_lds(TM, TN), WM = TN == 256 ? 1 : 2, WN = 4 / WM;
+    auto k_whole = gemm_persistent_kernel<FWD, T, OutT, TM, TN, WM, WN, BIAS ? kTailBias16 : kTailNone, false>;
+    auto k_edge = gemm_persistent_kernel<FWD, T, OutT, TM, TN, WM, WN, BIAS ? kTailBias16 : kTailNone, true>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -135,22 +135,22 @@ int launch_fwd_bias(const GemmParams &P, hipStream_t stream)
     }
     if (!ok) return -1;
     GemmParams Q = P;
-    Q.n_tiles = (int)((P.N + 255) / 256);
+    Q.n_tiles = (int)((P.N + TN - 1) / TN);
     Q.splits = 1;
     Q.total_tiles = Q.MB * Q.n_tiles;
     const int ncu = cu_count();
-    auto k = P.N % 256 != 0 ? k_edge : k_whole;
+    auto k = P.N % TN != 0 ? k_edge : k_whole;
     hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
     return hip_status(hipGetLastError());
 }
 
 // eq. (1) with the weight as [N,K], read in place (N a multiple of 256, no tail but the 16-bit bias with BIAS); SEEDED:
 // the mask drawn in the same launch (block grids of at most 128 x 64).  Returns -1 when the device does not grant the LDS.
-template <class T, class OutT, int TM, bool SEEDED = false, bool BIAS = false>
+template <class T, class OutT, int TM, int TN = 256, bool SEEDED = false, bool BIAS = false>
 int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
-    auto k = fwd_nk_kernel<T, OutT, TM, SEEDED, BIAS>;
+    constexpr int P_LDS = persistent_lds(TM, TN);
+    auto k = fwd_nk_kernel<T, OutT, TM, TN, SEEDED, BIAS>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -159,7 +159,7 @@ int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
     }
     if (!ok) return -1;
     GemmParams Q = P;
-    Q.n_tiles = (int)(P.N / 256);
+    Q.n_tiles = (int)(P.N / TN);
     Q.splits = 1;
     Q.total_tiles = Q.MB * Q.n_tiles;
     const int ncu = cu_count();
@@ -171,7 +171,7 @@ int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
 template <class T, class OutT, int TM>
 int launch_dw_nk(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (TM + 256) * TK * 2 + 4 * 4096;
+    constexpr int P_LDS = persistent_lds(TM, 256);
     auto k = dw_nk_kernel<T, OutT, TM>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
@@ -213,7 +213,7 @@ int launch_dx_persistent(const GemmParams &P, hipStream_t stream)
 template <class T, class OutT, int TN, int TAIL>
 int launch_dx_persistent_t(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (128 + TN) * TK * 2 + 4 * 4096;
+    constexpr int P_LDS = persistent_lds(128, TN);
     // two forms: N a multiple of the 64-wide slice, or with a ragged last slice
     auto k_whole = gemm_persistent_dx_kernel<T, OutT, 128, TN, 2, 2, TAIL, false>;
     auto k_ragged = gemm_persistent_dx_kernel<T, OutT, 128, TN, 2, 2, TAIL, true>;
@@ -237,7 +237,7 @@ int launch_dx_persistent_t(const GemmParams &P, hipStream_t stream)
 template <class T, class OutT>
 int launch_dx_pairs(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (128 + 256) * TK * 2 + 4 * 4096;
+    constexpr int P_LDS = persistent_lds(128, 256);
     auto k = gemm_persistent_dx_kernel<T, OutT, 128, 256, 2, 2, kTailNone, false, true>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
@@ -256,7 +256,7 @@ int launch_dx_pairs(const GemmParams &P, hipStream_t stream)
 template <class T, class OutT>
 int launch_dx_nk(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = 3 * (128 + 128) * TK * 2 + 4 * 4096;
+    constexpr int P_LDS = persistent_lds(128, 128);
     auto k = gemm_persistent_dx_kernel<T, OutT, 128, 128, 2, 2, kTailNone, false, false, true>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
@@ -301,19 +301,27 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
         }
     }
     if constexpr (OP == FWD) {
+        const bool narrow = !has_tail(P) && fwd_narrow(P);
         if (P.bias16) {
             if constexpr (sizeof(OutT) == 2) {
                 int rc;
-                if (P.w_nk) rc = P.BM == 128 ? launch_fwd_nk<T, OutT, 128, false, true>(P, stream) : launch_fwd_nk<T, OutT, 64, false, true>(P, stream);
-                else rc = P.BM == 128 ? launch_fwd_bias<T, OutT, 128>(P, stream) : launch_fwd_bias<T, OutT, 64>(P, stream);
+                if (P.w_nk) rc = narrow ? launch_fwd_nk<T, OutT, 128, 128, false, true>(P, stream)
+                               : P.BM == 128 ? launch_fwd_nk<T, OutT, 128, 256, false, true>(P, stream) : launch_fwd_nk<T, OutT, 64, 256, false, true>(P, stream);
+                else rc = narrow ? launch_fwd_plain<T, OutT, 128, 128, true>(P, stream)
+                        : P.BM == 128 ? launch_fwd_plain<T, OutT, 128, 256, true>(P, stream) : launch_fwd_plain<T, OutT, 64, 256, true>(P, stream);
                 return rc == -1 ? SDROP_EHIP : rc;
             } else {
                 return SDROP_EDTYPE;         // (the output has the bias's type: checked at the entry point)
             }
         }
         if (P.w_nk) {
-            const int rc = P.BM == 128 ? launch_fwd_nk<T, OutT, 128>(P, stream) : launch_fwd_nk<T, OutT, 64>(P, stream);
+            const int rc = narrow ? launch_fwd_nk<T, OutT, 128, 128>(P, stream)
+                         : P.BM == 128 ? launch_fwd_nk<T, OutT, 128>(P, stream) : launch_fwd_nk<T, OutT, 64>(P, stream);
             return rc == -1 ? SDROP_EHIP : rc;       // (the [K,N] persistent form needs the same LDS)
+        }
+        if (narrow) {
+            const int rc = launch_fwd_plain<T, OutT, 128, 128, false>(P, stream);
+            if (rc != -1) return rc;
         }
         P.n_tiles = (int)((P.N + 255) / 256);
         const int grid = P.MB * P.n_tiles;
@@ -366,7 +374,7 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
 template <class T, class OutDX, class OutDW, int TN_DX, bool PAIRS = false, bool W_NK = false>
 int launch_bwd_fused(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream)
 {
-    constexpr int LDS_DX = 3 * (128 + TN_DX) * TK * 2 + 4 * 4096, LDS_DW = 3 * (128 + 256) * TK * 2 + 4 * 4096;
+    constexpr int LDS_DX = persistent_lds(128, TN_DX), LDS_DW = persistent_lds(128, 256);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
     auto k = bwd_fused_kernel<T, OutDX, OutDW, TN_DX, PAIRS, W_NK>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
@@ -439,15 +447,20 @@ template <int OP, class T> int dispatch_typed(bool o32, GemmParams &P, hipStream
 template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream_t stream)
 {
     using O16 = typename In<T>::out16;
+    const bool narrow = fwd_narrow(P);
     if (P.bias16) {
         if (o32) return SDROP_EDTYPE;
-        if (P.w_nk) return P.BM == 128 ? launch_fwd_nk<T, O16, 128, true, true>(P, stream) : launch_fwd_nk<T, O16, 64, true, true>(P, stream);
-        return P.BM == 128 ? launch_fwd_seeded<T, O16, 128, true>(P, stream) : launch_fwd_seeded<T, O16, 64, true>(P, stream);
+        if (P.w_nk) return narrow ? launch_fwd_nk<T, O16, 128, 128, true, true>(P, stream)
+                         : P.BM == 128 ? launch_fwd_nk<T, O16, 128, 256, true, true>(P, stream) : launch_fwd_nk<T, O16, 64, 256, true, true>(P, stream);
+        return narrow ? launch_fwd_seeded<T, O16, 128, 128, true>(P, stream)
+             : P.BM == 128 ? launch_fwd_seeded<T, O16, 128, 256, true>(P, stream) : launch_fwd_seeded<T, O16, 64, 256, true>(P, stream);
     }
     if (P.w_nk) {
-        if (P.BM == 128) return o32 ? launch_fwd_nk<T, float, 128, true>(P, stream) : launch_fwd_nk<T, O16, 128, true>(P, stream);
-        return o32 ? launch_fwd_nk<T, float, 64, true>(P, stream) : launch_fwd_nk<T, O16, 64, true>(P, stream);
+        if (narrow) return o32 ? launch_fwd_nk<T, float, 128, 128, true>(P, stream) : launch_fwd_nk<T, O16, 128, 128, true>(P, stream);
+        if (P.BM == 128) return o32 ? launch_fwd_nk<T, float, 128, 256, true>(P, stream) : launch_fwd_nk<T, O16, 128, 256, true>(P, stream);
+        return o32 ? launch_fwd_nk<T, float, 64, 256, true>(P, stream) : launch_fwd_nk<T, O16, 64, 256, true>(P, stream);
     }
+    if (narrow) return o32 ? launch_fwd_seeded<T, float, 128, 128>(P, stream) : launch_fwd_seeded<T, O16, 128, 128>(P, stream);
     if (P.BM == 128) return o32 ? launch_fwd_seeded<T, float, 128>(P, stream) : launch_fwd_seeded<T, O16, 128>(P, stream);
     return o32 ? launch_fwd_seeded<T, float, 64>(P, stream) : launch_fwd_seeded<T, O16, 64>(P, stream);
 }

@@ -691,17 +691,17 @@ __global__ __launch_bounds__(512) void dw_nk_kernel(GemmParams P)
 }
 
 // eq. (1) with the weight as [N,K] (see W_NK above); SEEDED: it draws its own mask as well; BIAS: plus a 16-bit bias.
-template <class T, class OutT, int TM, bool SEEDED, bool BIAS>
+template <class T, class OutT, int TM, int TN, bool SEEDED, bool BIAS>
 __global__ __launch_bounds__(512) void fwd_nk_kernel(GemmParams P)
 {
-    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, BIAS ? kTailBias16 : kTailNone, false, SEEDED, true>(P, gridDim.x, blockIdx.x);
+    gemm_persistent_body<FWD, T, OutT, TM, TN, TN == 256 ? 1 : 2, TN == 256 ? 4 : 2, BIAS ? kTailBias16 : kTailNone, false, SEEDED, true>(P, gridDim.x, blockIdx.x);
 }
 
 // The forward kernel that draws its own mask and writes the mask object as well (see SEEDED above).
-template <class T, class OutT, int TM, bool RAGN, bool BIAS>
+template <class T, class OutT, int TM, int TN, bool RAGN, bool BIAS>
 __global__ __launch_bounds__(512) void fwd_seeded_kernel(GemmParams P)
 {
-    gemm_persistent_body<FWD, T, OutT, TM, 256, 1, 4, BIAS ? kTailBias16 : kTailNone, RAGN, true>(P, gridDim.x, blockIdx.x);
+    gemm_persistent_body<FWD, T, OutT, TM, TN, TN == 256 ? 1 : 2, TN == 256 ? 4 : 2, BIAS ? kTailBias16 : kTailNone, RAGN, true>(P, gridDim.x, blockIdx.x);
 }
 
 // a[i] for a uniform index i in 0..3, as selects (keeps everything in scalar registers)

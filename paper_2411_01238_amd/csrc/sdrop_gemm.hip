@@ -250,6 +250,21 @@ DxPlan dx_plan(const GemmParams &P, bool fused)
     return plan;
 }
 
+// eq. (1) with 128-row blocks on 128 x 128 tiles (WM = WN = 2) instead of 128 x 256: where the wide tiles leave the chip at
+// most half full.  A workgroup's time is that of its tile's slices, 0.6 us each for a wide tile and 0.37 for a narrow one
+// on a chip with CUs to spare, so halving the tile shortens the launch although it adds a third to the operand traffic.
+// Measured, wide -> narrow, us (bf16, seeded forward, half the blocks kept): 1024^3 11.1 -> 8.5; 4096 x 1024 x 72
+// 15.6 -> 12.1; 4096 x 1024 x 1024 (128 wide tiles) 15.2 -> 12.1; 4096^2 x 512 32.9 -> 23.6; 4096^2 x 768 32.9 -> 28.8;
+// 4096^2 x 1024 33.1 -> 31.3.  With all blocks kept: 4096^2 x 512 (64 wide tiles) 40.1 -> 34.1, x 768 (96) 40.3 -> 36.5,
+// x 1024 (128) 41.4 -> 43.6: between three eighths and half of the chip only with a dropout rate that leaves the rows'
+// counts uneven.  Beyond half of the chip a second round of narrow tiles loses to one of wide ones (160 wide tiles, all
+// kept, K = 1024: 16.1 -> 20.6).
+bool fwd_narrow(const GemmParams &P)
+{
+    const int64_t wide = P.MB * ((P.N + 255) / 256), ncu = cu_count();
+    return P.BM == 128 && (wide * 8 <= ncu * 3 || (wide * 2 <= ncu && P.p >= 0.1));
+}
+
 // Which calls read a weight given as [N,K] in place instead of through a transposed copy: eq. (1) on whole 256-wide
 // tile columns (its persistent kernel loads W's rows the way eq. 2 loads its operands), and eq. (3) on whole tile
 // columns where it runs its persistent kernel (which writes its tiles transposed), and eq. (2) with 128 x 128 blocks

@@ -168,11 +168,11 @@ int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
 }
 
 // eq. (3) with the gradient written as [N,K] (tiles of TM = BK rows, N a multiple of 256; P.splits parts).
-template <class T, class OutT, int TM>
+template <class T, class OutT, int TM, int TN = 256>
 int launch_dw_nk(const GemmParams &P, hipStream_t stream)
 {
-    constexpr int P_LDS = persistent_lds(TM, 256);
-    auto k = dw_nk_kernel<T, OutT, TM>;
+    constexpr int P_LDS = persistent_lds(TM, TN);
+    auto k = dw_nk_kernel<T, OutT, TM, TN>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -181,9 +181,35 @@ int launch_dw_nk(const GemmParams &P, hipStream_t stream)
     }
     if (!ok) return -1;
     GemmParams Q = P;
-    Q.n_tiles = (int)(P.N / 256);
+    Q.n_tiles = (int)(P.N / TN);
     Q.total_tiles = Q.KB * Q.n_tiles * Q.splits;
     const int ncu = cu_count();
+    hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
+    return hip_status(hipGetLastError());
+}
+
+// eq. (3) with 128-wide blocks on 128 x 128 tiles (whole or a ragged last tile column; P.splits parts in planes or P.folds
+// in the accumulators).  Returns -1 when the device does not grant the LDS.
+template <class T, class OutT>
+int launch_dw_narrow(const GemmParams &P, hipStream_t stream)
+{
+    constexpr int P_LDS = persistent_lds(128, 128);
+    auto k_whole = gemm_persistent_kernel<DW, T, OutT, 128, 128, 2, 2, kTailNone, false>;
+    auto k_edge = gemm_persistent_kernel<DW, T, OutT, 128, 128, 2, 2, kTailNone, true>;
+    static int ok = -1;     // per instantiation: does the device grant that much LDS?
+    if (ok < 0) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        ok = (e == hipSuccess);
+        if (!ok) (void)hipGetLastError();
+    }
+    if (!ok) return -1;
+    GemmParams Q = P;
+    Q.n_tiles = (int)((P.N + 127) / 128);
+    Q.total_tiles = Q.KB * Q.n_tiles * Q.splits;
+    const int ncu = cu_count();
+    auto k = P.N % 128 != 0 ? k_edge : k_whole;
     hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
     return hip_status(hipGetLastError());
 }
@@ -330,8 +356,13 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
         return launch<FWD, T, OutT, 64, 256, 1, 4>(P, grid, ragged, stream);
     } else if constexpr (OP == DW) {
         if (P.w_nk) {
-            const int rc = P.BK == 128 ? launch_dw_nk<T, OutT, 128>(P, stream) : launch_dw_nk<T, OutT, 64>(P, stream);
+            const int rc = P.dw_narrow ? launch_dw_nk<T, OutT, 128, 128>(P, stream)
+                         : P.BK == 128 ? launch_dw_nk<T, OutT, 128>(P, stream) : launch_dw_nk<T, OutT, 64>(P, stream);
             return rc == -1 ? SDROP_EHIP : rc;
+        }
+        if (P.dw_narrow) {
+            const int rc = launch_dw_narrow<T, OutT>(P, stream);
+            return rc == -1 ? SDROP_EHIP : rc;           // (half of what the 128 x 256 form needs)
         }
         P.n_tiles = (int)((P.N + 255) / 256);
         const int grid = P.KB * P.n_tiles * P.splits;
@@ -371,12 +402,12 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
     }
 }
 
-template <class T, class OutDX, class OutDW, int TN_DX, bool PAIRS = false, bool W_NK = false>
+template <class T, class OutDX, class OutDW, int TN_DX, bool PAIRS = false, bool W_NK = false, int TN_DW = 256>
 int launch_bwd_fused(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream)
 {
-    constexpr int LDS_DX = persistent_lds(128, TN_DX), LDS_DW = persistent_lds(128, 256);
+    constexpr int LDS_DX = persistent_lds(128, TN_DX), LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
-    auto k = bwd_fused_kernel<T, OutDX, OutDW, TN_DX, PAIRS, W_NK>;
+    auto k = bwd_fused_kernel<T, OutDX, OutDW, TN_DX, PAIRS, W_NK, TN_DW>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -392,12 +423,12 @@ int launch_bwd_fused(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t s
     return hip_status(hipGetLastError());
 }
 
-template <class T, class OutDX, class OutDW>
+template <class T, class OutDX, class OutDW, int TN_DW = 256>
 int launch_bwd_fused_tile(const GemmParams &Pdx, const GemmParams &Pdw, int n_dx, hipStream_t stream)
 {
-    constexpr int LDS_DX = 3 * (128 + 256) * TK * 2, LDS_DW = 3 * (128 + 256) * TK * 2 + 4 * 4096;
+    constexpr int LDS_DX = 3 * (128 + 256) * TK * 2, LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
-    auto k = bwd_fused_tile_kernel<T, OutDX, OutDW>;
+    auto k = bwd_fused_tile_kernel<T, OutDX, OutDW, TN_DW>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -414,6 +445,14 @@ int launch_bwd_fused_tile(const GemmParams &Pdx, const GemmParams &Pdw, int n_dx
 template <class T, class OutDX, class OutDW>
 int launch_bwd_fused_tn(int TN, const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream)
 {
+    if constexpr (sizeof(OutDX) == sizeof(OutDW)) {      // (128-wide dW tiles here only without planes of partial sums)
+        if (Pdw.dw_narrow) {
+            if (TN == kTNPairs) return launch_bwd_fused<T, OutDX, OutDW, 256, true, false, 128>(Pdx, Pdw, stream);
+            if (TN == kTNNK) return launch_bwd_fused<T, OutDX, OutDW, 128, false, true, 128>(Pdx, Pdw, stream);
+            if (TN == 128) return launch_bwd_fused<T, OutDX, OutDW, 128, false, false, 128>(Pdx, Pdw, stream);
+            return -1;
+        }
+    }
     if (TN == kTNPairs) return launch_bwd_fused<T, OutDX, OutDW, 256, true>(Pdx, Pdw, stream);
     if (TN == kTNNK) return launch_bwd_fused<T, OutDX, OutDW, 128, false, true>(Pdx, Pdw, stream);
     if (TN == 256) return launch_bwd_fused<T, OutDX, OutDW, 256>(Pdx, Pdw, stream);
@@ -473,7 +512,12 @@ template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, 
         using ODX = decltype(odx);
         using ODW = decltype(odw);
         if (form == kBwdPersistent) return launch_bwd_fused_tn<T, ODX, ODW>(TN, Pdx, Pdw, stream);
-        if (form == kBwdTile128) return launch_bwd_fused_tile<T, ODX, ODW>(Pdx, Pdw, n_dx, stream);
+        if (form == kBwdTile128) {
+            if constexpr (sizeof(ODX) == sizeof(ODW)) {
+                if (Pdw.dw_narrow) return launch_bwd_fused_tile<T, ODX, ODW, 128>(Pdx, Pdw, n_dx, stream);
+            }
+            return launch_bwd_fused_tile<T, ODX, ODW>(Pdx, Pdw, n_dx, stream);
+        }
         if (TN == 256) return launch_bwd_fused_tile64<T, ODX, ODW, 256>(Pdx, Pdw, n_dx, Pdw.total_tiles, stream);
         return launch_bwd_fused_tile64<T, ODX, ODW, 128>(Pdx, Pdw, n_dx, Pdw.total_tiles, stream);
     };

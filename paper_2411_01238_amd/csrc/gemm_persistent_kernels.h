@@ -35,6 +35,23 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
     }
+    // The sums of the parts of a reduction that are done (see FOLDS): adds the accumulators' part to them and clears the
+    // accumulators, or, after the last part, leaves the whole sum in the accumulators.
+    f32x16 done[MI][NI];
+    __device__ __forceinline__ void fold(bool first_part, bool last_part)
+    {
+        if (first_part && last_part) return;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float v = first_part ? acc[mi][ni][r] : done[mi][ni][r] + acc[mi][ni][r];
+                    done[mi][ni][r] = v;
+                    acc[mi][ni][r] = last_part ? v : 0.f;
+                }
+    }
     // operands of the first quarter of the slice in stage `st`
     __device__ __forceinline__ void first(const char *st)
     {
@@ -396,6 +413,10 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
     constexpr int WTM = TM / WM, WTN = TN / WN, MI = WTM / 32, NI = WTN / 32;
     constexpr bool A_KMAJ = (OP == FWD), A_TR = !A_KMAJ, B_TR = !(W_NK && OP == FWD);
     constexpr bool OUT_T = W_NK && OP == DW;             // the output tile is written transposed
+    // 128 x 128 tiles of eq. (3): the parts that a split reduction would give to several workgroups and a summing pass are
+    // summed here one after the other, in a second set of accumulators (the tile's own are half a wide tile's), in the
+    // summing pass's order: the same bits without the fp32 planes' 2 x 4 bytes per part and output and without its launch.
+    constexpr bool FOLDS = OP == DW && TM == 128 && TN == 128;
     constexpr int A_BYTES = TM * TK * 2, B_BYTES = TN * TK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
     constexpr int STAGES = 3, AHEAD = 2;
     constexpr int ESZ = (int)sizeof(OutT);
@@ -652,9 +673,20 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
             gcol0 = (int64_t)nt * TN + wn * WTN + nj * (128 / ESZ);
             return c_tile + (int64_t)(mi * 32) * ldc + nj * 128;
         };
-        for (int s = 0; s < nsteps; ++s) {
-            cw.template slice<OUT_T>(stage_ptr(st0), stage_ptr(st1));
-            const int t0 = st0; st0 = st1; st1 = st2; st2 = t0;
+        if constexpr (FOLDS) {
+            for (int f = 0, s = 0; f < P.folds; ++f) {
+                const int end = (int)((int64_t)len0 * (f + 1) / P.folds) << sub_shift;
+                for (; s < end; ++s) {
+                    cw.template slice<OUT_T>(stage_ptr(st0), stage_ptr(st1));
+                    const int t0 = st0; st0 = st1; st1 = st2; st2 = t0;
+                }
+                cw.fold(f == 0, f + 1 == P.folds);
+            }
+        } else {
+            for (int s = 0; s < nsteps; ++s) {
+                cw.template slice<OUT_T>(stage_ptr(st0), stage_ptr(st1));
+                const int t0 = st0; st0 = st1; st1 = st2; st2 = t0;
+            }
         }
         if constexpr (!SEEDED) {
             // the look-ups have had the whole tile to arrive and no store is in flight: this wait is free
@@ -684,10 +716,10 @@ __global__ __launch_bounds__(WM * WN * 128) void gemm_persistent_kernel(GemmPara
 }
 
 // eq. (3) with the gradient written as [N,K] (see W_NK above).
-template <class T, class OutT, int TM>
+template <class T, class OutT, int TM, int TN>
 __global__ __launch_bounds__(512) void dw_nk_kernel(GemmParams P)
 {
-    gemm_persistent_body<DW, T, OutT, TM, 256, 1, 4, kTailNone, false, false, true>(P, gridDim.x, blockIdx.x);
+    gemm_persistent_body<DW, T, OutT, TM, TN, TN == 256 ? 1 : 2, TN == 256 ? 4 : 2, kTailNone, false, false, true>(P, gridDim.x, blockIdx.x);
 }
 
 // eq. (1) with the weight as [N,K] (see W_NK above); SEEDED: it draws its own mask as well; BIAS: plus a 16-bit bias.
@@ -1123,25 +1155,26 @@ __global__ __launch_bounds__(WM * WN * 128) void gemm_persistent_dx_kernel(GemmP
 // idle tail between the two.  The dX workgroups come first, so dX workgroup w is workgroup w of
 // the launch and runs on XCD w % 8, which its schedule assumes; the dW schedule assumes nothing.
 // (W_NK: the weight is given and its gradient wanted as [N,K]; both bodies in their in-place forms.)
-template <class T, class OutDX, class OutDW, int TN_DX, bool PAIRS = false, bool W_NK = false>
+// TN_DW: dW's tiles (see DwPlan).
+template <class T, class OutDX, class OutDW, int TN_DX, bool PAIRS, bool W_NK, int TN_DW>
 __global__ __launch_bounds__(512) void bwd_fused_kernel(GemmParams Pdx, GemmParams Pdw, int g_dx)
 {
     if ((int)blockIdx.x < g_dx)
         gemm_persistent_dx_body<T, OutDX, 128, TN_DX, 2, 2, kTailNone, false, PAIRS, W_NK>(Pdx, g_dx, (int)blockIdx.x);
     else
-        gemm_persistent_body<DW, T, OutDW, 128, 256, 1, 4, kTailNone, false, false, W_NK>(Pdw, (int)gridDim.x - g_dx, (int)blockIdx.x - g_dx);
+        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone, false, false, W_NK>(Pdw, (int)gridDim.x - g_dx, (int)blockIdx.x - g_dx);
 }
 
 // The same where dX runs one workgroup per tile (tiles of two kept blocks that are too few per CU
 // for the persistent kernel): workgroups [0, n_dx) are those tiles, in the order of the separate
 // launch, the rest the persistent dW kernel.
-template <class T, class OutDX, class OutDW>
+template <class T, class OutDX, class OutDW, int TN_DW>
 __global__ __launch_bounds__(512) void bwd_fused_tile_kernel(GemmParams Pdx, GemmParams Pdw, int n_dx)
 {
     if ((int)blockIdx.x < n_dx)
         gemm_tile_body<DX, T, OutDX, 128, 256, 2, 2, false, true, false>(Pdx, (int)blockIdx.x);
     else
-        gemm_persistent_body<DW, T, OutDW, 128, 256, 1, 4, kTailNone>(Pdw, (int)gridDim.x - n_dx, (int)blockIdx.x - n_dx);
+        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone>(Pdw, (int)gridDim.x - n_dx, (int)blockIdx.x - n_dx);
 }
 
 // Both gradients in one launch for 64 x 64 blocks with short kept lists, where dX and dW both run one

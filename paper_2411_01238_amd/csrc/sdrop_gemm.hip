@@ -165,6 +165,42 @@ int dw_splits(int64_t M, int64_t N, int BM, int BK, int64_t K)
     return best;
 }
 
+// How eq. (3) with 128-wide blocks runs where its 128 x 256 tiles fill at most half of the chip (dw_splits then cuts the
+// kept lists into parts, with fp32 planes and a summing pass): as 128 x 128 tiles, with the same parts in the same order,
+//   folded:  every workgroup sums all the parts of its tile itself (GemmParams::folds): no planes and no second launch
+//   split:   parts and planes as before on half the tile, where the folded form would leave most of the chip idle
+// The bits are the same in every form.  Never more workgroups than CUs.  The costs are in units of a wide tile's slice, as
+// in dw_splits, plus 8 for the summing pass's launch; a narrow tile's slice is taken as 0.75 (measured 0.6 to 0.8) and its
+// set-up and epilogue as 8.  Measured, wide -> narrow, us (bf16; dW / sdrop_bwd):
+//   folded:  1024^3, half kept 14.8 -> 10.3 / 15.5 -> 11.3;  2048^3, 0.7 kept 26.7 -> 18.1 / 41.5 -> 33.6;
+//            4096^2 x 1024, half kept 35.7 -> 31.1 / 63.3 -> 56.4, 0.9 kept 43.9 -> 41.8 / 77.5 -> 76.1;
+//            4096 x 1024 x 4096, 0.8 kept 37.2 -> 30.7 / 65.3 -> 60.6;  512 x 4096 x 1024 (no parts) 10.0 -> 8.0 alone
+//   split:   4096 x 1024 x 72, eight parts 18.2 -> 14.6
+// Longer lists stay on wide tiles (16384 x 1024^2, eight parts: 36.8 us), as does sdrop_bwd's one launch where a list of
+// one part would only turn wide workgroups into twice as many that no longer fit the chip beside dX's (512 x 4096 x 1024:
+// 11.8 -> 13.5): fused_dx is the number of those, or 0 for a launch of dW's own.
+struct DwPlan { int splits, folds; bool narrow; };
+DwPlan dw_plan(int64_t M, int64_t N, int BM, int BK, int64_t K, int64_t fused_dx)
+{
+    const int s = dw_splits(M, N, BM, BK, K);
+    DwPlan plan = {s, 1, false};
+    const int64_t ncu = cu_count(), wide = (K / BK) * ((N + 255) / 256), narrow = (K / BK) * ((N + 127) / 128);
+    if (BK != 128 || narrow > ncu || (s == 1 && fused_dx + narrow > ncu)) return plan;
+    const double len = (double)(M / 64), planes = s > 1 ? 8.0 + s * ((double)K * (double)N / 0.86e6) : 0.0;
+    double best = (double)((wide * s + ncu - 1) / ncu) * (len / s + 10.0) + planes;
+    const double folded = 0.75 * len + 8.0, split = 0.75 * len / s + 8.0 + planes;
+    if (folded < best) { plan = {1, s, true}; best = folded; }
+    if (s > 1 && !fused_dx && narrow * s <= ncu && split < best) plan = {s, 1, true};
+    return plan;
+}
+// fused: for sdrop_bwd's one launch, which holds at most a workgroup per CU for dX's block positions
+void set_dw_plan(GemmParams &P, bool fused = false)
+{
+    const int64_t positions = (int64_t)P.MB * P.KB, ncu = cu_count();
+    const DwPlan plan = dw_plan(P.M, P.N, P.BM, P.BK, P.K, fused ? (positions < ncu ? positions : ncu) : 0);
+    P.splits = plan.splits; P.folds = plan.folds; P.dw_narrow = plan.narrow;
+}
+
 int cu_count()
 {
     static int n = 0;
@@ -309,7 +345,8 @@ GemmParams base_params(int op, const void *a, const void *b, const void *mask, v
     }
     P.MB = (int32_t)L.MB; P.KB = (int32_t)L.KB;
     P.n_tiles = 0;
-    P.splits = 1;
+    P.splits = P.folds = 1;
+    P.dw_narrow = false;
     P.total_tiles = 0;
     P.scale = (p < 1.0) ? (float)(1.0 / (1.0 - p)) : 0.0f;
     P.bias = nullptr; P.bias16 = nullptr; P.aux = nullptr; P.act = SDROP_ACT_NONE;
@@ -391,7 +428,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
         // 64-row tiles: only where the call takes the persistent kernel (see dw64_persistent)
         GemmParams Q = base_params(OP, a, b, mask, out, M, K, N, BM, BK, p, out_dtype, L);
         if (epi->kept_fraction > 0.0) Q.p = 1.0 - (epi->kept_fraction < 1.0 ? epi->kept_fraction : 1.0);
-        Q.splits = dw_splits(M, N, BM, BK, K);
+        set_dw_plan(Q);
         nk_native = dw64_persistent(Q);
     }
     if (OP == DX && nk_native) {
@@ -433,7 +470,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
     if (out2) P.C2 = static_cast<char *>(out2);
     P.bias16 = static_cast<const char *>(bias16);
     if constexpr (OP == DW) {
-        P.splits = dw_splits(M, N, BM, BK, K);
+        set_dw_plan(P);
         if (P.splits > 1) {
             // first pass: unscaled fp32 partial planes into the workspace; second pass: sum, scale, round
             const float scale = P.scale;
@@ -558,8 +595,8 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
                 Pdx.lda = l0 * 2; Pdx.ldb = l1 * 2; Pdx.ldc = l3 * esz_out;
                 Pdw.lda = l2 * 2; Pdw.ldb = l0 * 2; Pdw.ldc = l4 * esz_out;
                 Pdx.w_nk = Pdw.w_nk = true;
-                Pdw.splits = dw_splits(M, N, BM, BK, K);
-                Pdw.n_tiles = (int)(N / 256);
+                set_dw_plan(Pdw, true);
+                Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
                 Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
                 const float scale = Pdw.scale;
                 const bool split = Pdw.splits > 1;
@@ -602,7 +639,7 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
         Pdw.lda = lds[2] * 2; Pdw.ldb = lds[0] * 2; Pdw.ldc = lds[4] * esz_out;
     }
     const DxPlan plan = dx_plan(Pdx, g_bwd_fused && N % 256 == 0 && BM == 128 && BK == 128);
-    Pdw.splits = dw_splits(M, N, BM, BK, K);
+    set_dw_plan(Pdw, true);
     // Which single launch applies, if any (all need N to be a multiple of 256, so that neither product has a ragged edge):
     //   persistent dX + persistent dW                      128 x 128 blocks, dX on its persistent kernel
     //   dX a workgroup per tile of two blocks + persistent dW   128 x 128 blocks otherwise
@@ -616,7 +653,7 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
         const int G_ = plan.TN / BK;
         Pdx.n_tiles = (Pdx.KB + G_ - 1) / G_;
         const int n_dx = Pdx.MB * Pdx.n_tiles;           // the per-tile launch's grid: (group of the row, block row)
-        Pdw.n_tiles = (int)(N / 256);
+        Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
         Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
         const float scale = Pdw.scale;
         const bool split = Pdw.splits > 1;

@@ -1,0 +1,58 @@
+"""eq. (3) of arxiv 2411.01238 (Section 3.1) on 128 x 128 tiles, which serve gradients too small to fill the chip with 128 x 256
+ones: the parts of the reduction are summed in the summing pass's order, so the bits are those of the parts computed one
+by one and added."""
+import pytest
+import torch
+
+from oracle import sdrop_oracle as orc
+from paper_2411_01238_amd import sdrop
+from paper_2411_01238_amd.workloads import make_custom
+from _util import f64, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,out", [("bf16", None), ("f16", torch.float32)])
+@pytest.mark.parametrize("M,K,N,BM,p", [
+    (128, 128, 8, 128, 0.0),            # one row block, eight columns
+    (256, 256, 128, 64, 0.5),           # one part, exactly one tile column
+    (512, 384, 136, 128, 0.9),          # a second tile column of eight; columns with nothing kept
+    (1024, 256, 256, 128, 0.5),         # two parts of the list, summed in the accumulators
+    (1024, 1024, 1024, 128, 0.5),
+    (2048, 256, 512, 128, 0.3),         # four parts
+    (4096, 128, 72, 128, 0.3),          # many parts for two tiles: planes and the summing pass
+    (4096, 4096, 1024, 128, 0.5),       # the most tiles it is used for
+])
+def test_dw_on_narrow_tiles(M, K, N, BM, p, dtype, out):
+    print("dw_narrow", M, K, N, BM, p, dtype, flush=True)
+    X, W, dY = make_custom(M, K, N, dtype, seed=7)
+    Xg, Wg, dYg = X.cuda(), W.cuda(), dY.cuda()
+    od = out or X.dtype
+    m = sdrop.sdrop_mask(M, K, BM, 128, p, 5, 1)
+    dw = sdrop.sdrop_bwd_dw(Xg, dYg, m, out_dtype=od)
+    nk = sdrop.sdrop_bwd_dw_ex(Xg, dYg, m, out_dtype=od, w_layout=sdrop.W_NK)
+    assert torch.equal(nk.t(), dw)
+    dx1, dw1 = sdrop.sdrop_bwd(dYg, Wg, Xg, m, out_dtype=od)
+    assert torch.equal(dw1, dw) and torch.equal(dx1, sdrop.sdrop_bwd_dx(dYg, Wg, m, out_dtype=od))
+    dx2, dw2 = sdrop.sdrop_bwd(dYg, Wg.t().contiguous(), Xg, m, out_dtype=od, w_layout=sdrop.W_NK)
+    assert torch.equal(dw2.t(), dw) and torch.equal(dx2, dx1)
+    # the parts one by one, as calls on a caller's own bits, in fp32 and unscaled
+    parts = max(sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, BM, 128, X.dtype, od) // (K * N * 4), 1)
+    keep = orc.mask(M // BM, K // 128, p, 5, 1)
+    if parts > 1 and K * N <= 1 << 20:
+        total = None
+        for q in range(parts):
+            words = torch.zeros(M // BM, 1, dtype=torch.int64)
+            for j in range(K // 128):
+                rows = [i for i in range(M // BM) if keep[i][j]]
+                for i in rows[len(rows) * q // parts:len(rows) * (q + 1) // parts]:
+                    words[i, 0] |= 1 << j
+            mq = sdrop.sdrop_mask_from_bits(M, K, BM, 128, p, words.cuda())
+            # (dY's columns repeated until the output fills the chip: one part on wide tiles)
+            reps = -(-(256 * 128 * 256) // (K * N)) + 1
+            plane = sdrop.sdrop_bwd_dw_ex(Xg, torch.cat([dYg] * reps, 1).contiguous(), mq, scale_mode=sdrop.SCALE_ONE, out_dtype=torch.float32)[:, :N]
+            total = plane.clone() if total is None else total + plane
+        total *= torch.tensor(1.0 / (1.0 - p), dtype=torch.float32).cuda()
+        assert torch.equal(total.to(od), dw)
+    if M * K * N <= 1 << 26 and od == torch.float32:
+        assert_close(f64(dw), orc.bwd_dw(f64(X), f64(dY), keep, BM, 128, p), "narrow dW")

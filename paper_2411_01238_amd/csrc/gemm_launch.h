@@ -423,12 +423,12 @@ int launch_bwd_fused(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t s
     return hip_status(hipGetLastError());
 }
 
-template <class T, class OutDX, class OutDW, int TN_DW = 256>
+template <class T, class OutDX, class OutDW, int TN_DW, bool W_NK>
 int launch_bwd_fused_tile(const GemmParams &Pdx, const GemmParams &Pdw, int n_dx, hipStream_t stream)
 {
     constexpr int LDS_DX = 3 * (128 + 256) * TK * 2, LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
-    auto k = bwd_fused_tile_kernel<T, OutDX, OutDW, TN_DW>;
+    auto k = bwd_fused_tile_kernel<T, OutDX, OutDW, TN_DW, W_NK>;
     static int ok = -1;     // per instantiation: does the device grant that much LDS?
     if (ok < 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
@@ -514,9 +514,11 @@ template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, 
         if (form == kBwdPersistent) return launch_bwd_fused_tn<T, ODX, ODW>(TN, Pdx, Pdw, stream);
         if (form == kBwdTile128) {
             if constexpr (sizeof(ODX) == sizeof(ODW)) {
-                if (Pdw.dw_narrow) return launch_bwd_fused_tile<T, ODX, ODW, 128>(Pdx, Pdw, n_dx, stream);
+                if (Pdw.dw_narrow) return Pdw.w_nk ? launch_bwd_fused_tile<T, ODX, ODW, 128, true>(Pdx, Pdw, n_dx, stream)
+                                                   : launch_bwd_fused_tile<T, ODX, ODW, 128, false>(Pdx, Pdw, n_dx, stream);
             }
-            return launch_bwd_fused_tile<T, ODX, ODW>(Pdx, Pdw, n_dx, stream);
+            return Pdw.w_nk ? launch_bwd_fused_tile<T, ODX, ODW, 256, true>(Pdx, Pdw, n_dx, stream)
+                            : launch_bwd_fused_tile<T, ODX, ODW, 256, false>(Pdx, Pdw, n_dx, stream);
         }
         if (TN == 256) return launch_bwd_fused_tile64<T, ODX, ODW, 256>(Pdx, Pdw, n_dx, Pdw.total_tiles, stream);
         return launch_bwd_fused_tile64<T, ODX, ODW, 128>(Pdx, Pdw, n_dx, Pdw.total_tiles, stream);

@@ -1167,14 +1167,14 @@ __global__ __launch_bounds__(512) void bwd_fused_kernel(GemmParams Pdx, GemmPara
 
 // The same where dX runs one workgroup per tile (tiles of two kept blocks that are too few per CU
 // for the persistent kernel): workgroups [0, n_dx) are those tiles, in the order of the separate
-// launch, the rest the persistent dW kernel.
-template <class T, class OutDX, class OutDW, int TN_DW>
+// launch, the rest the persistent dW kernel.  (W_NK: dX reads a transposed copy of the weight, dW is written as [N,K].)
+template <class T, class OutDX, class OutDW, int TN_DW, bool W_NK>
 __global__ __launch_bounds__(512) void bwd_fused_tile_kernel(GemmParams Pdx, GemmParams Pdw, int n_dx)
 {
     if ((int)blockIdx.x < n_dx)
         gemm_tile_body<DX, T, OutDX, 128, 256, 2, 2, false, true, false>(Pdx, (int)blockIdx.x);
     else
-        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone>(Pdw, (int)gridDim.x - n_dx, (int)blockIdx.x - n_dx);
+        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone, false, false, W_NK>(Pdw, (int)gridDim.x - n_dx, (int)blockIdx.x - n_dx);
 }
 
 // Both gradients in one launch for 64 x 64 blocks with short kept lists, where dX and dW both run one

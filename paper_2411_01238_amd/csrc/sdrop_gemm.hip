@@ -415,8 +415,8 @@ int run(const void *a, const void *b, const void *mask, void *out,
     if (!tile_count_ok(N, L)) return SDROP_ESHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A weight in the [N,K] layout: the kernels read W as [K,N] (eq. 1 walks its row blocks, eq. 2 its rows), so the
-    // weight is transposed into the workspace first (one pass over K N elements; at 4096 x 4096 about 15 us beside a
-    // product of 60), and eq. 3 writes its [K,N] result there and transposes it into the output afterwards.
+    // weight is transposed into the workspace first (one pass over K N elements; at 3072 x 1024 about 6 us beside a
+    // product of 80), and eq. 3 writes its [K,N] result there and transposes it into the output afterwards.
     char *const ws_kn = static_cast<char *>(ws) + ws_planes;       // the K x N matrix behind the planes
     const int64_t esz_out = out_dtype == SDROP_F32 ? 4 : 2;
     void *final_out = out;
@@ -555,8 +555,8 @@ int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, 
 int g_bwd_fused = 1;
 
 // ld: null (contiguous), or the leading dimensions of dY, W, X, dX, dW in elements (0 = contiguous)
-// w_layout = SDROP_W_NK: W is given, and dW wanted, as [N,K] (ld[1], ld[4] then count rows of K elements): the two
-// products are launched in turn, each in place where its kernel has a form for it (see run).
+// w_layout = SDROP_W_NK: W is given, and dW wanted, as [N,K] (ld[1], ld[4] then count rows of K elements): one launch where
+// eq. (3) is written in place, else the two products in turn, each in place where its kernel has a form for it (see run).
 int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void *dx, void *dw,
             int64_t M, int64_t K, int64_t N, int BM, int BK, double p,
             int dtype, int out_dtype, void *ws, size_t ws_bytes, void *stream, const int64_t *ld = nullptr,
@@ -579,22 +579,26 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
             }
         const size_t need = ws_total_bytes(DW, M, K, N, BM, BK, out_dtype, true);
         if (ws_bytes < need || (need && (!ws || reinterpret_cast<uintptr_t>(ws) % 16))) return SDROP_EWORKSPACE;
-        // One launch where both products have their in-place forms (128 x 128 blocks, whole tile columns, eq. 2 on
-        // single-block tiles or where its [K,N] plan takes the pair list): the persistent bodies as in bwd_fused_kernel.
+        // One launch with 128 x 128 blocks and whole tile columns: where eq. 2 runs on single-block tiles, or its [K,N] plan
+        // takes the pair list, both in place (the persistent bodies as in bwd_fused_kernel); where it runs a workgroup per
+        // 256-wide tile, on a transposed copy of W (bwd_fused_tile_kernel).
         if (g_bwd_fused && BM == 128 && BK == 128 && N % 256 == 0) {
             sdrop_mask_layout_t L;
             sdrop_mask_layout(M, K, BM, BK, &L);
             if (!tile_count_ok(N, L)) return SDROP_ESHAPE;
             GemmParams Pdx = base_params(DX, dy, w, mask, dx, M, K, N, BM, BK, p, out_dtype, L);
             GemmParams Pdw = base_params(DW, x, dy, mask, dw, M, K, N, BM, BK, p, out_dtype, L);
+            // (one dX plan for the separate call and this one: what eq. 2 reads in place on its own it reads in place here)
             const DxPlan plan = dx_plan(Pdx);
-            if (plan.TN == 128 || plan.pairs) {
+            const bool in_place = plan.TN == 128 || plan.pairs;
+            if (in_place || !plan.persistent) {
                 const int64_t esz_out = out_dtype == SDROP_F32 ? 4 : 2;
                 const int64_t l0 = ld && ld[0] ? ld[0] : N, l1 = ld && ld[1] ? ld[1] : K, l2 = ld && ld[2] ? ld[2] : K;
                 const int64_t l3 = ld && ld[3] ? ld[3] : K, l4 = ld && ld[4] ? ld[4] : K;
                 Pdx.lda = l0 * 2; Pdx.ldb = l1 * 2; Pdx.ldc = l3 * esz_out;
                 Pdw.lda = l2 * 2; Pdw.ldb = l0 * 2; Pdw.ldc = l4 * esz_out;
-                Pdx.w_nk = Pdw.w_nk = true;
+                Pdw.w_nk = true;
+                Pdx.w_nk = in_place;
                 set_dw_plan(Pdw, true);
                 Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
                 Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
@@ -603,8 +607,23 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
                 if (split) { Pdw.C = static_cast<char *>(ws); Pdw.ldc = K * 4; Pdw.scale = 1.0f; }
                 hipStream_t st = static_cast<hipStream_t>(stream);
                 const bool o32 = out_dtype == SDROP_F32;
-                const int rf = dtype == SDROP_F16 ? bwd_fused_typed<F16>(kBwdPersistent, kTNNK, o32, split, Pdx, Pdw, 0, st)
-                                                  : bwd_fused_typed<BF16>(kBwdPersistent, kTNNK, o32, split, Pdx, Pdw, 0, st);
+                int form = kBwdPersistent, n_dx = 0;
+                if (!in_place) {
+                    // eq. 2 on 256-wide tiles of one block row, a workgroup each, beside eq. 3 in place: the weight goes through
+                    // a transposed copy behind the planes (the separate call puts it where the planes are).  One launch
+                    // boundary and dX's last round less: 16384 x 1024 x 3072 at p = 0.2, a layer's forward and backward with a
+                    // bias, 1.23 -> 1.25 of the speed of a fixed reference version (about 5 of 290 us).
+                    char *const w_kn = static_cast<char *>(ws) + ws_planes_bytes(DW, M, K, N, BM, BK);
+                    const int rt = launch_transpose(w, w_kn, N, K, l1, N, 2, st);
+                    if (rt != SDROP_OK) return rt;
+                    Pdx.B = w_kn;
+                    Pdx.ldb = N * 2;
+                    Pdx.n_tiles = (Pdx.KB + 1) / 2;
+                    n_dx = Pdx.MB * Pdx.n_tiles;
+                    form = kBwdTile128;
+                }
+                const int rf = dtype == SDROP_F16 ? bwd_fused_typed<F16>(form, kTNNK, o32, split, Pdx, Pdw, n_dx, st)
+                                                  : bwd_fused_typed<BF16>(form, kTNNK, o32, split, Pdx, Pdw, n_dx, st);
                 if (rf != -1) {     // -1: the device does not grant the LDS; the two calls then
                     if (rf != SDROP_OK || !split) return rf;
                     return launch_reduce(ws, dw, K * N, Pdw.splits, scale, dtype, out_dtype, st, K, l4, Pdw);

@@ -94,3 +94,37 @@ def test_one_launch_for_64_blocks_with_either_dx_tile_width(width):
         sdrop.set_tuning(sdrop.TUNE_DX_TILE_WIDTH, 0)
     assert_close(f64(dx), orc.bwd_dx(f64(dY), f64(W), keep, B, B, p), "dX 64-blocks width %d" % width)
     assert_close(f64(dw), orc.bwd_dw(f64(X), f64(dY), keep, B, B, p), "dW 64-blocks width %d" % width)
+
+
+@pytest.mark.parametrize("M,K,N,p,dtype,ld", [
+    (1536, 1536, 512, 0.0, "bf16", 0),      # dW on narrow tiles, its parts summed in the accumulators
+    (2560, 2560, 256, 0.1, "f16", 0),       # dW in parts, planes and a summing pass
+    (2560, 2688, 256, 0.1, "bf16", 24),     # an odd number of block columns, row-strided operands
+    (4096, 2560, 2816, 0.2, "bf16", 0),     # more dW tiles than CUs: one part
+])
+def test_nk_weight_through_a_copy_in_one_launch(M, K, N, p, dtype, ld):
+    """dX on tiles of two blocks reads a transposed copy of W[N,K] while dW is written as [N,K] in the same launch."""
+    print("bwd fused nk copy", M, K, N, p, dtype, ld, flush=True)
+    X, W, dY = make_custom(M, K, N, dtype, seed=23)
+    m = sdrop.sdrop_mask(M, K, 128, 128, p, 9, 0)
+
+    def strided(t):
+        t = t.cuda()
+        if ld == 0:
+            return t.contiguous()
+        wide = torch.zeros(t.shape[0], t.shape[1] + ld, dtype=t.dtype, device="cuda")
+        wide[:, :t.shape[1]] = t
+        return wide[:, :t.shape[1]]
+
+    Xg, Wnk, dYg = strided(X), strided(W.t()), strided(dY)
+    for out_dtype in (torch.float32, None):
+        ref_dx = sdrop.sdrop_bwd_dx(dY.cuda(), W.cuda(), m, out_dtype=out_dtype)
+        ref_dw = sdrop.sdrop_bwd_dw(X.cuda(), dY.cuda(), m, out_dtype=out_dtype)
+        try:
+            for fused in (1, 0):
+                sdrop.set_tuning(sdrop.TUNE_BWD_FUSED, fused)
+                dx, dw = sdrop.sdrop_bwd(dYg, Wnk, Xg, m, out_dtype=out_dtype, w_layout=sdrop.W_NK)
+                torch.cuda.synchronize()
+                assert torch.equal(dx, ref_dx) and torch.equal(dw, ref_dw.t()), (fused, out_dtype)
+        finally:
+            sdrop.set_tuning(sdrop.TUNE_BWD_FUSED, 1)

@@ -148,8 +148,10 @@ class SparseDropLinear(torch.nn.Module):
         self.calls = 0          # the mask's rng_stream: a new mask every forward call
 
     def forward(self, x):
-        lead = x.shape[:-1]
-        x2 = x.reshape(-1, x.shape[-1]).contiguous()
+        # a matrix goes in as it is: a reshape of x and one of y would be two more nodes in the graph, which the backward
+        # of a small layer feels (a 1024^3 layer is bound by its host time)
+        matrix = x.dim() == 2
+        x2 = (x if matrix else x.reshape(-1, x.shape[-1])).contiguous()
         p = self.p if self.training else 0.0
         nk = self.weight_layout == "nk"
         bias = self.bias
@@ -161,4 +163,4 @@ class SparseDropLinear(torch.nn.Module):
                 y = y + bias
         if self.training:
             self.calls += 1
-        return y.reshape(*lead, y.shape[-1])
+        return y if matrix else y.reshape(*x.shape[:-1], y.shape[-1])

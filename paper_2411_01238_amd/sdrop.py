@@ -169,27 +169,46 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    """The current HIP stream of the current device, as a pointer."""
+    """The current HIP stream of the current device, as an address."""
     if _raw_stream is not None:
         # one C call instead of building a torch.cuda.Stream object (a third of a call's host time)
-        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, name):
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()):
         raise ValueError("%s must be a contiguous GPU tensor" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
+# (Addresses go to the library as plain integers: with the argument types declared, a c_void_p of its own per argument only
+# costs host time, as does asking a tensor for its shape and strides once per condition.  A 256^3 step, two launches from
+# Python: 22 us of host time in that form, all of what it took.)
 def _mat(t, name):
     """Device pointer and leading dimension (elements) of a 2-D GPU tensor whose rows are contiguous:
     a contiguous matrix or a column range of a wider one."""
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dim() == 2 and (t.shape[1] == 1 or t.stride(1) == 1)
-            and (t.shape[0] == 1 or t.stride(0) >= t.shape[1])):
-        raise ValueError("%s must be a 2-D GPU tensor with contiguous rows" % name)
-    ld = t.stride(0) if t.shape[0] > 1 else t.shape[1]
-    return ctypes.c_void_p(t.data_ptr()), int(ld)
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dim() == 2:
+        rows, cols = t.shape
+        sr, sc = t.stride()
+        if (cols == 1 or sc == 1) and (rows == 1 or sr >= cols):
+            return t.data_ptr(), (sr if rows > 1 else cols)
+    raise ValueError("%s must be a 2-D GPU tensor with contiguous rows" % name)
+
+
+_layouts = {}
+
+
+def _layout_of(M, K, BM, BK):
+    """mask_layout, kept per shape (a bounded number; a Mask only reads it)."""
+    key = (M, K, BM, BK)
+    v = _layouts.get(key)
+    if v is None:
+        v = mask_layout(M, K, BM, BK)
+        if len(_layouts) >= 256:
+            _layouts.clear()
+        _layouts[key] = v
+    return v
 
 
 def mask_layout(M, K, BM, BK):
@@ -207,7 +226,7 @@ class Mask:
 
     def __init__(self, M, K, BM, BK, p, device="cuda"):
         self.M, self.K, self.BM, self.BK, self.p = M, K, BM, BK, float(p)
-        self.layout = mask_layout(M, K, BM, BK)
+        self.layout = _layout_of(M, K, BM, BK)
         self.buf = torch.empty(self.layout.total_bytes, dtype=torch.uint8, device=device)
 
     @property
@@ -302,11 +321,17 @@ def sdrop_mask_from_bits(M, K, BM, BK, p, bits, out=None):
 _ws_cache = {}
 
 
-def workspace_bytes(op, M, K, N, BM, BK, dtype, out_dtype):
-    key = (op, M, K, N, BM, BK, dtype, out_dtype)
+def workspace_bytes(op, M, K, N, BM, BK, dtype, out_dtype, w_layout=W_KN):
+    key = (op, M, K, N, BM, BK, dtype, out_dtype, w_layout)
     v = _ws_cache.get(key)
     if v is None:
-        v = int(lib().sdrop_workspace_bytes(op, M, K, N, BM, BK, _DTYPES[dtype], _DTYPES[out_dtype]))
+        if w_layout == W_KN:
+            v = int(lib().sdrop_workspace_bytes(op, M, K, N, BM, BK, _DTYPES[dtype], _DTYPES[out_dtype]))
+        else:
+            e = Epilogue(w_layout=w_layout)
+            v = int(lib().sdrop_workspace_bytes_ex(op, M, K, N, BM, BK, _DTYPES[dtype], _DTYPES[out_dtype], ctypes.byref(e)))
+        if len(_ws_cache) >= 1024:
+            _ws_cache.clear()
         _ws_cache[key] = v
     return v
 
@@ -321,12 +346,11 @@ def _epilogue(scale_mode, act, bias, relu_mask, ncols, out_shape, dtype, gate_mo
     if bias is not None:
         if bias.dtype != torch.float32 or tuple(bias.shape) != (ncols,):
             raise ValueError("bias must be fp32 with one value per output column")
-        e.bias = _dev(bias, "bias").value
+        e.bias = _dev(bias, "bias")
     if relu_mask is not None:
         if relu_mask.dtype != dtype or tuple(relu_mask.shape) != tuple(out_shape):
             raise ValueError("relu_mask must have the operands' dtype and the output's shape")
-        ptr, e.relu_mask_ld = _mat(relu_mask, "relu_mask")
-        e.relu_mask = ptr.value
+        e.relu_mask, e.relu_mask_ld = _mat(relu_mask, "relu_mask")
     return e
 
 
@@ -341,13 +365,10 @@ def _gemm(name, op, a, b, mask, out_shape, M, K, N, out_dtype, out, ws, epi=None
         raise ValueError("out has the wrong shape or dtype")
     if dtype not in (torch.float16, torch.bfloat16) or out_dtype not in _DTYPES:
         raise SdropError(EDTYPE, name)
-    if epi is not None and epi.w_layout != W_KN:
-        need = int(lib().sdrop_workspace_bytes_ex(op, M, K, N, mask.BM, mask.BK, _DTYPES[dtype], _DTYPES[out_dtype], ctypes.byref(epi)))
-    else:
-        need = workspace_bytes(op, M, K, N, mask.BM, mask.BK, dtype, out_dtype)
+    need = workspace_bytes(op, M, K, N, mask.BM, mask.BK, dtype, out_dtype, W_KN if epi is None else epi.w_layout)
     if ws is None and need:
         ws = torch.empty(need, dtype=torch.uint8, device=a.device)
-    ws_ptr = ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0)
+    ws_ptr = ws.data_ptr() if ws is not None else None
     ws_bytes = ws.numel() * ws.element_size() if ws is not None else 0
     (pa, lda), (pb, ldb), (po, ldo) = _mat(a, "a"), _mat(b, "b"), _mat(out, "out")
     args = (pa, pb, _dev(mask.buf, "mask"), po,
@@ -408,12 +429,11 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
                                     M, K, N, BM, BK, float(p), int(seed), int(rng_stream),
                                     _DTYPES[dtype], _DTYPES[out_dtype], _stream())
     else:
-        e = _epilogue(SCALE_DROPOUT, ACT_NONE, None, None, N, (M, N), dtype, w_layout=w_layout)
-        e.ld_a, e.ld_b, e.ld_out = ldx, ldw, ldy
-        need = int(lib().sdrop_workspace_bytes_ex(OP_FWD, M, K, N, BM, BK, _DTYPES[dtype], _DTYPES[out_dtype], ctypes.byref(e)))
+        e = Epilogue(ld_a=ldx, ld_b=ldw, ld_out=ldy, w_layout=int(w_layout))     # (everything else 0: the plain product)
+        need = workspace_bytes(OP_FWD, M, K, N, BM, BK, dtype, out_dtype, w_layout)
         if ws is None and need:
             ws = torch.empty(need, dtype=torch.uint8, device=X.device)
-        ws_ptr = ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0)
+        ws_ptr = ws.data_ptr() if ws is not None else None
         ws_bytes = ws.numel() * ws.element_size() if ws is not None else 0
         if bias is not None:
             rc = lib().sdrop_fwd_seeded_bias(xp, wp, _dev(bias, "bias"), _dev(m.buf, "mask"), m.buf.numel(), yp,
@@ -487,14 +507,10 @@ def sdrop_bwd(dY, W, X, mask, out_dtype=None, out_dx=None, out_dw=None, ws=None,
         elif tuple(o.shape) != shape or o.dtype != out_dtype:
             raise ValueError("an output has the wrong shape or dtype")
         outs.append(o)
-    if w_layout == W_KN:
-        need = workspace_bytes(OP_BWD_DW, M, K, N, mask.BM, mask.BK, dtype, out_dtype)
-    else:
-        e = _epilogue(SCALE_DROPOUT, ACT_NONE, None, None, N, (K, N), dtype, w_layout=w_layout)
-        need = int(lib().sdrop_workspace_bytes_ex(OP_BWD_DW, M, K, N, mask.BM, mask.BK, _DTYPES[dtype], _DTYPES[out_dtype], ctypes.byref(e)))
+    need = workspace_bytes(OP_BWD_DW, M, K, N, mask.BM, mask.BK, dtype, out_dtype, w_layout)
     if ws is None and need:
         ws = torch.empty(need, dtype=torch.uint8, device=dY.device)
-    ws_ptr = ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0)
+    ws_ptr = ws.data_ptr() if ws is not None else None
     ws_bytes = ws.numel() * ws.element_size() if ws is not None else 0
     mats = [_mat(t, n) for t, n in ((dY, "dY"), (W, "W"), (X, "X"), (outs[0], "dX"), (outs[1], "dW"))]
     ptrs = [m[0] for m in mats]
@@ -572,12 +588,12 @@ def sdrop_producer(H, W0, bias, mask, act=ACT_NONE, out_dtype=None, out=None, pr
     if preact is not None and (tuple(preact.shape) != (M, K) or preact.dtype != out_dtype):
         raise ValueError("preact has the wrong shape or dtype")
     (ph, ldh), (pw, ldw), (po, ldo) = _mat(H, "H"), _mat(W0, "W0"), _mat(out, "out")
-    pz = ctypes.c_void_p(0)
+    pz = None
     if preact is not None:
         pz, ldz = _mat(preact, "preact")
         if ldz != ldo:
             raise ValueError("preact must have the output's leading dimension")
-    args = (ph, pw, _dev(bias, "bias") if bias is not None else ctypes.c_void_p(0), _dev(mask.buf, "mask"), po, pz,
+    args = (ph, pw, _dev(bias, "bias") if bias is not None else None, _dev(mask.buf, "mask"), po, pz,
             M, N0, K, mask.BM, mask.BK, mask.p, int(act), _DTYPES[dtype], _DTYPES[out_dtype], _stream())
     if (ldh, ldw, ldo) == (N0, N0, K):
         rc = lib().sdrop_producer(*args)
@@ -609,7 +625,7 @@ def sdrop_bias_grad(dZ, mask, out=None, ws=None):
     ptr, ld = _mat(dZ, "dZ")
     rc = lib().sdrop_bias_grad(ptr, _dev(mask.buf, "mask"), _dev(out, "out"), M, K, mask.BM, mask.BK,
                                _DTYPES[dZ.dtype], ld,
-                               ctypes.c_void_p(ws.data_ptr()) if ws is not None else ctypes.c_void_p(0),
+                               ws.data_ptr() if ws is not None else None,
                                ws.numel() * ws.element_size() if ws is not None else 0, _stream())
     _check(rc, "sdrop_bias_grad")
     return out
@@ -628,7 +644,7 @@ def sdrop_col_sum(dY, out=None, ws=None):
     ptr, ld = _mat(dY, "dY")
     if ws is None:
         ws = torch.empty(max(int(lib().sdrop_col_sum_workspace_bytes(M, N)), 16), dtype=torch.uint8, device=dY.device)
-    rc = lib().sdrop_col_sum(ptr, _dev(out, "out"), M, N, _DTYPES[dY.dtype], ld, ctypes.c_void_p(ws.data_ptr()),
+    rc = lib().sdrop_col_sum(ptr, _dev(out, "out"), M, N, _DTYPES[dY.dtype], ld, ws.data_ptr(),
                              ws.numel() * ws.element_size(), _stream())
     _check(rc, "sdrop_col_sum")
     return out

@@ -119,3 +119,30 @@ def test_sparse_block_matches_oracle_forward_and_gradients(act, kind):
         fro = np.linalg.norm(got - gref[name]) / np.linalg.norm(gref[name])
         assert fro <= 6e-3, "block %s: relative Frobenius error %.3e" % (name, fro)
     assert b.grad.dtype == torch.float32
+
+
+def test_gelu_block_under_saved_tensor_hooks():
+    """Saved tensors that a hook sees hold no uninitialised blocks, and packing them changes no gradient."""
+    print("gelu block saved-tensor hooks", flush=True)
+    M, K, N0, N, p = 512, 512, 256, 256, 0.5
+    g = torch.Generator(device="cpu")
+    g.manual_seed(3)
+    h, w0, w, dy = (torch.randn(s, generator=g).to(torch.bfloat16).cuda() for s in ((M, N0), (K, N0), (K, N), (M, N)))
+    b0 = torch.randn(K, generator=g).cuda()
+    args = [t.requires_grad_(True) for t in (h, w0, b0, w)]
+    poison = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device="cuda")      # what the allocator hands out next
+    del poison
+    plain = torch.autograd.grad(sparse_act_block(*args, p, "gelu", 128, 128, 4, 0), args, dy)
+    seen = []
+
+    def pack(t):
+        seen.append(bool(torch.isfinite(t).all()))
+        return t.clone()
+
+    poison = torch.full((M, K), float("nan"), dtype=torch.bfloat16, device="cuda")
+    del poison
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+        y = sparse_act_block(*args, p, "gelu", 128, 128, 4, 0)
+    hooked = torch.autograd.grad(y, args, dy)
+    assert len(seen) >= 5 and all(seen)
+    assert all(torch.equal(a, b) for a, b in zip(plain, hooked))

@@ -26,12 +26,10 @@ struct GemmParams {
     int32_t BM, BK, MB, KB;
     int32_t n_tiles;    // FWD/DW: TN-wide tiles along N.  DX: groups of kept blocks per block row
     int32_t splits;     // DW: parts the kept-row list of a block column is cut into (1 = no split)
-    int32_t folds;      // DW on 128 x 128 tiles: parts of the list that one workgroup sums one after the other (see DwPlan)
     int32_t total_tiles; // persistent kernels: tiles of the whole launch
     float scale;
     // optional element-wise tail of FWD and DX (see Tail below); all null / 0 for eq. (1)-(3) proper
     const float *bias;
-    const char *bias16; // FWD only: one value of the operands' type per output column (no other tail with it), or null
     const char *aux;
     int32_t act;
     int32_t gate_mode;  // how aux gates the output (SDROP_GATE_*)
@@ -43,9 +41,12 @@ struct GemmParams {
     uint64_t threshold;
     double p_call;      // the dropout probability of the call (compared with the one a drawn mask records)
     int *status;        // the library's status word on this device, or null
-    bool dw_narrow;     // host side: eq. (3) on 128 x 128 tiles (see DwPlan)
     bool w_nk;          // host side: the weight is [N,K] and the kernel reads it so (see w_nk_native in the launch code)
     bool kept_given;    // host side: the caller stated the kept share itself (a mask of its own bits, whose structure is unknown)
+    bool dw_narrow;     // host side: eq. (3) on 128 x 128 tiles (see DwPlan)
+    // (behind the fields that every kernel reads, whose places in the argument block the kernels without these keep)
+    int32_t folds;      // DW on 128 x 128 tiles: parts of the list that one workgroup sums one after the other (see DwPlan)
+    const char *bias16; // FWD only: one value of the operands' type per output column (no other tail with it), or null
 };
 
 namespace {

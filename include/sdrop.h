@@ -415,7 +415,8 @@ int sdrop_fwd_seeded_ex(const void *X, const void *W, void *mask, size_t mask_by
                         const sdrop_epilogue_t *epi);
 
 /*
- * sdrop_fwd_seeded_ex plus the layer's own bias:  Y = s (X . m') W + bias, the sum in fp32 before the one rounding.
+ * sdrop_fwd_seeded_ex plus the layer's own bias:  Y = s (X . m') W + bias.  The product is rounded to `dtype`
+ * (as sdrop_fwd_seeded_ex writes it), then its sum with the bias: the same bits as that call followed by an addition.
  *   bias   device pointer, N values of type `dtype`, 16-byte aligned
  *   Y      has type `dtype`
  * epi, ws and ws_bytes as for sdrop_fwd_seeded_ex (epi may be NULL: contiguous matrices, [K,N] weight).

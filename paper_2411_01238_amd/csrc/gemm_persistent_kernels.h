@@ -216,8 +216,14 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                         const f32x16 &a = acc[mi][nj * NIP + nl];
                         float v[4] = {a[4 * q] * scale, a[4 * q + 1] * scale, a[4 * q + 2] * scale, a[4 * q + 3] * scale};
                         if constexpr (MODE == kTailBias16) {
+                            // the product rounded, then the sum: what adding the bias to a finished Y gives, bit for bit.  (The
+                            // empty statement keeps the scaled value in fp32, as the plain epilogue has it: the compiler would
+                            // scale and convert to fp16 in one instruction with one rounding where that form has two.)
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] += static_cast<float>(bias16_r[nj][nl * 4 + q][e]);
+                            for (int e = 0; e < 4; ++e) {
+                                asm("" : "+v"(v[e]));
+                                v[e] = static_cast<float>(static_cast<OutT>(v[e])) + static_cast<float>(bias16_r[nj][nl * 4 + q][e]);
+                            }
                         } else if constexpr (TAIL) {
                             if (tl.bias) {
                                 const f32x4 bv = bias_r[nj][nl * 4 + q];
@@ -338,7 +344,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
         if constexpr (MODE == kTailNone) {
             store<kTailNone, 0, MI, 0, NJ, RAGN>(reg, scale, ldc, tl, dst);
         } else if constexpr (MODE == kTailBias16) {
-            // A layer's own bias, read as it is (16 bits) and added before the rounding, also on a ragged last tile column and
+            // A layer's own bias, read as it is (16 bits) and added to the rounded product, also on a ragged last tile column and
             // with a drawn mask, where the other tails have no form: the pass over Y that adds it otherwise costs 48 us at
             // 16384 x 3072 and 9 at 8192 x 1000, this epilogue 1-3.  16 registers of bias values for the whole sub-tile:
             // the operand registers are free by now.

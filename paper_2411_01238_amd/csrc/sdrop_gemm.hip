@@ -524,7 +524,7 @@ bool fwd_seeded_applies(const sdrop_mask_layout_t &L)
 }
 
 // epi: null, or the weight layout and the leading dimensions of X, W and Y (nothing else of it may be set)
-// bias16: null, or N values of the operands' type that are added before the rounding (output of that type only)
+// bias16: null, or N values of the operands' type that are added to the rounded product (output of that type only)
 int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, void *y,
                    int64_t M, int64_t K, int64_t N, int BM, int BK, double p, uint64_t seed, uint64_t rng_stream,
                    int dtype, int out_dtype, void *stream, const sdrop_epilogue_t *epi = nullptr, void *ws = nullptr, size_t ws_bytes = 0,

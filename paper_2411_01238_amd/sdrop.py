@@ -404,7 +404,7 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
     """The step's mask and eq. (1) in one call (one launch for small block grids): returns (Y, Mask).
     The Mask is the object sdrop_mask would have written; the backward calls of the step take it.
     w_layout=W_NK: W is given as [N, K].  Row-strided X, W or out (column ranges of wider matrices) are taken in place.
-    bias: None, or N values of X's type that are added to Y before its rounding (Y of X's type)."""
+    bias: None, or N values of X's type that are added to the rounded product (Y of X's type; the bits of Y + bias)."""
     M, K = X.shape
     K2, N = W.shape if w_layout == W_KN else (W.shape[1], W.shape[0])
     if K2 != K:

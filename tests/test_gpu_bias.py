@@ -6,7 +6,7 @@ import torch
 
 from oracle import sdrop_oracle as orc
 from paper_2411_01238_amd import sdrop
-from paper_2411_01238_amd.autograd import SparseDropLinear
+from paper_2411_01238_amd.autograd import SparseDropLinear, sparsedrop_matmul
 from paper_2411_01238_amd.workloads import make_custom
 from _util import f64
 
@@ -39,18 +39,18 @@ def test_forward_with_bias(M, K, N, BM, BK, nk, dtype):
     lay = sdrop.W_NK if nk else sdrop.W_KN
     guard = torch.full((M + 2, N), 7.0, dtype=X.dtype, device="cuda")
     y, m = sdrop.sdrop_fwd_seeded(X.cuda(), Wg, BM, BK, p, 3, 1, w_layout=lay, bias=b.cuda(), out=guard[1:M + 1])
-    y0, m0 = sdrop.sdrop_fwd_seeded(X.cuda(), Wg, BM, BK, p, 3, 1, w_layout=lay, out_dtype=torch.float32)
+    y0, m0 = sdrop.sdrop_fwd_seeded(X.cuda(), Wg, BM, BK, p, 3, 1, w_layout=lay)
     torch.cuda.synchronize()
     assert bool((guard[0] == 7).all()) and bool((guard[M + 1] == 7).all())
     assert torch.equal(m.bits(), m0.bits())
-    # the fp32 output of the plain call plus the bias, rounded once.  The kernel scales and adds in one fused operation,
-    # so its fp32 sum lacks the rounding of the product (2^-24 of it) that y0 carries: half an ulp of the output plus that
-    s = y0.double() + b.cuda().double()
-    assert bool(((y.double() - s).abs() <= 0.5 * EPS[dtype] * s.abs() + 2.0 ** -23 * y0.double().abs() + 2.0 ** -25).all())
+    assert torch.equal(y, y0 + b.cuda())        # the plain call's output with the bias added to it
     keep = orc.mask(M // BM, K // BK, p, 3, 1)
     if M <= 256:
-        ref = orc.fwd(f64(X), f64(W), keep, BM, BK, p) + f64(b)
-        assert np.all(np.abs(f64(y) - ref) <= 0.5 * EPS[dtype] * np.abs(ref) + 2e-5 * np.max(np.abs(ref)))
+        # two roundings: half a unit of the product and half a unit of the sum, plus the fp32 accumulation
+        prod = orc.fwd(f64(X), f64(W), keep, BM, BK, p)
+        ref = prod + f64(b)
+        bound = 0.5 * EPS[dtype] * (np.abs(prod) + (1 + EPS[dtype]) * np.abs(ref)) + 2e-5 * np.max(np.abs(ref))
+        assert np.all(np.abs(f64(y) - ref) <= bound)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
@@ -91,3 +91,33 @@ def test_layer_gradients_and_the_forms_that_stay_torch(bias_dtype):
     (db2,) = torch.autograd.grad(layer(x), [layer.bias], dy, create_graph=True)
     (ddy,) = torch.autograd.grad(db2.float().sum(), [dy])
     assert bool((ddy == 1).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,K,N,B,layout,train", [
+    (256, 256, 72, 64, "kn", True), (512, 256, 256, 128, "nk", True), (256, 256, 1000, 64, "kn", False), (256, 256, 72, 128, "nk", True),
+])
+def test_layer_with_a_bias_is_the_product_plus_the_bias(M, K, N, B, layout, train, dtype):
+    """The layer's output and gradients are those of the product and an addition, whichever kernel adds the bias."""
+    print("layer with bias", M, K, N, B, layout, train, dtype, flush=True)
+    X, W, dY = make_custom(M, K, N, dtype, seed=11)
+    dt = X.dtype
+    layer = SparseDropLinear(K, N, p=0.3, BM=B, BK=B, bias=True, seed=5, dtype=dt, weight_layout=layout)
+    g = torch.Generator().manual_seed(2)
+    with torch.no_grad():
+        layer.weight.copy_(W.t() if layout == "nk" else W)
+        layer.bias.copy_(torch.randn(N, generator=g))
+    layer.train(train)
+    x = X.cuda().requires_grad_(True)
+    dy = dY.cuda()
+    y = layer(x)
+    y0 = sparsedrop_matmul(x, layer.weight, 0.3 if train else 0.0, B, B, 5, 0, layout) + layer.bias
+    assert torch.equal(y, y0)
+    got = torch.autograd.grad(y, [x, layer.weight, layer.bias], dy)
+    want = torch.autograd.grad(y0, [x, layer.weight], dy)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    ref = f64(dY).sum(0)
+    assert np.all(np.abs(f64(got[2]) - ref) <= 0.5 * EPS[dtype] * np.abs(ref) + 1e-5 * np.abs(f64(dY)).sum(0))
+    # a batch of sequences is the same matrix
+    layer.calls = 0
+    assert torch.equal(layer(X.cuda().view(2, M // 2, K)).view(M, N), y)

@@ -16,14 +16,17 @@ class _SparseDropMatmul(torch.autograd.Function):
         # the mask and eq. (1), plus the bias if there is one, in one call (one launch for block grids up to 128 x 64);
         # m serves the backward
         y, m = sdrop.sdrop_fwd_seeded(x, w, BM, BK, p, seed, rng_stream, w_layout=w_layout, bias=bias)
-        ctx.save_for_backward(x, w)
-        ctx.mask = m
+        # (a step that trains the bias alone needs none of these)
+        if ctx.needs_input_grad[0] or ctx.needs_input_grad[1]:
+            ctx.save_for_backward(x, w)
+            ctx.mask = m
         ctx.w_layout = w_layout
         return y
 
     @staticmethod
     def backward(ctx, dy):
-        x, w = ctx.saved_tensors
+        if ctx.needs_input_grad[0] or ctx.needs_input_grad[1]:
+            x, w = ctx.saved_tensors
         dy = dy.contiguous()
         wl = ctx.w_layout
         if ctx.needs_input_grad[0] and ctx.needs_input_grad[1]:

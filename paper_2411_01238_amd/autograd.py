@@ -10,6 +10,17 @@ import torch
 from . import sdrop
 
 
+def _kernel_readable(t):
+    """May a kernel take a contiguous tensor's memory for its value?  A plain tensor with 16-byte aligned memory, outside
+    forward-mode differentiation (a tangent would be lost); a batch of vmap has no memory of its own and says so."""
+    if type(t) not in (torch.Tensor, torch.nn.Parameter) or torch.autograd.forward_ad._current_level >= 0:
+        return False
+    try:
+        return t.data_ptr() % 16 == 0
+    except RuntimeError:
+        return False
+
+
 class _SparseDropMatmul(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, w, bias, p, BM, BK, seed, rng_stream, w_layout):
@@ -36,8 +47,9 @@ class _SparseDropMatmul(torch.autograd.Function):
             dw = sdrop.sdrop_bwd_dw_ex(x, dy, ctx.mask, w_layout=wl) if ctx.needs_input_grad[1] else None
         db = None
         if ctx.needs_input_grad[2]:
-            # (as a torch operation where the caller differentiates the gradient once more: it is linear in dy)
-            db = dy.sum(0) if torch.is_grad_enabled() and dy.requires_grad else sdrop.sdrop_col_sum(dy)
+            # (as a torch operation where the caller differentiates the gradient once more, it is linear in dy, and where dy
+            # is not memory that the kernel can read)
+            db = dy.sum(0) if (torch.is_grad_enabled() and dy.requires_grad) or not _kernel_readable(dy) else sdrop.sdrop_col_sum(dy)
         return dx, dw, db, None, None, None, None, None, None
 
 
@@ -53,11 +65,10 @@ def sparsedrop_matmul(x, w, p, BM=128, BK=128, seed=0, rng_stream=0, weight_layo
 
 
 def _fusable_bias(bias, x, n):
-    """May the forward's kernel add this bias (and its gradient come from sdrop_col_sum)?  A plain vector of x's type, as the
-    kernel reads it.  Anything else, and a call under forward-mode differentiation, adds it as a torch operation."""
-    return (type(bias) in (torch.Tensor, torch.nn.Parameter) and bias.dtype == x.dtype and bias.device == x.device
-            and tuple(bias.shape) == (n,) and bias.is_contiguous() and bias.data_ptr() % 16 == 0
-            and torch.autograd.forward_ad._current_level < 0)
+    """May the forward's kernel add this bias?  A plain vector of x's type, as the kernel reads it.  Anything else is added
+    as a torch operation."""
+    return (bias.dtype == x.dtype and bias.device == x.device and tuple(bias.shape) == (n,) and bias.is_contiguous()
+            and _kernel_readable(bias))
 
 
 _ACTS = {"relu": (sdrop.ACT_RELU, sdrop.GATE_RELU), "gelu_tanh": (sdrop.ACT_GELU_TANH, sdrop.GATE_GELU_TANH),

@@ -4,6 +4,7 @@ The library's calls are stood in for by dense products on the CPU (with nothing 
 is under test: eq. (1)-(3) of arxiv 2411.01238, Section 3.1, with the layer's own bias behind them."""
 import pytest
 import torch
+from torch.autograd import forward_ad
 
 from paper_2411_01238_amd import autograd, sdrop
 
@@ -52,3 +53,28 @@ def test_gradients_of_a_whole_step(summed):
     dx, dw, db = torch.autograd.grad(layer(x), [x, layer.weight, layer.bias], dy)
     assert torch.equal(dx, dy @ layer.weight.t()) and torch.equal(dw, x.t() @ dy) and torch.equal(db, dy.sum(0))
     assert len(summed) == 1
+
+
+def test_gradients_the_kernel_cannot_read_are_summed_by_torch(summed):
+    layer = _Layer(64, 8)
+    x = torch.randn(64, 64)
+    # a gradient whose memory is not 16-byte aligned
+    wide = torch.randn(64 * 8 + 1)
+    dy = wide[1:].view(64, 8)
+    assert dy.data_ptr() % 16 != 0
+    assert torch.equal(torch.autograd.grad(layer(x), [layer.bias], dy)[0], dy.sum(0))
+    # several gradients at once
+    dys = torch.randn(3, 64, 8)
+    (db,) = torch.autograd.grad(layer(x), [layer.bias], dys, is_grads_batched=True)
+    assert torch.allclose(db, dys.sum(1))
+    # a gradient that carries a tangent
+    y = layer(x)
+    with forward_ad.dual_level():
+        (db,) = torch.autograd.grad(y, [layer.bias], forward_ad.make_dual(dys[0], dys[1]))
+        tangent = forward_ad.unpack_dual(db).tangent
+        assert tangent is not None and torch.allclose(tangent, dys[1].sum(0))
+    # a gradient that is itself differentiated
+    dy = dys[2].clone().requires_grad_(True)
+    (db,) = torch.autograd.grad(layer(x), [layer.bias], dy, create_graph=True)
+    assert torch.equal(torch.autograd.grad(db.sum(), [dy])[0], torch.ones_like(dy))
+    assert not summed

@@ -146,3 +146,20 @@ def test_gelu_block_under_saved_tensor_hooks():
     hooked = torch.autograd.grad(y, args, dy)
     assert len(seen) >= 5 and all(seen)
     assert all(torch.equal(a, b) for a, b in zip(plain, hooked))
+
+
+def test_gelu_block_saves_no_uninitialised_memory():
+    """The saved pre-activation is zero on dropped blocks also where no hook is in force."""
+    print("gelu block saved tensors", flush=True)
+    M, K, N0, N, p = 512, 512, 256, 256, 0.5
+    h, w0, w = (torch.randn(s, device="cuda").to(torch.bfloat16).requires_grad_(True) for s in ((M, N0), (K, N0), (K, N)))
+    b0 = torch.randn(K, device="cuda")
+    # what the allocator hands out next, whichever of the call's buffers of this size comes first
+    poison = [torch.full((M, K), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+    del poison
+    y = sparse_act_block(h, w0, b0, w, p, "gelu", 128, 128, 4, 0)
+    x, z = y.grad_fn.saved_tensors[3:5]
+    dropped = (x == 0).view(M // 128, 128, K // 128, 128).all(3).all(1)
+    assert 0 < int(dropped.sum()) < dropped.numel()
+    zb = z.view(M // 128, 128, K // 128, 128).transpose(1, 2)
+    assert bool((zb[dropped] == 0).all()) and bool(torch.isfinite(z).all())

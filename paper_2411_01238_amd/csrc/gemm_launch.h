@@ -450,7 +450,7 @@ int launch_bwd_fused_tn(int TN, const GemmParams &Pdx, const GemmParams &Pdw, hi
             if (TN == kTNPairs) return launch_bwd_fused<T, OutDX, OutDW, 256, true, false, 128>(Pdx, Pdw, stream);
             if (TN == kTNNK) return launch_bwd_fused<T, OutDX, OutDW, 128, false, true, 128>(Pdx, Pdw, stream);
             if (TN == 128) return launch_bwd_fused<T, OutDX, OutDW, 128, false, false, 128>(Pdx, Pdw, stream);
-            return -1;
+            return launch_bwd_fused<T, OutDX, OutDW, 256, false, false, 128>(Pdx, Pdw, stream);
         }
     }
     if (TN == kTNPairs) return launch_bwd_fused<T, OutDX, OutDW, 256, true>(Pdx, Pdw, stream);

@@ -1,6 +1,8 @@
 """sdrop_bwd: eq. (2) and eq. (3) of arxiv 2411.01238 (Section 3.1) in one call, and in one launch
 where the shapes allow it.  Against the float64 oracle through the C ABI, and bit for bit against
 the two separate entry points, with the single launch switched on and off."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -128,3 +130,40 @@ def test_nk_weight_through_a_copy_in_one_launch(M, K, N, p, dtype, ld):
                 assert torch.equal(dx, ref_dx) and torch.equal(dw, ref_dw.t()), (fused, out_dtype)
         finally:
             sdrop.set_tuning(sdrop.TUNE_BWD_FUSED, 1)
+
+
+def _launches(f):
+    """Launches that a call records into a graph (nothing runs)."""
+    f()                                                 # (modules loaded, attributes set)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    s = torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=s):
+        f()
+    n = ctypes.c_size_t(0)
+    get_nodes = sdrop.lib().hipGraphGetNodes            # (of the HIP runtime that the library is linked to)
+    get_nodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get_nodes(g.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("M,K,N,p,groups,launches", [
+    (4736, 14336, 256, 0.0, None, 1),       # dX tiles of two blocks on the persistent kernel, dW's parts summed in the accumulators
+    (2560, 2560, 1024, 0.1, 0, 1),          # the same form forced at a smaller size
+    (2560, 2560, 1024, 0.1, None, 1),       # dX a workgroup per tile of two blocks, the same dW
+    (1536, 1536, 512, 0.0, None, 1),        # dX on single blocks
+    (2560, 2560, 256, 0.1, 0, 2),           # dW in parts: the summing pass follows
+])
+def test_one_call_is_one_launch(M, K, N, p, groups, launches):
+    print("bwd launches", M, K, N, p, groups, flush=True)
+    X, W, dY = (torch.randn(s, device="cuda").to(torch.bfloat16) for s in ((M, K), (K, N), (M, N)))
+    m = sdrop.sdrop_mask(M, K, 128, 128, p, 3, 0)
+    dx, dw = torch.empty_like(X), torch.empty_like(W)
+    ws = torch.empty(max(sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, 128, 128, X.dtype, X.dtype), 16), dtype=torch.uint8, device="cuda")
+    if groups is not None:
+        sdrop.set_tuning(sdrop.TUNE_DX_PERSISTENT_GROUPS_PER_CU, groups)
+    try:
+        assert _launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw, ws=ws)) == launches
+        assert torch.equal(dx, sdrop.sdrop_bwd_dx(dY, W, m)) and torch.equal(dw, sdrop.sdrop_bwd_dw(X, dY, m, ws=ws))
+    finally:
+        sdrop.set_tuning(sdrop.TUNE_DX_PERSISTENT_GROUPS_PER_CU, sdrop.DX_PERSISTENT_GROUPS_PER_CU_DEFAULT)

@@ -140,14 +140,17 @@ int launch_transpose(const void *src, void *dst, int64_t rows, int64_t cols, int
     return hip_status(hipGetLastError());
 }
 
-int dw_splits(int64_t M, int64_t N, int BM, int BK, int64_t K);
+// eq. (3)'s launch (see dw_plan)
+struct DwPlan { int splits, folds; bool narrow; };
+DwPlan dw_plan(int64_t M, int64_t N, int BM, int BK, int64_t K, int64_t fused_dx);
 
-// Workspace of one product: the fp32 planes of a split dW first, then (weight in the [N,K] layout) a K x N matrix: the
+// Workspace of one product: the fp32 planes of a split dW first (none where its parts are summed in the accumulators; a
+// plan that folds dW's own launch folds it in sdrop_bwd's as well, so one size serves both), then (weight in the [N,K] layout) a K x N matrix: the
 // transposed weight for FWD / DX (operand type), the gradient before its transposition for DW (output type).
 size_t ws_planes_bytes(int op, int64_t M, int64_t K, int64_t N, int BM, int BK)
 {
     if (op != SDROP_OP_BWD_DW) return 0;
-    const int splits = dw_splits(M, N, BM, BK, K);
+    const int splits = dw_plan(M, N, BM, BK, K, 0).splits;
     return splits > 1 ? (size_t)splits * (size_t)K * (size_t)N * sizeof(float) : 0;
 }
 size_t ws_total_bytes(int op, int64_t M, int64_t K, int64_t N, int BM, int BK, int out_dtype, bool w_nk)
@@ -201,7 +204,6 @@ int dw_splits(int64_t M, int64_t N, int BM, int BK, int64_t K)
 // Longer lists stay on wide tiles (16384 x 1024^2, eight parts: 36.8 us), as does sdrop_bwd's one launch where a list of
 // one part would only turn wide workgroups into twice as many that no longer fit the chip beside dX's (512 x 4096 x 1024:
 // 11.8 -> 13.5): fused_dx is the number of those, or 0 for a launch of dW's own.
-struct DwPlan { int splits, folds; bool narrow; };
 DwPlan dw_plan(int64_t M, int64_t N, int BM, int BK, int64_t K, int64_t fused_dx)
 {
     const int s = dw_splits(M, N, BM, BK, K);

@@ -198,6 +198,18 @@ def test_tail_arguments_are_checked_on_the_host():
     assert g(*ok[:5], ctypes.c_void_p(addr + 8), *ok[6:]) == sdrop.EALIGN      # the second output
 
 
+def test_a_reduction_folded_in_the_accumulators_asks_for_no_planes():
+    # eq. (3) on 128 x 128 tiles that sum their parts themselves (256 CUs assumed without a device); an [N,K] weight asks
+    # for its transposed matrix alone
+    L = sdrop.lib()
+    e = sdrop.Epilogue(w_layout=sdrop.W_NK)
+    for M, K, N in ((1024, 1024, 1024), (2048, 2048, 2048), (4096, 4096, 1024)):
+        assert L.sdrop_workspace_bytes(sdrop.OP_BWD_DW, M, K, N, 128, 128, sdrop.BF16, sdrop.BF16) == 0
+        assert L.sdrop_workspace_bytes_ex(sdrop.OP_BWD_DW, M, K, N, 128, 128, sdrop.BF16, sdrop.F32, ctypes.byref(e)) == K * N * 4
+    # folded in sdrop_bwd's launch only: dW's own launch writes planes
+    assert L.sdrop_workspace_bytes(sdrop.OP_BWD_DW, 1536, 256, 512, 128, 128, sdrop.BF16, sdrop.BF16) == 2 * 256 * 512 * 4
+
+
 def test_workspace_size_is_a_whole_number_of_fp32_planes():
     # only dW asks for a workspace: `parts` fp32 planes of K x N, parts a power of two up to 16, none
     # when K/BK * ceil(N/256) output tiles already fill the chip (256 CUs assumed without a device)

@@ -13,17 +13,18 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,out", [("bf16", None), ("f16", torch.float32)])
-@pytest.mark.parametrize("M,K,N,BM,p", [
-    (128, 128, 8, 128, 0.0),            # one row block, eight columns
-    (256, 256, 128, 64, 0.5),           # one part, exactly one tile column
-    (512, 384, 136, 128, 0.9),          # a second tile column of eight; columns with nothing kept
-    (1024, 256, 256, 128, 0.5),         # two parts of the list, summed in the accumulators
-    (1024, 1024, 1024, 128, 0.5),
-    (2048, 256, 512, 128, 0.3),         # four parts
-    (4096, 128, 72, 128, 0.3),          # many parts for two tiles: planes and the summing pass
-    (4096, 4096, 1024, 128, 0.5),       # the most tiles it is used for
+@pytest.mark.parametrize("M,K,N,BM,p,parts,planes", [
+    (128, 128, 8, 128, 0.0, 1, 0),      # one row block, eight columns
+    (256, 256, 128, 64, 0.5, 1, 0),     # one part, exactly one tile column
+    (512, 384, 136, 128, 0.9, 1, 0),    # a second tile column of eight; columns with nothing kept
+    (1024, 256, 256, 128, 0.5, 2, 0),   # two parts of the list, summed in the accumulators
+    (1024, 1024, 1024, 128, 0.5, 2, 0),
+    (1536, 256, 512, 128, 0.3, 2, 2),   # two parts: planes in dW's own launch, the accumulators in sdrop_bwd's
+    (2048, 256, 512, 128, 0.3, 4, 4),   # four parts: planes and the summing pass
+    (4096, 128, 72, 128, 0.3, 8, 8),    # many parts for two tiles
+    (4096, 4096, 1024, 128, 0.5, 2, 0), # the most tiles it is used for
 ])
-def test_dw_on_narrow_tiles(M, K, N, BM, p, dtype, out):
+def test_dw_on_narrow_tiles(M, K, N, BM, p, parts, planes, dtype, out):
     print("dw_narrow", M, K, N, BM, p, dtype, flush=True)
     X, W, dY = make_custom(M, K, N, dtype, seed=7)
     Xg, Wg, dYg = X.cuda(), W.cuda(), dY.cuda()
@@ -37,7 +38,7 @@ def test_dw_on_narrow_tiles(M, K, N, BM, p, dtype, out):
     dx2, dw2 = sdrop.sdrop_bwd(dYg, Wg.t().contiguous(), Xg, m, out_dtype=od, w_layout=sdrop.W_NK)
     assert torch.equal(dw2.t(), dw) and torch.equal(dx2, dx1)
     # the parts one by one, as calls on a caller's own bits, in fp32 and unscaled
-    parts = max(sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, BM, 128, X.dtype, od) // (K * N * 4), 1)
+    assert sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, BM, 128, X.dtype, od) == planes * K * N * 4
     keep = orc.mask(M // BM, K // 128, p, 5, 1)
     if parts > 1 and K * N <= 1 << 20:
         total = None

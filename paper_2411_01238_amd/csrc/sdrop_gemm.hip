@@ -201,15 +201,19 @@ int dw_splits(int64_t M, int64_t N, int BM, int BK, int64_t K)
 //            4096^2 x 1024, half kept 35.7 -> 31.1 / 63.3 -> 56.4, 0.9 kept 43.9 -> 41.8 / 77.5 -> 76.1;
 //            4096 x 1024 x 4096, 0.8 kept 37.2 -> 30.7 / 65.3 -> 60.6;  512 x 4096 x 1024 (no parts) 10.0 -> 8.0 alone
 //   split:   4096 x 1024 x 72, eight parts 18.2 -> 14.6
-// Longer lists stay on wide tiles (16384 x 1024^2, eight parts: 36.8 us), as does sdrop_bwd's one launch where a list of
-// one part would only turn wide workgroups into twice as many that no longer fit the chip beside dX's (512 x 4096 x 1024:
-// 11.8 -> 13.5): fused_dx is the number of those, or 0 for a launch of dW's own.
+// Longer lists stay on wide tiles (16384 x 1024^2, eight parts: 36.8 us).  fused_dx is the number of dX's workgroups in
+// sdrop_bwd's one launch, or 0 for a launch of dW's own.  In that launch a list of one part stays on wide tiles
+//   where narrow ones, twice as many, would no longer fit the chip beside dX's (512 x 4096 x 1024: 11.8 -> 13.5), and
+//   where dX's reduction is the longer of the two (N > M), so that dX decides the launch and dW's second workgroup per tile
+//   only takes from it (sdrop_bwd, 0.3 dropped: 256 x 2048 x 1024 10.59 -> 10.70, 384 x 512 x 768 9.45 -> 9.51,
+//   256 x 512^2 8.12 -> 8.16, 256 x 1024^2 and 512 x 1024^2 the same).
+// With N <= M it gains: 512^3 8.61 -> 8.25, 768 x 1024 x 768 11.8 -> 9.6, 512 x 1024 x 512 9.6 -> 8.3, 512 x 256^2 9.5 -> 7.0.
 DwPlan dw_plan(int64_t M, int64_t N, int BM, int BK, int64_t K, int64_t fused_dx)
 {
     const int s = dw_splits(M, N, BM, BK, K);
     DwPlan plan = {s, 1, false};
     const int64_t ncu = cu_count(), wide = (K / BK) * ((N + 255) / 256), narrow = (K / BK) * ((N + 127) / 128);
-    if (BK != 128 || narrow > ncu || (s == 1 && fused_dx + narrow > ncu)) return plan;
+    if (BK != 128 || narrow > ncu || (s == 1 && fused_dx && (fused_dx + narrow > ncu || N > M))) return plan;
     const double len = (double)(M / 64), planes = s > 1 ? 8.0 + s * ((double)K * (double)N / 0.86e6) : 0.0;
     double best = (double)((wide * s + ncu - 1) / ncu) * (len / s + 10.0) + planes;
     const double folded = 0.75 * len + 8.0, split = 0.75 * len / s + 8.0 + planes;

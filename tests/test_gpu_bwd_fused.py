@@ -132,19 +132,30 @@ def test_nk_weight_through_a_copy_in_one_launch(M, K, N, p, dtype, ld):
             sdrop.set_tuning(sdrop.TUNE_BWD_FUSED, 1)
 
 
+class _KernelNode(ctypes.Structure):        # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
 def _launches(f):
-    """Launches that a call records into a graph (nothing runs)."""
+    """Workgroups of each launch that a call records into a graph, in the order of the graph's nodes (nothing runs)."""
     f()                                                 # (modules loaded, attributes set)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph(keep_graph=True)
     s = torch.cuda.Stream()
     with torch.cuda.graph(g, stream=s):
         f()
-    n = ctypes.c_size_t(0)
-    get_nodes = sdrop.lib().hipGraphGetNodes            # (of the HIP runtime that the library is linked to)
-    get_nodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
-    assert get_nodes(g.raw_cuda_graph(), None, ctypes.byref(n)) == 0
-    return n.value
+    L, n, node = sdrop.lib(), ctypes.c_size_t(0), _KernelNode()      # (the HIP runtime that the library is linked to)
+    L.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    L.hipGraphKernelNodeGetParams.argtypes = [ctypes.c_void_p, ctypes.POINTER(_KernelNode)]
+    assert L.hipGraphGetNodes(g.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert L.hipGraphGetNodes(g.raw_cuda_graph(), nodes, ctypes.byref(n)) == 0
+    grids = []
+    for i in range(n.value):
+        assert L.hipGraphKernelNodeGetParams(nodes[i], ctypes.byref(node)) == 0
+        grids.append(node.grid[0] * node.grid[1] * node.grid[2])
+    return grids
 
 
 @pytest.mark.parametrize("M,K,N,p,groups,launches", [
@@ -163,7 +174,23 @@ def test_one_call_is_one_launch(M, K, N, p, groups, launches):
     if groups is not None:
         sdrop.set_tuning(sdrop.TUNE_DX_PERSISTENT_GROUPS_PER_CU, groups)
     try:
-        assert _launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw, ws=ws)) == launches
+        assert len(_launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw, ws=ws))) == launches
         assert torch.equal(dx, sdrop.sdrop_bwd_dx(dY, W, m)) and torch.equal(dw, sdrop.sdrop_bwd_dw(X, dY, m, ws=ws))
     finally:
         sdrop.set_tuning(sdrop.TUNE_DX_PERSISTENT_GROUPS_PER_CU, sdrop.DX_PERSISTENT_GROUPS_PER_CU_DEFAULT)
+
+
+@pytest.mark.parametrize("M,K,N,dw_groups", [
+    (256, 512, 512, 8),         # dX's reduction is the longer one: dW on 128 x 256 tiles
+    (512, 512, 512, 16),        # no longer than dW's: 128 x 128 tiles
+    (512, 512, 768, 12),
+    (768, 512, 768, 24),
+])
+def test_tiles_of_a_list_of_one_part(M, K, N, dw_groups):
+    print("bwd one part", M, K, N, flush=True)
+    X, W, dY = (torch.randn(s, device="cuda").to(torch.bfloat16) for s in ((M, K), (K, N), (M, N)))
+    m = sdrop.sdrop_mask(M, K, 128, 128, 0.0, 3, 0)
+    dx, dw = torch.empty_like(X), torch.empty_like(W)
+    grids = _launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw))
+    assert grids == [(M // 128) * (K // 128) + dw_groups]       # a workgroup for each of dX's blocks, and dW's
+    assert torch.equal(dx, sdrop.sdrop_bwd_dx(dY, W, m)) and torch.equal(dw, sdrop.sdrop_bwd_dw(X, dY, m))

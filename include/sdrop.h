@@ -310,7 +310,7 @@ int sdrop_bwd(const void *dY, const void *W, const void *X, const void *mask, vo
  * Same launches and results as sdrop_bwd on contiguous copies; nothing outside the column ranges is written.
  * w_layout = SDROP_W_NK: W is given and dW delivered as [N,K] (ld_w, ld_dw >= K): one launch for 128 x 128 blocks and N a
  * multiple of 256 (eq. 2 on single blocks reads W in place, on 256-wide tiles of one block row a transposed copy in the
- * workspace), else sdrop_bwd_dx_ex followed by sdrop_bwd_dw_ex with that layout; the same bits as those two calls, and the workspace
+ * workspace; long, narrow eq. 3 excepted, which is the faster as a launch of its own), else sdrop_bwd_dx_ex followed by sdrop_bwd_dw_ex with that layout; the same bits as those two calls, and the workspace
  * is that of sdrop_bwd_dw_ex with that layout (sdrop_workspace_bytes_ex(SDROP_OP_BWD_DW, ...)).
  */
 int sdrop_bwd_ex(const void *dY, const void *W, const void *X, const void *mask, void *dX, void *dW,

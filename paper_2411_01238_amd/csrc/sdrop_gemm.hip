@@ -619,7 +619,15 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
             // (one dX plan for the separate call and this one: what eq. 2 reads in place on its own it reads in place here)
             const DxPlan plan = dx_plan(Pdx);
             const bool in_place = plan.TN == 128 || plan.pairs;
-            if (in_place || !plan.persistent) {
+            set_dw_plan(Pdw);
+            const bool dw_alone_narrow = Pdw.dw_narrow && Pdw.splits > 1;
+            set_dw_plan(Pdw, true);
+            Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
+            Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
+            // (where the form with a copied weight gains: see there)
+            const double dx_tiles = (1.0 - p) * Pdx.MB * Pdx.KB / 2 + (p > 0.0 ? Pdx.MB / 4.0 : 0.0);
+            const bool copied = !plan.persistent && !(dw_alone_narrow && M > 8192 && dx_tiles + Pdw.total_tiles > cu_count());
+            if (in_place || copied) {
                 const int64_t esz_out = out_dtype == SDROP_F32 ? 4 : 2;
                 const int64_t l0 = ld && ld[0] ? ld[0] : N, l1 = ld && ld[1] ? ld[1] : K, l2 = ld && ld[2] ? ld[2] : K;
                 const int64_t l3 = ld && ld[3] ? ld[3] : K, l4 = ld && ld[4] ? ld[4] : K;
@@ -627,9 +635,6 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
                 Pdw.lda = l2 * 2; Pdw.ldb = l0 * 2; Pdw.ldc = l4 * esz_out;
                 Pdw.w_nk = true;
                 Pdx.w_nk = in_place;
-                set_dw_plan(Pdw, true);
-                Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
-                Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
                 const float scale = Pdw.scale;
                 const bool split = Pdw.splits > 1;
                 if (split) { Pdw.C = static_cast<char *>(ws); Pdw.ldc = K * 4; Pdw.scale = 1.0f; }
@@ -638,9 +643,13 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
                 int form = kBwdPersistent, n_dx = 0;
                 if (!in_place) {
                     // eq. 2 on 256-wide tiles of one block row, a workgroup each, beside eq. 3 in place: the weight goes through
-                    // a transposed copy behind the planes (the separate call puts it where the planes are).  One launch
-                    // boundary and dX's last round less: 16384 x 1024 x 3072 at p = 0.2, a layer's forward and backward with a
-                    // bias, 1.23 -> 1.25 of the speed of a fixed reference version (about 5 of 290 us).
+                    // a transposed copy behind the planes (the separate call puts it where the planes are).  dW's workgroups
+                    // start on the CUs that dX's last round leaves idle.  Two calls -> one, us: 16384 x 1024 x 3072 at p = 0.1,
+                    // 0.2, 0.3: 192.6 -> 190.0, 181.9 -> 180.2, 157.3 -> 151.1; 4096^3 at 0.2: 215.7 -> 213.7; 8192 x 1024^2
+                    // at 0.2: 56.7 -> 50.7; 2560^2 x 512 at 0.1: 39.1 -> 36.3; 6144 x 1024 x 256 at 0.1 (all of it in one
+                    // round): 31.9 -> 25.0.  Not where dW on its own would run its parts on narrow tiles, its lists are long and
+                    // the launch takes more than a round: 32768 x 512^2 at p = 0: 64.9 -> 70.0, at 0.2 61.6 -> 64.3;
+                    // 16384 x 512 x 256 at 0.2 36.4 -> 37.7; 8192 x 1024 x 256 at p = 0 (the line) 36.4 -> 37.0, at 0.2 35.6 -> 35.2.
                     char *const w_kn = static_cast<char *>(ws) + ws_planes_bytes(DW, M, K, N, BM, BK);
                     const int rt = launch_transpose(w, w_kn, N, K, l1, N, 2, st);
                     if (rt != SDROP_OK) return rt;

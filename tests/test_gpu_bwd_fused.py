@@ -194,3 +194,21 @@ def test_tiles_of_a_list_of_one_part(M, K, N, dw_groups):
     grids = _launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw))
     assert grids == [(M // 128) * (K // 128) + dw_groups]       # a workgroup for each of dX's blocks, and dW's
     assert torch.equal(dx, sdrop.sdrop_bwd_dx(dY, W, m)) and torch.equal(dw, sdrop.sdrop_bwd_dw(X, dY, m))
+
+
+@pytest.mark.parametrize("M,K,N,p,launches", [
+    (8192, 1024, 512, 0.2, 3),          # the weight's copy, both gradients, the sum of dW's parts
+    (16384, 512, 512, 0.0, 4),          # the copy, dX, dW's parts on narrow tiles, their sum
+    (16384, 1024, 512, 0.2, 3),         # as long, but dW alone would take wide tiles
+    (10240, 512, 256, 0.0, 3),          # as long and narrow, but all of it fits the chip at once
+])
+def test_launches_with_an_nk_weight_through_a_copy(M, K, N, p, launches):
+    print("bwd launches nk", M, K, N, p, flush=True)
+    X, W, dY = (torch.randn(s, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (M, N)))
+    m = sdrop.sdrop_mask(M, K, 128, 128, p, 3, 0)
+    dx, dw = torch.empty_like(X), torch.empty_like(W)
+    need = sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, 128, 128, X.dtype, X.dtype, sdrop.W_NK)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    assert len(_launches(lambda: sdrop.sdrop_bwd(dY, W, X, m, out_dx=dx, out_dw=dw, ws=ws, w_layout=sdrop.W_NK))) == launches
+    Wk = W.t().contiguous()
+    assert torch.equal(dx, sdrop.sdrop_bwd_dx(dY, Wk, m)) and torch.equal(dw.t(), sdrop.sdrop_bwd_dw(X, dY, m))

@@ -362,7 +362,7 @@ int dispatch_tile(GemmParams &P, hipStream_t stream)
         }
         if (P.dw_narrow) {
             const int rc = launch_dw_narrow<T, OutT>(P, stream);
-            return rc == -1 ? SDROP_EHIP : rc;           // (half of what the 128 x 256 form needs)
+            return rc == -1 ? SDROP_EHIP : rc;           // (112 KB of LDS, where the 128 x 256 form needs 160)
         }
         P.n_tiles = (int)((P.N + 255) / 256);
         const int grid = P.KB * P.n_tiles * P.splits;

@@ -1,5 +1,5 @@
 // The persistent forms of the three block-sparse GEMMs and the launches that hold both gradients (included by
-// the typed GEMM translation units only; the design notes are at the top of that file).
+// sdrop_gemm_inst.hip only, through gemm_launch.h; the design notes are at the top of sdrop_gemm.hip).
 #ifndef SDROP_GEMM_PERSISTENT_KERNELS_H
 #define SDROP_GEMM_PERSISTENT_KERNELS_H
 #include "gemm_tile_kernel.h"

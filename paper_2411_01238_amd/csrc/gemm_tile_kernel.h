@@ -1,5 +1,5 @@
-// The one-launch-per-tile form of the three block-sparse GEMMs (included by the typed GEMM translation units only; the design notes are
-// at the top of that file).
+// The one-launch-per-tile form of the three block-sparse GEMMs (included by sdrop_gemm_inst.hip only, through
+// gemm_launch.h; the design notes are at the top of sdrop_gemm.hip).
 #ifndef SDROP_GEMM_TILE_KERNEL_H
 #define SDROP_GEMM_TILE_KERNEL_H
 #include "gemm_device_common.h"

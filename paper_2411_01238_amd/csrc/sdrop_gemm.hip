@@ -59,7 +59,7 @@
 
 namespace sdrop {
 
-// ---- launch heuristics and knobs (shared with the typed translation units through gemm_host.h) ----
+// ---- launch heuristics and knobs (shared with the kernels' launch code through gemm_host.h) ----
 // out[e] = scale * sum_c part[c][e], rounded once (the second pass of a split DW)
 template <class OutT>
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *part, OutT *out_base, int64_t n, int splits, float scale,
@@ -321,7 +321,11 @@ DxPlan dx_plan(const GemmParams &P, bool fused)
 // 15.6 -> 12.1; 4096 x 1024 x 1024 (128 wide tiles) 15.2 -> 12.1; 4096^2 x 512 32.9 -> 23.6; 4096^2 x 768 32.9 -> 28.8;
 // 4096^2 x 1024 33.1 -> 31.3.  With all blocks kept: 4096^2 x 512 (64 wide tiles) 40.1 -> 34.1, x 768 (96) 40.3 -> 36.5,
 // x 1024 (128) 41.4 -> 43.6: between three eighths and half of the chip only with a dropout rate that leaves the rows'
-// counts uneven.  Beyond half of the chip a second round of narrow tiles loses to one of wide ones (160 wide tiles, all
+// counts uneven, and from p = 0.1 on that is enough.  128 wide tiles, three masks each, p = 0.1 / 0.2 / 0.5:
+//   4096^2 x 1024 45.0 -> 41.0 / 42.9 -> 38.5 / 32.3 -> 28.5;  4096 x 1024^2 17.3 -> 14.2 / 17.5 -> 14.1 / 16.2 -> 12.9;
+//   4096 x 2048 x 896 25.0 -> 23.7 / 24.0 -> 22.5 / 23.2 -> 20.1;  2048^3 25.9 -> 21.0 / 24.9 -> 20.0 / 21.4 -> 16.2;
+//   16384 x 4096 x 256 53.5 -> 48.2 / 49.5 -> 45.2 / 41.3 -> 35.4;  112: 14336 x 1024 x 256 22.1 -> 18.8 / 23.4 -> 20.0 / 22.0 -> 18.5.
+// (At p = 0 the same shapes gave 1.00 to 1.30 of the wide form's speed in that run.)  Beyond half of the chip a second round of narrow tiles loses to one of wide ones (160 wide tiles, all
 // kept, K = 1024: 16.1 -> 20.6).
 bool fwd_narrow(const GemmParams &P)
 {

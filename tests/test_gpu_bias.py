@@ -28,6 +28,14 @@ EPS = {"bf16": 2.0 ** -7, "f16": 2.0 ** -10}
     (129 * 64, 128, 256, 64, 64, False),     # a grid too tall for the seeded form: mask, then the product
     (129 * 64, 128, 520, 64, 64, False),
     (129 * 128, 128, 256, 128, 128, True),
+    # 128 x 256 tiles with the mask drawn in the launch: whole, ragged, [N,K], more tiles than CUs (a workgroup reads its
+    # bias values anew for each), and without the draw
+    (8192, 256, 1024, 128, 128, False),
+    (8192, 128, 1000, 128, 128, False),
+    (8192, 256, 1536, 128, 128, True),
+    (16384, 128, 1032, 128, 64, False),
+    (129 * 128, 128, 512, 128, 128, False),
+    (129 * 128, 128, 264, 128, 128, False),
 ])
 def test_forward_with_bias(M, K, N, BM, BK, nk, dtype):
     p = 0.4
@@ -72,6 +80,28 @@ def test_column_sums(M, N, ld, dtype):
     assert torch.equal(got, sdrop.sdrop_col_sum(wide[:, :N]))
 
 
+def test_infinities_and_nan_go_where_they_belong():
+    """Non-finite values of a bias and of dY reach their own columns, and only those."""
+    print("bias non-finite", flush=True)
+    inf, nan = float("inf"), float("nan")
+    M, K, N = 256, 256, 264
+    X, W, _ = make_custom(M, K, N, "bf16", seed=4)
+    b = torch.zeros(N, dtype=torch.bfloat16)
+    b[3], b[64], b[263] = inf, -inf, nan
+    for B in (64, 128):
+        y, _ = sdrop.sdrop_fwd_seeded(X.cuda(), W.cuda(), B, B, 0.3, 3, 1, bias=b.cuda())
+        y0, _ = sdrop.sdrop_fwd_seeded(X.cuda(), W.cuda(), B, B, 0.3, 3, 1)
+        assert torch.equal(y.isnan().cpu(), b.isnan().expand(M, N)) and torch.equal(y.nan_to_num(), (y0 + b.cuda()).nan_to_num())
+    for rows in (7, 1000):
+        d = torch.randn(rows, N, dtype=torch.float32).to(torch.bfloat16)
+        d[rows - 1, 0], d[2, 63] = inf, -inf
+        d[1, 127], d[5, 127] = inf, -inf           # of both signs: no number
+        d[4, 263] = nan
+        got, ref = sdrop.sdrop_col_sum(d.cuda()).cpu().double(), d.double().sum(0)
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+        assert torch.equal(got[got.isinf()], ref[ref.isinf()])
+
+
 @pytest.mark.parametrize("bias_dtype", [torch.bfloat16, torch.float32])
 def test_layer_gradients_and_the_forms_that_stay_torch(bias_dtype):
     torch.manual_seed(0)
@@ -84,7 +114,9 @@ def test_layer_gradients_and_the_forms_that_stay_torch(bias_dtype):
     dx, dw, db = torch.autograd.grad(y, [x, layer.weight, layer.bias], dy)
     assert db.dtype == bias_dtype
     ref = f64(dy).sum(0)
-    assert np.all(np.abs(f64(db) - ref) <= 0.5 * EPS["bf16"] * np.abs(ref) + 1e-5)
+    # an fp32 sum of 128 values errs by less than 128 * 2^-24 of the magnitudes' sum; a bf16 one is rounded as well
+    eps = 0.5 * EPS["bf16"] if bias_dtype == torch.bfloat16 else 0.0
+    assert np.all(np.abs(f64(db) - ref) <= eps * np.abs(ref) + 128 * 2.0 ** -24 * np.abs(f64(dy)).sum(0))
     # the gradient of the bias is linear in dy and can be differentiated again
     dy.requires_grad_(True)
     layer.calls = 0

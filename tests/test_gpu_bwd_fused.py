@@ -17,10 +17,12 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # M, K, N, BM, BK, dtype, p, seed, dX kernel forced persistent
     (1024, 512, 512, 128, 128, "bf16", 0.5, 1, False),    # one launch: one kept block per dX tile, 8 dW tiles
-    (1536, 256, 512, 128, 128, "f16", 0.3, 2, False),     # one launch; the dW part writes split fp32 planes, a summing pass follows
+    (1536, 256, 512, 128, 128, "f16", 0.3, 2, False),     # one launch; dW on 128 x 128 tiles, its parts summed in the accumulators
+    (2048, 256, 512, 128, 128, "f16", 0.3, 12, False),    # one launch; the dW part writes split fp32 planes, a summing pass follows
     (2560, 2560, 256, 128, 128, "bf16", 0.1, 3, True),    # one launch: dX tiles of two kept blocks, persistent form
     (2560, 2560, 256, 128, 128, "f16", 0.1, 13, False),   # one launch: dX tiles of two kept blocks, a workgroup per tile
-    (1536, 1536, 512, 128, 128, "bf16", 0.0, 14, False),  # the same with nothing dropped and a split dW
+    (1536, 1536, 512, 128, 128, "bf16", 0.0, 14, False),  # nothing dropped, one kept block per dX tile, dW summed in the accumulators
+    (2560, 2560, 512, 128, 128, "bf16", 0.0, 15, False),  # nothing dropped, dX tiles of two kept blocks and a split dW
     (4096, 1024, 256, 128, 128, "f16", 0.7, 4, False),    # one launch: more dX workgroups than kept blocks
     (512, 768, 328, 128, 128, "bf16", 0.3, 5, False),     # ragged N: two launches
     (384, 512, 256, 64, 64, "f16", 0.5, 6, False),        # 64 x 64 blocks, short kept lists: one launch, both a workgroup per tile
@@ -99,10 +101,12 @@ def test_one_launch_for_64_blocks_with_either_dx_tile_width(width):
 
 
 @pytest.mark.parametrize("M,K,N,p,dtype,ld", [
-    (1536, 1536, 512, 0.0, "bf16", 0),      # dW on narrow tiles, its parts summed in the accumulators
+    (1536, 1536, 512, 0.0, "bf16", 0),      # dX on single blocks: no copy, both in place; dW's parts summed in the accumulators
+    (2560, 2560, 1024, 0.0, "bf16", 0),     # the copy; dW's parts summed in the accumulators
     (2560, 2560, 256, 0.1, "f16", 0),       # dW in parts, planes and a summing pass
     (2560, 2688, 256, 0.1, "bf16", 24),     # an odd number of block columns, row-strided operands
-    (4096, 2560, 2816, 0.2, "bf16", 0),     # more dW tiles than CUs: one part
+    (4096, 2560, 2816, 0.2, "bf16", 0),     # both in place, dW in one part
+    (4096, 4096, 2048, 0.1, "bf16", 0),     # the copy; as many dW tiles as CUs: one part
 ])
 def test_nk_weight_through_a_copy_in_one_launch(M, K, N, p, dtype, ld):
     """dX on tiles of two blocks reads a transposed copy of W[N,K] while dW is written as [N,K] in the same launch."""

@@ -57,3 +57,33 @@ def test_dw_on_narrow_tiles(M, K, N, BM, p, parts, planes, dtype, out):
         assert torch.equal(total.to(od), dw)
     if M * K * N <= 1 << 26 and od == torch.float32:
         assert_close(f64(dw), orc.bwd_dw(f64(X), f64(dY), keep, BM, 128, p), "narrow dW")
+
+
+@pytest.mark.parametrize("M,K,N", [(1024, 256, 256), (4096, 128, 72)])       # parts in the accumulators; in planes
+def test_infinities_and_nan_of_kept_blocks_only(M, K, N):
+    print("dw_narrow non-finite", M, K, N, flush=True)
+    inf, nan, p = float("inf"), float("nan"), 0.5
+    X, W, dY = make_custom(M, K, N, "bf16", seed=9)
+    keep = torch.from_numpy(orc.mask(M // 128, K // 128, p, 5, 1).astype(bool))
+    rows = keep.repeat_interleave(128, 0).repeat_interleave(128, 1)
+    kept, dropped = torch.nonzero(keep), torch.nonzero(~keep)
+    for (i, j), v in ((kept[0], inf), (kept[-1], -inf), (kept[len(kept) // 2], nan)):
+        X[i * 128 + 5, j * 128 + 17] = v
+    for i, j in dropped[:2]:
+        X[i * 128, j * 128:(j + 1) * 128] = nan
+    dY[kept[1][0] * 128 + 64, 7] = inf
+    Xm = torch.where(rows, X.double(), torch.zeros((), dtype=torch.float64))
+    # the products block row by block row: a dropped block contributes nothing, also against an infinite dY
+    ref = torch.zeros(K, N, dtype=torch.float64)
+    for i, j in kept:
+        r, c = slice(i * 128, (i + 1) * 128), slice(j * 128, (j + 1) * 128)
+        ref[c] += Xm[r, c].t() @ dY[r].double()
+    ref /= 1 - p
+    m = sdrop.sdrop_mask(M, K, 128, 128, p, 5, 1)
+    outs = [sdrop.sdrop_bwd_dw(X.cuda(), dY.cuda(), m, out_dtype=torch.float32),
+            sdrop.sdrop_bwd(dY.cuda(), W.cuda(), X.cuda(), m, out_dtype=torch.float32)[1]]
+    for dw in outs:
+        dw = dw.cpu().double()
+        assert torch.equal(dw.isnan(), ref.isnan()) and torch.equal(dw.isinf(), ref.isinf()) and torch.equal(dw[dw.isinf()], ref[ref.isinf()])
+        ok = ref.isfinite()
+        assert ok.any() and float((dw[ok] - ref[ok]).norm() / ref[ok].norm()) < 1e-5

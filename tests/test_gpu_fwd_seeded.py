@@ -75,7 +75,10 @@ def _case(X, W, BM, BK, p, seed, stream, tag, oracle_product=True, out_dtypes=(N
 
 @pytest.mark.parametrize("M,K,N,BM,BK,dtype,p,seed,stream", [
     (256, 256, 256, 64, 64, "f16", 0.5, 0, 0),                 # the tiny workload: 4 x 4 blocks, fewer tiles than pieces
-    (1024, 1024, 1000, 128, 128, "bf16", 0.5, 3, 1),           # ragged last tile column
+    (1024, 1024, 1000, 128, 128, "bf16", 0.5, 3, 1),           # ragged last tile column, 128 x 128 tiles
+    (8192, 128, 1000, 128, 128, "bf16", 0.5, 13, 1),           # ragged last tile column, 128 x 256 tiles
+    (16384, 128, 520, 128, 64, "f16", 0.3, 14, 1),             # the same with more tiles than CUs
+    (8192, 256, 1024, 128, 128, "f16", 0.0, 15, 1),            # whole 128 x 256 tiles, nothing dropped
     (640, 384, 264, 64, 64, "f16", 0.3, 4, 2),                 # 10 x 6 blocks, ragged
     (128, 8192, 512, 128, 128, "bf16", 0.5, 5, 3),             # one block row, 64 block columns (the widest grid)
     (8192, 2048, 256, 64, 64, "f16", 0.5, 6, 4),               # 128 x 32 blocks: the largest grid a workgroup draws

@@ -37,6 +37,7 @@ SHAPES = [
     (4096, 1024, 72, 128, 128, torch.bfloat16),      # 72 columns: ragged tile column, ragged slice (72 = 64 + 8)
     (4096, 1024, 72, 64, 64, torch.float16),
     (1024, 1024, 264, 128, 128, torch.bfloat16),     # one whole tile column and 8 columns more
+    (8192, 128, 1000, 128, 128, torch.bfloat16),     # ragged 128 x 256 tiles in the forward (the ones above take 128 x 128)
     (128, 4096, 1000, 128, 128, torch.float16),      # a single block row
     (4096, 128, 520, 128, 128, torch.bfloat16),      # a single block column
     (2048, 2048, 256, 128, 64, torch.bfloat16),

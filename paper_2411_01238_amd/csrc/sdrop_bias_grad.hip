@@ -109,8 +109,9 @@ void launch_parts(const void *dz, int64_t ld, const MaskView &V, float *out, int
 // Bound by memory: the matrix is read once.  A workgroup sums L x 8 columns (16-byte loads, whole 512-byte runs of a row
 // for L = 32) over its part of the rows, eight rows in flight per thread; the row groups meet in LDS in a fixed order and
 // an fp32 row per part goes to the workspace.  About eight workgroups per CU in all, at most 256 parts, and about
-// eight steps' worth of rows or more each (one full batch of loads per thread) where there are that many.  16384 x 3072 bf16: 15.7 us (6.4 TB/s, part of it from the Infinity Cache) plus 4.2 for the
-// second launch, against 46 us for a library sum.
+// eight steps' worth of rows or more each (one full batch of loads per thread) where there are that many.
+// 16384 x 3072 bf16: 15.7 us (6.4 TB/s, part of it from the Infinity Cache) plus 4.2 for the second launch, against 46 us
+// for a library sum.
 template <class T, int L>
 __global__ __launch_bounds__(256) void dense_colsum_kernel(const T *src, int64_t ld, int64_t M, int64_t N, int64_t rows_per_part, float *part)
 {

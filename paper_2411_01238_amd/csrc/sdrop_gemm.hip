@@ -325,8 +325,8 @@ DxPlan dx_plan(const GemmParams &P, bool fused)
 //   4096^2 x 1024 45.0 -> 41.0 / 42.9 -> 38.5 / 32.3 -> 28.5;  4096 x 1024^2 17.3 -> 14.2 / 17.5 -> 14.1 / 16.2 -> 12.9;
 //   4096 x 2048 x 896 25.0 -> 23.7 / 24.0 -> 22.5 / 23.2 -> 20.1;  2048^3 25.9 -> 21.0 / 24.9 -> 20.0 / 21.4 -> 16.2;
 //   16384 x 4096 x 256 53.5 -> 48.2 / 49.5 -> 45.2 / 41.3 -> 35.4;  112: 14336 x 1024 x 256 22.1 -> 18.8 / 23.4 -> 20.0 / 22.0 -> 18.5.
-// (At p = 0 the same shapes gave 1.00 to 1.30 of the wide form's speed in that run.)  Beyond half of the chip a second round of narrow tiles loses to one of wide ones (160 wide tiles, all
-// kept, K = 1024: 16.1 -> 20.6).
+// (At p = 0 the same shapes gave 1.00 to 1.30 of the wide form's speed in that run.)  Beyond half of the chip a second
+// round of narrow tiles loses to one of wide ones (160 wide tiles, all kept, K = 1024: 16.1 -> 20.6).
 bool fwd_narrow(const GemmParams &P)
 {
     const int64_t wide = P.MB * ((P.N + 255) / 256), ncu = cu_count();

@@ -426,6 +426,17 @@ int sdrop_fwd_seeded_bias(const void *X, const void *W, const void *bias, void *
                           int dtype, void *ws, size_t ws_bytes, void *stream, const sdrop_epilogue_t *epi);
 
 /*
+ * sdrop_fwd_seeded_bias with nothing dropped (p = 0), for a layer in inference: no mask object.  Same bits as that call
+ * (bias = NULL: as sdrop_fwd_seeded_ex) with any seed.  Not every shape has such a kernel: *done = 0 with SDROP_OK means
+ * that nothing was enqueued and the caller makes the call with a mask instead; *done = 1: Y is on its way.
+ *   bias   null, or as for sdrop_fwd_seeded_bias
+ *   Y      has type `dtype`
+ *   BM, BK the layer's mask block (checked as in every call; the kernel's tiles do not depend on it)
+ */
+int sdrop_fwd_dense(const void *X, const void *W, const void *bias, void *Y, int64_t M, int64_t K, int64_t N, int BM, int BK,
+                    int dtype, void *stream, const sdrop_epilogue_t *epi, int *done);
+
+/*
  * The gradient of that bias: db[n] = sum over all rows m of dY[m, n], accumulated in fp32, rounded once to `dtype`.
  *   dY[M,N]   rows ld_dy elements apart (0 = N; else >= N, a multiple of 8); N a multiple of 8
  *   db        N values of type `dtype`, 16-byte aligned

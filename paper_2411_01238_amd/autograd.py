@@ -23,7 +23,12 @@ def _kernel_readable(t):
 
 class _SparseDropMatmul(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, x, w, bias, p, BM, BK, seed, rng_stream, w_layout):
+    def forward(ctx, x, w, bias, p, BM, BK, seed, rng_stream, w_layout, inference):
+        if inference and p == 0.0:
+            # nothing is dropped and no backward follows: the product without a mask, where there is a kernel for it
+            y = sdrop.sdrop_fwd_dense(x, w, BM, BK, w_layout=w_layout, bias=bias)
+            if y is not None:
+                return y
         # the mask and eq. (1), plus the bias if there is one, in one call (one launch for block grids up to 128 x 64);
         # m serves the backward
         y, m = sdrop.sdrop_fwd_seeded(x, w, BM, BK, p, seed, rng_stream, w_layout=w_layout, bias=bias)
@@ -50,7 +55,7 @@ class _SparseDropMatmul(torch.autograd.Function):
             # (as a torch operation where the caller differentiates the gradient once more, it is linear in dy, and where dy
             # is not memory that the kernel can read)
             db = dy.sum(0) if (torch.is_grad_enabled() and dy.requires_grad) or not _kernel_readable(dy) else sdrop.sdrop_col_sum(dy)
-        return dx, dw, db, None, None, None, None, None, None
+        return dx, dw, db, None, None, None, None, None, None, None
 
 
 def sparsedrop_matmul(x, w, p, BM=128, BK=128, seed=0, rng_stream=0, weight_layout="kn"):
@@ -61,7 +66,7 @@ def sparsedrop_matmul(x, w, p, BM=128, BK=128, seed=0, rng_stream=0, weight_layo
     its gradient.
     """
     wl = {"kn": sdrop.W_KN, "nk": sdrop.W_NK}[weight_layout]
-    return _SparseDropMatmul.apply(x, w, None, float(p), int(BM), int(BK), int(seed), int(rng_stream), wl)
+    return _SparseDropMatmul.apply(x, w, None, float(p), int(BM), int(BK), int(seed), int(rng_stream), wl, not torch.is_grad_enabled())
 
 
 def _fusable_bias(bias, x, n):
@@ -171,7 +176,8 @@ class SparseDropLinear(torch.nn.Module):
         nk = self.weight_layout == "nk"
         bias = self.bias
         if bias is not None and _fusable_bias(bias, x2, self.weight.shape[0 if nk else 1]):
-            y = _SparseDropMatmul.apply(x2, self.weight, bias, p, self.BM, self.BK, self.seed, self.calls, sdrop.W_NK if nk else sdrop.W_KN)
+            y = _SparseDropMatmul.apply(x2, self.weight, bias, p, self.BM, self.BK, self.seed, self.calls, sdrop.W_NK if nk else sdrop.W_KN,
+                                         not torch.is_grad_enabled())
         else:
             y = sparsedrop_matmul(x2, self.weight, p, self.BM, self.BK, self.seed, self.calls, self.weight_layout)
             if bias is not None:

@@ -61,11 +61,15 @@ template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, 
 // The forward product by the kernel that draws its own mask and writes the mask object (see gemm_seeded_grid.h).
 // Returns -1 when the device does not grant the LDS the launch needs.
 template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream_t stream);
+// The forward product with nothing dropped, without a mask object (128-row tiles, 16-bit output).
+// Returns -1 when the device does not grant the LDS the launch needs.
+template <class T> int fwd_dense_typed(const GemmParams &P, hipStream_t stream);
 #define SDROP_EXTERN(T)                                                                \
     extern template int dispatch_typed<FWD, T>(bool, GemmParams &, hipStream_t);       \
     extern template int dispatch_typed<DX, T>(bool, GemmParams &, hipStream_t);        \
     extern template int dispatch_typed<DW, T>(bool, GemmParams &, hipStream_t);        \
     extern template int fwd_seeded_typed<T>(bool, const GemmParams &, hipStream_t);    \
+    extern template int fwd_dense_typed<T>(const GemmParams &, hipStream_t);           \
     extern template int bwd_fused_typed<T>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t)
 SDROP_EXTERN(F16);
 SDROP_EXTERN(BF16);

@@ -144,6 +144,34 @@ int launch_fwd_plain(const GemmParams &P, hipStream_t stream)
     return hip_status(hipGetLastError());
 }
 
+// eq. (1) with nothing dropped, without a mask object: 128-row tiles (whole tile columns; with a [K,N] weight also a ragged
+// last one).  Returns -1 when the device does not grant the LDS.
+template <class T, int TN, bool W_NK, bool BIAS>
+int launch_fwd_dense(const GemmParams &P, hipStream_t stream)
+{
+    using OutT = typename In<T>::out16;
+    constexpr int P_LDS = persistent_lds(128, TN);
+    auto k_whole = fwd_dense_kernel<T, OutT, TN, false, W_NK, BIAS>;
+    auto k_edge = fwd_dense_kernel<T, OutT, TN, !W_NK, W_NK, BIAS>;
+    static int ok = -1;     // per instantiation: does the device grant that much LDS?
+    if (ok < 0) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        ok = (e == hipSuccess);
+        if (!ok) (void)hipGetLastError();
+    }
+    if (!ok) return -1;
+    GemmParams Q = P;
+    Q.n_tiles = (int)((P.N + TN - 1) / TN);
+    Q.splits = 1;
+    Q.total_tiles = Q.MB * Q.n_tiles;
+    const int ncu = cu_count();
+    auto k = P.N % TN != 0 ? k_edge : k_whole;
+    hipLaunchKernelGGL(k, dim3((unsigned)(Q.total_tiles < ncu ? Q.total_tiles : ncu)), dim3(512), P_LDS, stream, Q);
+    return hip_status(hipGetLastError());
+}
+
 // eq. (1) with the weight as [N,K], read in place (N a multiple of 256, no tail but the 16-bit bias with BIAS); SEEDED:
 // the mask drawn in the same launch (block grids of at most 128 x 64).  Returns -1 when the device does not grant the LDS.
 template <class T, class OutT, int TM, int TN = 256, bool SEEDED = false, bool BIAS = false>
@@ -502,6 +530,17 @@ template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream
     if (narrow) return o32 ? launch_fwd_seeded<T, float, 128, 128>(P, stream) : launch_fwd_seeded<T, O16, 128, 128>(P, stream);
     if (P.BM == 128) return o32 ? launch_fwd_seeded<T, float, 128>(P, stream) : launch_fwd_seeded<T, O16, 128>(P, stream);
     return o32 ? launch_fwd_seeded<T, float, 64>(P, stream) : launch_fwd_seeded<T, O16, 64>(P, stream);
+}
+
+template <class T> int fwd_dense_typed(const GemmParams &P, hipStream_t stream)
+{
+    const bool narrow = fwd_narrow(P);
+    if (P.w_nk) {
+        if (P.bias16) return narrow ? launch_fwd_dense<T, 128, true, true>(P, stream) : launch_fwd_dense<T, 256, true, true>(P, stream);
+        return narrow ? launch_fwd_dense<T, 128, true, false>(P, stream) : launch_fwd_dense<T, 256, true, false>(P, stream);
+    }
+    if (P.bias16) return narrow ? launch_fwd_dense<T, 128, false, true>(P, stream) : launch_fwd_dense<T, 256, false, true>(P, stream);
+    return narrow ? launch_fwd_dense<T, 128, false, false>(P, stream) : launch_fwd_dense<T, 256, false, false>(P, stream);
 }
 
 template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, const GemmParams &Pdx, const GemmParams &Pdw,

@@ -405,12 +405,16 @@ constexpr int waitcnt_lgkm0_only() { return 15 | (3 << 14) | (7 << 4) | (0 << 8)
 // W_NK for eq. (3): the gradient goes out as [N,K].  Operands and loads are as ever; the MFMAs take their operands the
 // other way round, which leaves the transposed 32 x 32 blocks in the accumulators, and the epilogue writes the tile
 // transposed (Compute::store_t), into the output or into planes of partial sums laid out [N][K].
+//
+// DENSE (the forward): nothing is dropped and there is no mask object at all: block rows in their own order, every list
+// 0, 1, .. KB - 1.
 template <int OP, class T, class OutT, int TM, int TN, int WM, int WN, int TAIL, bool RAGN = false, bool SEEDED = false,
-          bool W_NK = false>
+          bool W_NK = false, bool DENSE = false>
 __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const int G, const int w)
 {
     static_assert(OP == FWD || OP == DW, "output-sparse dX is not handled here");
     static_assert(!SEEDED || OP == FWD, "only the forward kernel draws its own mask");
+    static_assert(!DENSE || (OP == FWD && !SEEDED), "only the forward runs without a mask");
     static_assert(TAIL != kTailBias16 || OP == FWD, "the 16-bit bias belongs to the forward product");
     static_assert(!W_NK || (!RAGN && (TAIL == kTailNone || TAIL == kTailBias16)), "[N,K] weights: the plain products on whole tiles");
     static_assert(!W_NK || OP == FWD || (TM / WM / 32) % (128 / (32 * (int)sizeof(OutT))) == 0, "the transposed tile's rows must fill 128-byte pieces");
@@ -512,7 +516,7 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
         auto level3 = [&](Meta &m) __attribute__((always_inline)) { m.e0 = entry(m, 0); m.e1 = entry(m, 1); };
 
         Meta cur, n1, n2, n3;
-        if constexpr (!SEEDED) {
+        if constexpr (!SEEDED && !DENSE) {
             n1 = level1(0); n2 = level1(1); n3 = level1(2);
             if (!mask_ok()) return;
             level2(n1); level3(n1);
@@ -542,6 +546,14 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
                     nsteps = (int)__popcll(word) << sub_shift;
                     e_cur = word ? (int)__builtin_ctzll(word) : 0;
                     w_rem = word & (word - 1);
+                } else if constexpr (DENSE) {
+                    const int t = tile_of(k);
+                    if (t >= total) { ended = true; return false; }
+                    ord_cur = t / per_line;
+                    nt_cur = t % per_line;
+                    s = 0;
+                    nsteps = P.KB << sub_shift;
+                    e_cur = 0;
                 } else {
                     cur = n1;
                     if (cur.t >= total) { ended = true; return false; }
@@ -582,6 +594,8 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
                 if constexpr (SEEDED) {
                     e_cur = w_rem ? (int)__builtin_ctzll(w_rem) : 0;
                     w_rem &= w_rem - 1;
+                } else if constexpr (DENSE) {
+                    ++e_cur;
                 } else {
                     e_cur = e_nxt;
                     e_nxt = entry(cur, (s >> sub_shift) + 1);
@@ -630,7 +644,7 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
     if constexpr (SEEDED) {
         // this wavefront's pieces of the mask object, while the first operands are on their way
         sg.write_pieces(P, w * NW + wave, G * NW);
-    } else {
+    } else if constexpr (!DENSE) {
         const int ord0_v = c_order(0), ord1_v = c_order(1), ord2_v = c_order(2);
         if (!mask_ok()) return;
         ord0 = uni(ord0_v);
@@ -656,6 +670,9 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
         if constexpr (SEEDED) {
             ord0 = sg.row_of_rank(t / per_line);
             len0 = sg.row_count(ord0);
+        } else if constexpr (DENSE) {
+            ord0 = t / per_line;
+            len0 = P.KB;
         } else {
             // requests for the tiles after this one; consumed after this tile's slices
             cnt1_v = c_count(ord1);
@@ -694,7 +711,7 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
                 const int t0 = st0; st0 = st1; st1 = st2; st2 = t0;
             }
         }
-        if constexpr (!SEEDED) {
+        if constexpr (!SEEDED && !DENSE) {
             // the look-ups have had the whole tile to arrive and no store is in flight: this wait is free
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_only(0));
             len0 = uni(c_len(k + 1, cnt1_v));
@@ -733,6 +750,13 @@ template <class T, class OutT, int TM, int TN, bool SEEDED, bool BIAS>
 __global__ __launch_bounds__(512) void fwd_nk_kernel(GemmParams P)
 {
     gemm_persistent_body<FWD, T, OutT, TM, TN, TN == 256 ? 1 : 2, TN == 256 ? 4 : 2, BIAS ? kTailBias16 : kTailNone, false, SEEDED, true>(P, gridDim.x, blockIdx.x);
+}
+
+// eq. (1) with nothing dropped and no mask object (see DENSE above); W_NK: the weight as [N,K]; BIAS: plus a 16-bit bias.
+template <class T, class OutT, int TN, bool RAGN, bool W_NK, bool BIAS>
+__global__ __launch_bounds__(512) void fwd_dense_kernel(GemmParams P)
+{
+    gemm_persistent_body<FWD, T, OutT, 128, TN, TN == 256 ? 1 : 2, TN == 256 ? 4 : 2, BIAS ? kTailBias16 : kTailNone, RAGN, false, W_NK, true>(P, gridDim.x, blockIdx.x);
 }
 
 // The forward kernel that draws its own mask and writes the mask object as well (see SEEDED above).

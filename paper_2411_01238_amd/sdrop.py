@@ -24,7 +24,7 @@ MASK_NUNITS_OFFSET = 80
 
 EXPORTS = ("sdrop_strerror", "sdrop_last_hip_error", "sdrop_status", "sdrop_set_tuning", "sdrop_mask_layout", "sdrop_mask_bytes",
            "sdrop_mask", "sdrop_mask_split", "sdrop_mask_from_bits", "sdrop_mask_bits", "sdrop_workspace_bytes",
-           "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_fwd_seeded_bias", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
+           "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_fwd_seeded_bias", "sdrop_fwd_dense", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
            "sdrop_bwd", "sdrop_bwd_ex", "sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex", "sdrop_workspace_bytes_ex",
            "sdrop_producer", "sdrop_producer_ex",
            "sdrop_bias_grad_workspace_bytes", "sdrop_bias_grad", "sdrop_col_sum_workspace_bytes", "sdrop_col_sum")
@@ -105,6 +105,8 @@ def lib():
         L.sdrop_fwd_seeded_bias.argtypes = [vp, vp, vp, vp, sz, vp, i64, i64, i64, ci, ci, dbl, u64, u64, ci, vp, sz, vp,
                                             ctypes.POINTER(Epilogue)]
         L.sdrop_fwd_seeded_bias.restype = ci
+        L.sdrop_fwd_dense.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, ci, ci, vp, ctypes.POINTER(Epilogue), ctypes.POINTER(ci)]
+        L.sdrop_fwd_dense.restype = ci
         L.sdrop_bwd_dw_static.argtypes = [vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, ci, vp]
         L.sdrop_bwd_dw_static.restype = ci
         for name in ("sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex"):
@@ -445,6 +447,29 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
                                            _DTYPES[dtype], _DTYPES[out_dtype], ws_ptr, ws_bytes, _stream(), ctypes.byref(e))
     _check(rc, "sdrop_fwd_seeded")
     return out, m
+
+
+def sdrop_fwd_dense(X, W, BM, BK, w_layout=W_KN, bias=None):
+    """eq. (1) with nothing dropped, without a mask object: Y of X's type, the bits of sdrop_fwd_seeded with p = 0; None
+    where the library has no such kernel for the shape (call sdrop_fwd_seeded then)."""
+    M, K = X.shape
+    K2, N = W.shape if w_layout == W_KN else (W.shape[1], W.shape[0])
+    if K2 != K:
+        raise SdropError(ESHAPE, "sdrop_fwd_dense")
+    dtype = X.dtype
+    if W.dtype != dtype:
+        raise ValueError("operands must have the same dtype")
+    if dtype not in (torch.float16, torch.bfloat16):
+        raise SdropError(EDTYPE, "sdrop_fwd_dense")
+    if bias is not None and (bias.dtype != dtype or tuple(bias.shape) != (N,)):
+        raise ValueError("bias must have one value of the operands' dtype per output column")
+    out = torch.empty((M, N), dtype=dtype, device=X.device)
+    (xp, ldx), (wp, ldw) = _mat(X, "X"), _mat(W, "W")
+    e = Epilogue(ld_a=ldx, ld_b=ldw, ld_out=N, w_layout=int(w_layout))
+    done = ctypes.c_int(0)
+    _check(lib().sdrop_fwd_dense(xp, wp, _dev(bias, "bias") if bias is not None else None, out.data_ptr(), M, K, N, BM, BK,
+                                 _DTYPES[dtype], _stream(), ctypes.byref(e), ctypes.byref(done)), "sdrop_fwd_dense")
+    return out if done.value else None
 
 
 def sdrop_bwd_dx(dY, W, mask, out_dtype=None, out=None, ws=None):

@@ -55,6 +55,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32q;      // an accumulator quad
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -62,18 +63,14 @@ template <class T> struct In;
 template <> struct In<F16> {
     using vec = f16x8;
     using out16 = _Float16;
-    __device__ static f32x16 mfma(vec a, vec b, f32x16 c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-    }
+    __device__ static f32q mfma(vec a, vec b, f32q c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+    __device__ static f32x16 mfma(vec a, vec b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 template <> struct In<BF16> {
     using vec = bf16x8;
     using out16 = __bf16;
-    __device__ static f32x16 mfma(vec a, vec b, f32x16 c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-    }
+    __device__ static f32q mfma(vec a, vec b, f32q c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+    __device__ static f32x16 mfma(vec a, vec b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 };
 
 // Compile-time loop: f(integral_constant<int, 0>{}), ..., f(integral_constant<int, N-1>{}).
@@ -87,6 +84,7 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 constexpr int TK = 64;           // reduction slice staged per step
 constexpr int kThreads = 256;    // 4 wavefronts per workgroup
 // LDS stages: three for tiles of 128 rows (one workgroup per CU; the deeper prefetch measured
@@ -225,15 +223,10 @@ __device__ __forceinline__ uint4 gate16(uint4 out, uint4 gate)
     return __builtin_bit_cast(uint4, o);
 }
 
-// Slot swizzle of an LDS operand row: a 3-bit value XORed into the chunk index.
-// With m = (r>>1)&7: rotate m left by one and flip with bits 4,5 of r.  Measured
-// conflict-free for ds_read_b128 of 32 consecutive rows x 2 chunks per wavefront,
-// for row-wise 16-byte stores and for the transposed stores below.
-__device__ __forceinline__ int swz(int r)
-{
-    const int m = (r >> 1) & 7;
-    return (((m & 3) << 1) | (m >> 2)) ^ ((r >> 3) & 6);
-}
+// Slot swizzle of an LDS operand row: a 3-bit value XORed into the chunk index.  Rows two apart take another slot,
+// so the 16 rows of an operand read cover all banks (measured 128 bytes per clock), and it is the same for every 16 rows:
+// one lane address serves all the reads of a half slice.
+__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 // Byte offset of 16-byte chunk c (0..7) of row r in an LDS operand tile.
 __device__ __forceinline__ int lds_off(int r, int c) { return r * 128 + (((c ^ swz(r)) & 7) << 4); }
 
@@ -254,23 +247,22 @@ __device__ __forceinline__ void dma16(const char *sbase, uint32_t voff, const ch
 // apart in HBM (reduction index contiguous).  One instruction of one wavefront fills
 // 1 KiB = 8 LDS rows: lane l lands in row 8*I + l/8, slot l%8, so it fetches chunk
 // (l%8) ^ swz(row) of that row.  Wavefront w of NW issues instructions I = w + NW*i.  Row of
-// this lane in pass i is r = 8*NW*i + r0; of the pass offset swz(r) sees only bit 5, so two
-// lane offsets serve every pass and the rest of the address is uniform.
+// this lane in pass i is r = 8*NW*i + r0; swz(r) does not see the pass, so one lane offset serves
+// every pass and the rest of the address is uniform.
 template <int ROWS, int NGRP, int NW> struct DmaK {
     static constexpr int PASS_ROWS = 8 * NW;              // rows filled by one pass of the NW wavefronts
     static constexpr int PER_WAVE = ROWS / PASS_ROWS, GROUP_ROWS = ROWS / NGRP;
-    static_assert(GROUP_ROWS % PASS_ROWS == 0 && ROWS % PASS_ROWS == 0, "row groups must cover whole passes");
-    uint32_t voff_even, voff_odd;
-    int wave, chunk_even;                                 // chunk_even: the 16-byte chunk this lane fetches in even passes
+    static_assert(GROUP_ROWS % PASS_ROWS == 0 && ROWS % PASS_ROWS == 0 && PASS_ROWS % 16 == 0, "row groups must cover whole passes");
+    uint32_t voff;
+    int wave, chunk;                                      // chunk: the 16-byte chunk of its rows that this lane fetches
     __device__ __forceinline__ void init(int64_t ld_bytes, int w)
     {
         const int lane = threadIdx.x & 63;
         wave = w;
         const int r0 = 8 * wave + (lane >> 3);
         const uint32_t row_off = (uint32_t)r0 * (uint32_t)ld_bytes;
-        chunk_even = (lane & 7) ^ swz(r0);
-        voff_even = row_off + (chunk_even << 4);
-        voff_odd = row_off + ((chunk_even ^ 4) << 4);
+        chunk = (lane & 7) ^ swz(r0);
+        voff = row_off + (chunk << 4);
     }
     // pass i of this wavefront.  nch < 8: the slice is the ragged last one of the reduction and holds
     // only nch valid 16-byte chunks per row; lanes whose chunk lies beyond fetch nothing and clear
@@ -279,39 +271,42 @@ template <int ROWS, int NGRP, int NW> struct DmaK {
     {
         const int g = (PASS_ROWS * i) / GROUP_ROWS;       // uniform: pass i covers rows PASS_ROWS*i ..
         const char *sbase = base[g] + (int64_t)(PASS_ROWS * i - g * GROUP_ROWS) * ld_bytes;
-        // bit 5 of the row (the only bit of a pass offset that swz() sees) picks the lane offset
-        const bool odd = ((PASS_ROWS * i) & 32) != 0;
         char *const dst = lds + (wave + NW * i) * 1024;
         if (nch == 8) {
-            dma16(sbase, odd ? voff_odd : voff_even, dst);
+            dma16(sbase, voff, dst);
         } else {
             const int lane = threadIdx.x & 63;
-            if ((odd ? chunk_even ^ 4 : chunk_even) < nch) dma16(sbase, odd ? voff_odd : voff_even, dst);
+            if (chunk < nch) dma16(sbase, voff, dst);
             else *reinterpret_cast<uint4 *>(dst + lane * 16) = make_uint4(0, 0, 0, 0);
         }
     }
 };
 
 // Slot swizzle of an LDS tile kept as it lies in HBM when the reduction index is the strided
-// one: [64 reduction rows][ROWS contiguous].  The transposing read of one 16-lane group
-// touches 4 consecutive rows x 32 bytes; XORing the 64-byte slot index with (row & 3) (with
-// (row>>1)&1 for 128-byte rows) keeps those rows on different banks.
+// one: [64 reduction rows][ROWS contiguous].  The transposing read of 32 lanes touches, for operands of 32
+// columns, 4 consecutive rows x 64 bytes; for operands of 16 columns, rows k .. k+3 and k+8 .. k+11 x 32 bytes.
+// XORing the 64-byte slot index with (row & 3) and the 32-byte half with bit 3 of the row keeps either on different
+// banks (without bit 3 the second costs two conflict cycles per read, counted).  128-byte rows, two of which share a round
+// of the banks, are read as 32 columns only: the 64-byte slot with bit 1 of the row.
 template <int ROWS> __device__ __forceinline__ int swz_t(int k)
 {
-    return ROWS >= 128 ? ((k & 3) << 2) : (((k >> 1) & 1) << 2);
+    return ROWS >= 128 ? ((k & 3) << 2) | (((k >> 3) & 1) << 1) : (((k >> 1) & 1) << 2);
 }
 
 // HBM -> LDS without registers for an operand tile [64][ROWS] (ROWS contiguous, rows ld_bytes
 // apart).  One instruction fills 1 KiB = 1024/(2*ROWS) tile rows; lane l lands at byte 16*l of
-// it and fetches the chunk whose swizzled slot that is.  Row k = RPI*I + kl with I = w + NW*i:
-// k & 3 (or (k>>1)&1) does not depend on i, so one lane offset serves every pass.
+// it and fetches the chunk whose swizzled slot that is.  Row k = RPI*I + kl with I = w + NW*i: of the
+// bits that swz_t() sees only bit 3 depends on i, and only for 256-wide tiles, where it is i's lowest: two lane
+// offsets, for even and odd passes (the same one otherwise).
 template <int ROWS, int NW> struct DmaT {
     static constexpr int ROW_BYTES = 2 * ROWS, RPI = 1024 / ROW_BYTES;       // rows per instruction
     static constexpr int PER_WAVE = ROWS / (8 * NW);
     static_assert(ROWS % (8 * NW) == 0, "every wavefront issues whole instructions");
     static_assert(ROWS == 64 || ROWS == 128 || ROWS == 256, "unsupported tile edge");
-    uint32_t voff;
-    int wave, chunk;                                         // chunk: the 16-byte chunk of the row this lane fetches
+    static constexpr int ODD = ROWS == 256 ? 2 : 0;          // what an odd pass adds (XOR) to the chunk
+    static_assert(NW == 4, "the passes' row bits");
+    uint32_t voff[2];
+    int wave, chunk;                                         // chunk: the 16-byte chunk of the row this lane fetches in even passes
     __device__ __forceinline__ void init(int64_t ld_bytes, int w)
     {
         const int lane = threadIdx.x & 63;
@@ -320,7 +315,8 @@ template <int ROWS, int NW> struct DmaT {
         const int cpos = ((lane * 16) % ROW_BYTES) >> 4;     // 16-byte slot within the row
         const int k0 = RPI * wave + kl;
         chunk = cpos ^ swz_t<ROWS>(k0);
-        voff = (uint32_t)kl * (uint32_t)ld_bytes + (chunk << 4);
+        voff[0] = (uint32_t)kl * (uint32_t)ld_bytes + (chunk << 4);
+        voff[1] = (uint32_t)kl * (uint32_t)ld_bytes + ((chunk ^ ODD) << 4);
     }
     // nch < ROWS / 8: the tile hangs over the end of the rows (the last tile column of a ragged N)
     // and only its first nch >= 1 chunks per row exist: the other lanes fetch nothing, and their
@@ -328,8 +324,9 @@ template <int ROWS, int NW> struct DmaT {
     __device__ __forceinline__ void issue(const char *const (&base)[1], int64_t ld_bytes, char *lds, int i, int nch = ROWS / 8) const
     {
         const int I = wave + NW * i;
-        if (nch == ROWS / 8) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, voff, lds + I * 1024);
-        else if (chunk < nch) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, voff, lds + I * 1024);
+        const uint32_t vo = voff[ODD && (i & 1)];
+        if (nch == ROWS / 8) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, vo, lds + I * 1024);
+        else if ((ODD && (i & 1) ? chunk ^ ODD : chunk) < nch) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, vo, lds + I * 1024);
     }
 };
 
@@ -432,21 +429,33 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
     }
 };
 
-// MFMA operand for the 32 rows (or columns) starting at `base32` of an LDS operand tile,
-// reduction indices [kk*16, kk*16+16): lane l gets index base32 + l%32, reduction 8*(l/32)..+8.
+// The matrix instruction of a kernel: v_mfma_f32_32x32x16 or (S16) v_mfma_f32_16x16x32.  The sums are the same bits (a
+// reduction of 32 in one instruction adds up as two of 16 in turn do).  Beside the operand reads from LDS the 16 x 16 form
+// sustains 1.90 PFLOP/s against 1.70 (a loop of either on all CUs, random bf16; the chip holds a higher clock), but a
+// half slice of it is twice the operands at a time.  Measured, 32 -> 16, us: both operands read by rows (eq. 2, eq. 1 with an
+// [N,K] weight), 4096^3: p = 0 117 -> 107 and 112 -> 103, p = 0.5 (single blocks) 89 -> 85; eq. 1 with a [K,N] weight on
+// 256-wide tiles 69 -> 66 at p = 0.5, 64-row tiles (8192 x 1024^2) 19.2 -> 18.6; but eq. 3, whose operands both need
+// transposing reads, 64 -> 68 and 114 -> 120, eq. 1 on 128-wide tiles 9.67 -> 9.86 (1024^3), 29.5 -> 29.8 (4096^2 x 1024), and
+// 64-row tiles with a workgroup per tile 6.9 -> 7.1 (256^3), 28.3 -> 28.8 (dX of 8192 x 1024 x 1000).
+
+// MFMA operand for the 32 (S16: 16) rows or columns starting at `base` of an LDS operand tile,
+// reduction indices [16 kk, 16 kk + 16) (S16: [32 kk, 32 kk + 32)): lane l gets index base + l%32, reduction 8*(l/32)..+8
+// (S16: base + l%16, 8*(l/16)..+8).
 // TR = false: tile [rows][64], one ds_read_b128.  TR = true: tile [64][ROWS] as in HBM, two
 // transposing reads (ds_read_b64_tr_b16): within a group of 16 lanes, lane q loads 4 elements
 // of row q/4 at columns 4*(q%4).. and receives column q of that 4 x 16 patch.
-template <class T, bool TR, int ROWS>
-__device__ __forceinline__ typename In<T>::vec read_frag(const char *lds, int base32, int kk)
+template <class T, bool TR, int ROWS, bool S16>
+__device__ __forceinline__ typename In<T>::vec read_frag(const char *lds, int base, int kk)
 {
     const int l = threadIdx.x & 63;
     if constexpr (!TR) {
-        return *reinterpret_cast<const typename In<T>::vec *>(lds + lds_off(base32 + (l & 31), kk * 2 + (l >> 5)));
+        return *reinterpret_cast<const typename In<T>::vec *>(
+            lds + (S16 ? lds_off(base + (l & 15), kk * 4 + (l >> 4)) : lds_off(base + (l & 31), kk * 2 + (l >> 5))));
     } else {
+        static_assert(!S16 || ROWS >= 128, "see swz_t");
         constexpr int ROW_BYTES = 2 * ROWS;
-        const int k = kk * 16 + (l >> 5) * 8 + ((l & 15) >> 2);
-        const int col = base32 + ((l >> 4) & 1) * 16 + (l & 3) * 4;
+        const int k = S16 ? kk * 32 + (l >> 4) * 8 + ((l & 15) >> 2) : kk * 16 + (l >> 5) * 8 + ((l & 15) >> 2);
+        const int col = base + (S16 ? 0 : ((l >> 4) & 1) * 16) + (l & 3) * 4;
         const char *p = lds + k * ROW_BYTES + ((((col >> 3) ^ swz_t<ROWS>(k))) << 4) + ((col * 2) & 15);
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * ROW_BYTES));
@@ -455,9 +464,97 @@ __device__ __forceinline__ typename In<T>::vec read_frag(const char *lds, int ba
     }
 }
 
+// The accumulators of a 32 x 32 block, as four quads of four consecutive columns of one row (quad_row, quad_col) per lane.
+// S16: one quad per 16 x 16 block, quad q = 2 * (row half) + (column half).
+template <bool S16> struct Block;
+template <> struct Block<false> {
+    f32x16 v;
+    __device__ __forceinline__ f32q quad(int q) const { return f32q{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; }
+    __device__ __forceinline__ void set(int q, f32q x)
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * q + e] = x[e];
+    }
+};
+template <> struct Block<true> {
+    f32q v[4];
+    __device__ __forceinline__ f32q quad(int q) const { return v[q]; }
+    __device__ __forceinline__ void set(int q, f32q x) { v[q] = x; }
+};
+template <bool S16> __device__ __forceinline__ int quad_row(int q) { return S16 ? (q >> 1) * 16 + (int)(threadIdx.x & 15) : (int)(threadIdx.x & 31); }
+template <bool S16> __device__ __forceinline__ int quad_col(int q)
+{
+    const int l = threadIdx.x & 63;
+    return S16 ? (q & 1) * 16 + (l >> 4) * 4 : 8 * q + 4 * (l >> 5);
+}
+
+// A wavefront's MI x NI blocks of 32 x 32, a slice of 64 reduction indices: the slice in PARTS parts of one instruction's
+// depth, AF + BF operands and AF x BF = NM MFMAs each, in which order, and after which of them the next part's operands are
+// read.
+//   SINGLE (S16, 8 x 4 operands read by rows): every operand is read into the registers it had, right after the last
+//     MFMA that needed it.  The longer side is taken in two halves of four, so that each of the twelve is free at least 13
+//     MFMAs (208 clocks) before the next part needs it again: a second set of registers (48) spills beside the pair list's
+//     code.  With transposing reads, two per operand, the reads of a part are too many for its last 20 MFMAs.
+//   else: a second set, read in the order in which the next part's MFMAs first use it (A0, B0 .. , A1 ..).
+// NB: MFMAs of a slice's last part that precede its barrier; the next slice's operands are read behind it.
+template <int MI, int NI, bool S16, bool TR> struct SlicePlan {
+    static constexpr int PARTS = S16 ? 2 : 4, DEPTH = S16 ? 32 : 16, ROWS = S16 ? 16 : 32;
+    static constexpr int AF = MI * 32 / ROWS, BF = NI * 32 / ROWS, NM = AF * BF, NOPS = AF + BF;
+    static constexpr bool SINGLE = S16 && !TR && NM == 32 && (AF == 8 || BF == 8), LONG_A = AF == 8;
+    static constexpr int SETS = SINGLE ? 1 : 2;
+    static constexpr int NB = SINGLE ? 12 : NM >= 4 ? 2 : 0;
+    static constexpr int RPM_MIN = ceil_div(NOPS, NM - NB), RPM = 2 > RPM_MIN ? 2 : RPM_MIN;       // reads per MFMA (!S16)
+    static constexpr int long_of(int c) { return c / 16 * 4 + c % 4; }
+    static constexpr int short_of(int c) { return c % 16 / 4; }
+    static constexpr int a_of(int c) { return !SINGLE ? c / BF : LONG_A ? long_of(c) : short_of(c); }
+    static constexpr int b_of(int c) { return !SINGLE ? c % BF : LONG_A ? short_of(c) : long_of(c); }
+    static constexpr int set_of(int g) { return SINGLE ? 0 : g & 1; }
+    // reads, of the NOPS, that precede MFMA c of part g
+    static constexpr int reads_before(int g, int c)
+    {
+        const int c0 = g == PARTS - 1 ? NB : 0;
+        if (c < c0) return 0;
+        const int r = S16 ? ceil_div((c - c0) * NOPS, NM - c0) : (c - c0) * RPM;
+        return r < NOPS ? r : NOPS;
+    }
+    // calls read_a(i) / read_b(i) for the operands that are read after MFMA C of part G
+    template <int G, int C, class FA, class FB> __device__ __forceinline__ static void reads(FA &&read_a, FB &&read_b)
+    {
+        if constexpr (SINGLE) {
+            constexpr int l = C >= 28 ? C - 24 : C >= 12 && C < 16 ? C - 12 : -1, s = C >= 16 && C % 4 == 3 ? (C - 16) / 4 : -1;
+            if constexpr (s >= 0) {
+                if constexpr (LONG_A) read_b(std::integral_constant<int, s>{});
+                else read_a(std::integral_constant<int, s>{});
+            }
+            if constexpr (l >= 0) {
+                if constexpr (LONG_A) read_a(std::integral_constant<int, l>{});
+                else read_b(std::integral_constant<int, l>{});
+            }
+        } else {
+            constexpr int r0 = reads_before(G, C), r1 = reads_before(G, C + 1);
+            static_for<r1 - r0>([&](auto ri) __attribute__((always_inline)) {
+                constexpr int r = r0 + decltype(ri)::value;
+                if constexpr (r == 0) read_a(std::integral_constant<int, 0>{});
+                else if constexpr (r <= BF) read_b(std::integral_constant<int, r - 1>{});
+                else read_a(std::integral_constant<int, r - BF>{});
+            });
+        }
+    }
+    // MFMA of operands a and b into the blocks.  SWAP: see Compute::slice.
+    template <class T, int A, int B, bool SWAP, class Acc, class V> __device__ __forceinline__ static void mfma(Acc &acc, const V &va, const V &vb)
+    {
+        if constexpr (S16) {
+            f32q &d = acc[A / 2][B / 2].v[SWAP ? 2 * (B & 1) + (A & 1) : 2 * (A & 1) + (B & 1)];
+            d = SWAP ? In<T>::mfma(va, vb, d) : In<T>::mfma(vb, va, d);
+        } else {
+            f32x16 &d = acc[A][B].v;
+            d = SWAP ? In<T>::mfma(va, vb, d) : In<T>::mfma(vb, va, d);
+        }
+    }
+};
+
 // Scheduling recipe for one MFMA group: each of the NM MFMAs is followed by its share of
 // the LDS reads, global loads, VALU ops and LDS writes that were emitted with it.
-constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 template <int NM, int NDSR, int NVALU, int NDSW, int NVMEM>
 __device__ __forceinline__ void interleave()
 {

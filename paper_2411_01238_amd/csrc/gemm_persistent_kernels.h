@@ -10,20 +10,18 @@ namespace {
 
 // The computing side of a persistent kernel: one wavefront's accumulators and operand registers,
 // the MFMA schedule of one slice, and the epilogue.
-template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int WN> struct Compute {
+template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int WN, bool S16> struct Compute {
     static constexpr int WTM = TM / WM, WTN = TN / WN, MI = WTM / 32, NI = WTN / 32;
     static constexpr int A_BYTES = TM * TK * 2;
-    static constexpr int NM = MI * NI, NOPS = MI + NI;
-    // operand reads requested per MFMA (at least what fits the group)
-    static constexpr int RPM_MIN = ceil_div(NOPS, NM >= 4 ? NM - 2 : NM), RPM = 2 > RPM_MIN ? 2 : RPM_MIN;
+    using SP = SlicePlan<MI, NI, S16, A_TR || B_TR>;
     static constexpr int ESZ = (int)sizeof(OutT);
     static constexpr int STAGING = 32 * 128;         // output staging per wavefront: 32 rows of 128 bytes
     static constexpr int NIP = 128 / (32 * ESZ);     // 32-column accumulator blocks per 128-byte row
     static constexpr int NJ = NI / NIP;              // 128-byte column groups of the wavefront's sub-tile
     static_assert(NI % NIP == 0, "a wavefront's columns must fill whole 128-byte rows");
 
-    typename In<T>::vec fa[2][MI], fb[2][NI];
-    f32x16 acc[MI][NI];
+    typename In<T>::vec fa[SP::SETS][SP::AF], fb[SP::SETS][SP::BF];
+    Block<S16> acc[MI][NI];
     int wm, wn;
 
     __device__ __forceinline__ void zero()
@@ -33,11 +31,11 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+                for (int q = 0; q < 4; ++q) acc[mi][ni].set(q, f32q{0.f, 0.f, 0.f, 0.f});
     }
     // The sums of the parts of a reduction that are done (see FOLDS): adds the accumulators' part to them and clears the
     // accumulators, or, after the last part, leaves the whole sum in the accumulators.
-    f32x16 done[MI][NI];
+    Block<S16> done[MI][NI];
     __device__ __forceinline__ void fold(bool first_part, bool last_part)
     {
         if (first_part && last_part) return;
@@ -46,61 +44,52 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float v = first_part ? acc[mi][ni][r] : done[mi][ni][r] + acc[mi][ni][r];
-                    done[mi][ni][r] = v;
-                    acc[mi][ni][r] = last_part ? v : 0.f;
+                for (int q = 0; q < 4; ++q) {
+                    const f32q a = acc[mi][ni].quad(q), v = first_part ? a : done[mi][ni].quad(q) + a;
+                    done[mi][ni].set(q, v);
+                    acc[mi][ni].set(q, last_part ? v : f32q{0.f, 0.f, 0.f, 0.f});
                 }
     }
-    // operands of the first quarter of the slice in stage `st`
+    // operands of the first part of the slice in stage `st`
     __device__ __forceinline__ void first(const char *st)
     {
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) fa[0][mi] = read_frag<T, A_TR, TM>(st, wm * WTM + mi * 32, 0);
+        for (int i = 0; i < SP::AF; ++i) fa[0][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, 0);
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) fb[0][ni] = read_frag<T, B_TR, TN>(st + A_BYTES, wn * WTN + ni * 32, 0);
+        for (int i = 0; i < SP::BF; ++i) fb[0][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, 0);
     }
-    // One slice: 4 quarters of NM MFMAs.  On entry the first quarter's operands are in flight to
-    // register set 0; each MFMA is followed by up to RPM operand reads for the next quarter, in the
-    // order that quarter's MFMAs (A index major) first use them: A0, B0 .. B(NI-1), A1 .. A(MI-1).
-    // After the first MFMAs of the last quarter comes the slice's barrier (every wavefront is done
+    // One slice, part by part (SlicePlan).  On entry the first part's operands are in flight; during every part the
+    // next one's are read.  After the first MFMAs of the last part comes the slice's barrier (every wavefront is done
     // reading `cur`; the slice in `nx1` has landed), then the first operands of `nx1`.
     // SWAP: the MFMAs take the operands the other way round, which leaves the transposed 32 x 32 blocks in the
     // accumulators (lane <-> tile column, registers <-> tile rows); store_t writes such a tile out transposed.
     template <bool SWAP = false> __device__ __forceinline__ void slice(const char *cur, const char *nx1)
     {
         __builtin_amdgcn_sched_barrier(0);
-        static_for<4>([&](auto gi) __attribute__((always_inline)) {
-            constexpr int g = decltype(gi)::value;
-            constexpr int NB = (g == 3 && NM >= 4) ? 2 : 0;   // MFMAs of the last quarter that precede the barrier
-            static_for<NM>([&](auto ci) __attribute__((always_inline)) {
+        static_for<SP::PARTS>([&](auto gi) __attribute__((always_inline)) {
+            constexpr int g = decltype(gi)::value, LAST = SP::PARTS - 1;
+            static_for<SP::NM>([&](auto ci) __attribute__((always_inline)) {
                 constexpr int c = decltype(ci)::value;
-                constexpr int mi = c / NI, ni = c % NI, cb = g & 1, nb = (g + 1) & 1;
-                if constexpr (g == 3 && c == NB) {
+                constexpr int a = SP::a_of(c), b = SP::b_of(c), cb = SP::set_of(g), nb = SP::set_of(g + 1);
+                if constexpr (g == LAST && c == SP::NB) {
                     __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(63));
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if constexpr (SWAP) acc[mi][ni] = In<T>::mfma(fa[cb][mi], fb[cb][ni], acc[mi][ni]);
-                else acc[mi][ni] = In<T>::mfma(fb[cb][ni], fa[cb][mi], acc[mi][ni]);
-                constexpr int r0 = c < NB ? 0 : (c - NB) * RPM < NOPS ? (c - NB) * RPM : NOPS;
-                constexpr int r1 = c < NB ? 0 : (c - NB + 1) * RPM < NOPS ? (c - NB + 1) * RPM : NOPS;
-                static_for<r1 - r0>([&](auto ri) __attribute__((always_inline)) {
-                    constexpr int r = r0 + decltype(ri)::value;
-                    const char *st = g < 3 ? cur : nx1;
-                    constexpr int kk = g < 3 ? g + 1 : 0;
-                    if constexpr (r == 0) fa[nb][0] = read_frag<T, A_TR, TM>(st, wm * WTM, kk);
-                    else if constexpr (r <= NI) fb[nb][r - 1] = read_frag<T, B_TR, TN>(st + A_BYTES, wn * WTN + (r - 1) * 32, kk);
-                    else fa[nb][r - NI] = read_frag<T, A_TR, TM>(st, wm * WTM + (r - NI) * 32, kk);
-                });
+                SP::template mfma<T, a, b, SWAP>(acc, fa[cb][a], fb[cb][b]);
+                const char *const st = g < LAST ? cur : nx1;
+                constexpr int kk = g < LAST ? g + 1 : 0;
+                SP::template reads<g, c>(
+                    [&](auto i) __attribute__((always_inline)) { fa[nb][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk); },
+                    [&](auto i) __attribute__((always_inline)) { fb[nb][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
     }
     // Epilogue: scale in fp32, round once, park 32 rows x 128 bytes at a time in this wavefront's
     // own piece of LDS (`reg`) and write them out as whole 128-byte lines.  The MFMAs took the
-    // operands swapped, so accumulator register 4q+e of lane l is row l%32, column 8q + 4(l/32) + e
-    // of its 32x32 block.  8-byte slot u of row r lies at slot u ^ (r & 15): the 8-byte writes of 32
+    // operands swapped, so an accumulator quad is four consecutive columns of one row (quad_row, quad_col).
+    // 8-byte slot u of row r lies at slot u ^ (r & 15): the 8-byte writes of 32
     // rows then spread over all banks, and a 16-byte read finds its two halves in one 16-byte
     // piece, exchanged when r is odd.  dst(mi, nj) is the address of row 0 of the 32 x 128-byte
     // piece (mi, nj) of the wavefront's sub-tile, or null if that piece is not to be written.
@@ -110,21 +99,21 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     // range (see finish): one wait for all of them instead of one per piece.  For 16-bit outputs under
     // a ReLU gate the gate values lie where the outputs go; store requests them a piece ahead.
     uint4 gate_q[MI * NJ][4];
-    f32x4 bias_r[NJ][NIP * 4];
+    static constexpr int QC = S16 ? 2 : 4;           // quads with different columns per 32 columns (quad q: columns of quad q % QC)
+    f32x4 bias_r[NJ][NIP * QC];
     typedef __attribute__((__vector_size__(4 * sizeof(typename In<T>::out16)))) typename In<T>::out16 bias4;
-    bias4 bias16_r[NJ][NIP * 4];
-    // The 16-bit bias values of the wavefront's columns (8 bytes per lane and 8-column group), requested together.
+    bias4 bias16_r[NJ][NIP * QC];
+    // The 16-bit bias values of the wavefront's columns (8 bytes per lane and quad of columns), requested together.
     // RAGN: lanes beyond the last column read the last four values instead (their results are not stored).
     template <bool RAGN, class F> __device__ __forceinline__ void bias16_prefetch(const Tail &tl, F &&dst)
     {
-        const int whalf = (threadIdx.x & 63) >> 5;
 #pragma unroll
         for (int nj = 0; nj < NJ; ++nj) {
             int64_t gcol0 = 0;
             (void)dst(0, nj, gcol0);
 #pragma unroll
-            for (int i = 0; i < NIP * 4; ++i) {
-                int64_t c = gcol0 + (i >> 2) * 32 + 8 * (i & 3) + 4 * whalf;
+            for (int i = 0; i < NIP * QC; ++i) {
+                int64_t c = gcol0 + (i / QC) * 32 + quad_col<S16>(i % QC);
                 if (RAGN && c > ncols - 4) c = ncols - 4;
                 bias16_r[nj][i] = *reinterpret_cast<const bias4 *>(tl.bias16 + c * 2);
             }
@@ -133,8 +122,6 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     template <int MI0 = 0, int MI1 = MI, int NJ0 = 0, int NJ1 = NJ, class F>
     __device__ __forceinline__ void tail_prefetch(int64_t ldc, const Tail &tl, F &&dst)
     {
-        const int lane = threadIdx.x & 63;
-        const int whalf = lane >> 5;
 #pragma unroll
         for (int mi = MI0; mi < MI1; ++mi)
 #pragma unroll
@@ -144,8 +131,8 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                 if (!out) continue;                        // uniform
                 if (mi == 0 && tl.bias) {
 #pragma unroll
-                    for (int i = 0; i < NIP * 4; ++i)
-                        bias_r[nj][i] = *(const_f4)(uintptr_t)(tl.bias + gcol0 + (i >> 2) * 32 + 8 * (i & 3) + 4 * whalf);
+                    for (int i = 0; i < NIP * QC; ++i)
+                        bias_r[nj][i] = *(const_f4)(uintptr_t)(tl.bias + gcol0 + (i / QC) * 32 + quad_col<S16>(i % QC));
                 }
             }
     }
@@ -175,7 +162,6 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     {
         constexpr bool TAIL = MODE != kTailNone;
         const int lane = threadIdx.x & 63;
-        const int wrow = lane & 31, whalf = lane >> 5;
         const int rrow = lane >> 3, rch = lane & 7;
         // 16-bit outputs under a ReLU gate are gated after rounding, on whole rows; everything else in the accumulator's layout
         const bool gate_rows = MODE == kTailReluGate ? ESZ == 2
@@ -213,8 +199,9 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                 for (int nl = 0; nl < NIP; ++nl)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const f32x16 &a = acc[mi][nj * NIP + nl];
-                        float v[4] = {a[4 * q] * scale, a[4 * q + 1] * scale, a[4 * q + 2] * scale, a[4 * q + 3] * scale};
+                        const f32q a = acc[mi][nj * NIP + nl].quad(q);
+                        const int wrow = quad_row<S16>(q), wcol = nl * 32 + quad_col<S16>(q);      // place of the quad in the piece
+                        float v[4] = {a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
                         if constexpr (MODE == kTailBias16) {
                             // the product rounded, then the sum: what adding the bias to a finished Y gives, bit for bit.  (The
                             // empty statement keeps the scaled value in fp32, as the plain epilogue has it: the compiler would
@@ -222,11 +209,11 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
                                 asm("" : "+v"(v[e]));
-                                v[e] = static_cast<float>(static_cast<OutT>(v[e])) + static_cast<float>(bias16_r[nj][nl * 4 + q][e]);
+                                v[e] = static_cast<float>(static_cast<OutT>(v[e])) + static_cast<float>(bias16_r[nj][nl * QC + q % QC][e]);
                             }
                         } else if constexpr (TAIL) {
                             if (tl.bias) {
-                                const f32x4 bv = bias_r[nj][nl * 4 + q];
+                                const f32x4 bv = bias_r[nj][nl * QC + q % QC];
                                 v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
                             }
                             if constexpr (MODE == kTailLight) {
@@ -240,8 +227,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                                 // the gate matrix has 16-bit elements, read here in the accumulator's layout
                                 using E = typename In<T>::out16;
                                 typedef __attribute__((__vector_size__(4 * sizeof(E)))) E e4;
-                                const int c = nl * 32 + 8 * q + 4 * whalf;   // column within the piece
-                                const int64_t elem = (out - tl.c0) / ESZ + wrow * (ldc / ESZ) + c;
+                                const int64_t elem = (out - tl.c0) / ESZ + wrow * (ldc / ESZ) + wcol;
                                 const e4 x = *reinterpret_cast<const e4 *>(tl.aux + elem * (int64_t)sizeof(E));
                                 const float xf[4] = {static_cast<float>(x[0]), static_cast<float>(x[1]), static_cast<float>(x[2]), static_cast<float>(x[3])};
                                 gate4(gate_mode, v, xf);
@@ -249,13 +235,13 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                         }
                         const float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
                         if constexpr (ESZ == 4) {
-                            // 16 bytes per lane: 16-byte slot 2q + half, exchanged as a whole with (row & 7)
-                            const int slot = (2 * q + whalf) ^ (wrow & 7);
+                            // 16 bytes per lane: 16-byte slot, exchanged as a whole with (row & 7)
+                            const int slot = (wcol >> 2) ^ (wrow & 7);
                             *reinterpret_cast<float4 *>(reg + wrow * 128 + slot * 16) = make_float4(v0, v1, v2, v3);
                         } else {
                             typedef __attribute__((__vector_size__(4 * sizeof(OutT)))) OutT out4;
                             const out4 o = {static_cast<OutT>(v0), static_cast<OutT>(v1), static_cast<OutT>(v2), static_cast<OutT>(v3)};
-                            const int slot8 = (nl * 8 + 2 * q + whalf) ^ (wrow & 15);
+                            const int slot8 = (wcol >> 2) ^ (wrow & 15);
                             *reinterpret_cast<out4 *>(reg + wrow * 128 + slot8 * 8) = o;
                         }
                     }
@@ -293,7 +279,6 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     {
         static_assert(MI % NIP == 0, "a wavefront's rows must fill whole 128-byte rows of the transposed tile");
         const int lane = threadIdx.x & 63;
-        const int wrow = lane & 31, whalf = lane >> 5;
         const int rrow = lane >> 3, rch = lane & 7;
 #pragma unroll
         for (int r = 0; r < NI; ++r)
@@ -305,15 +290,16 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                 for (int nl = 0; nl < NIP; ++nl)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const f32x16 &a = acc[pj * NIP + nl][r];
-                        const float v0 = a[4 * q] * scale, v1 = a[4 * q + 1] * scale, v2 = a[4 * q + 2] * scale, v3 = a[4 * q + 3] * scale;
+                        const f32q a = acc[pj * NIP + nl][r].quad(q);
+                        const int wrow = quad_row<S16>(q), wcol = nl * 32 + quad_col<S16>(q);
+                        const float v0 = a[0] * scale, v1 = a[1] * scale, v2 = a[2] * scale, v3 = a[3] * scale;
                         if constexpr (ESZ == 4) {
-                            const int slot = (2 * q + whalf) ^ (wrow & 7);
+                            const int slot = (wcol >> 2) ^ (wrow & 7);
                             *reinterpret_cast<float4 *>(reg + wrow * 128 + slot * 16) = make_float4(v0, v1, v2, v3);
                         } else {
                             typedef __attribute__((__vector_size__(4 * sizeof(OutT)))) OutT out4;
                             const out4 o = {static_cast<OutT>(v0), static_cast<OutT>(v1), static_cast<OutT>(v2), static_cast<OutT>(v3)};
-                            const int slot8 = (nl * 8 + 2 * q + whalf) ^ (wrow & 15);
+                            const int slot8 = (wcol >> 2) ^ (wrow & 15);
                             *reinterpret_cast<out4 *>(reg + wrow * 128 + slot8 * 8) = o;
                         }
                     }
@@ -654,7 +640,9 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
         ord2 = uni(ord2_v);
     }
 
-    Compute<T, OutT, A_TR, B_TR, TM, TN, WM, WN> cw;
+    // (see read_frag; with an element-wise tail the second operand set spills)
+    constexpr bool S16 = OP == FWD && TN == 256 && (TAIL == kTailNone || TAIL == kTailBias16);
+    Compute<T, OutT, A_TR, B_TR, TM, TN, WM, WN, S16> cw;
     cw.wm = wm; cw.wn = wn;
     cw.ncols = P.N;
     int st0 = 0, st1 = 1, st2 = 2;       // stages of the stream's slices g, g+1, g+2
@@ -1054,7 +1042,7 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
         }
         return g;
     };
-    Compute<T, OutT, false, W_NK, TM, TN, WM, WN> cw;
+    Compute<T, OutT, false, W_NK, TM, TN, WM, WN, true> cw;
     cw.wm = wm; cw.wn = wn;
     int st0 = 0, st1 = 1, st2 = 2;
     bool started = false;

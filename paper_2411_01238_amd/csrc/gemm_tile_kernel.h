@@ -183,13 +183,14 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
         a_tile = P.A + (int64_t)i * P.BM * lda;
     }
 
-    f32x16 acc[MI][NI];
+    constexpr bool S16 = OP == DX && TM == 128 && A_DMA && B_DMA;     // (see read_frag)
+    Block<S16> acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+            for (int q = 0; q < 4; ++q) acc[mi][ni].set(q, f32q{0.f, 0.f, 0.f, 0.f});
 
     if (nsteps > 0) {
         using SliceA = Slice<A_KMAJ, TM, RAGGED && OP == DX>;
@@ -289,24 +290,22 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
             __builtin_amdgcn_s_barrier();
         }
 
-        typename In<T>::vec fa[2][MI], fb[2][NI];
+        using SP = SlicePlan<MI, NI, S16, A_TR || B_TR>;
+        typename In<T>::vec fa[SP::SETS][SP::AF], fb[SP::SETS][SP::BF];
         auto read_frags = [&](int buf, const char *st, int kk) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) fa[buf][mi] = read_frag<T, A_TR, TM>(st, wm * WTM + mi * 32, kk);
+            for (int i = 0; i < SP::AF; ++i) fa[buf][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk);
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) fb[buf][ni] = read_frag<T, B_TR, TN>(st + A_BYTES, wn * WTN + ni * 32, kk);
+            for (int i = 0; i < SP::BF; ++i) fb[buf][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk);
         };
         auto mfmas = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = In<T>::mfma(fb[buf][ni], fa[buf][mi], acc[mi][ni]);
+            static_for<SP::NM>([&](auto ci) __attribute__((always_inline)) {
+                constexpr int c = decltype(ci)::value, a = SP::a_of(c), b = SP::b_of(c);
+                SP::template mfma<T, a, b, false>(acc, fa[buf][a], fb[buf][b]);
+            });
         };
-        constexpr int NM = MI * NI, NOPS = MI + NI;
-        // operand reads requested per MFMA in the fine-grained loop (at least what fits the group)
-        constexpr int RPM_MIN = ceil_div(NOPS, NM >= 4 ? NM - 2 : NM), RPM = 2 > RPM_MIN ? 2 : RPM_MIN;
-        static_assert((NM >= 4 ? NM - 2 : NM) * RPM >= NOPS, "every operand of the next group must be requested within the group");
-        constexpr int NFR = MI * (A_TR ? 2 : 1) + NI * (B_TR ? 2 : 1);              // LDS reads per operand set
+        constexpr int NM = SP::NM;
+        constexpr int NFR = SP::AF * (A_TR ? 2 : 1) + SP::BF * (B_TR ? 2 : 1);      // LDS reads per operand set
 
         int st0 = 0, st1 = 1, st2 = 2;      // stages of slices s, s+1, s+2
         if (!loader) read_frags(0, stage_ptr(0), 0);
@@ -341,16 +340,15 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
                 const Src s2 = src_at(WITH_DMA ? nxt_off : 0);        // slice s + AHEAD
                 if constexpr (WITH_DMA) refresh_for(s + AHEAD + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                static_for<4>([&](auto gi) __attribute__((always_inline)) {
-                    constexpr int g = decltype(gi)::value;
-                    // In the last group the first NB MFMAs go out before the barrier (they need only
+                static_for<SP::PARTS>([&](auto gi) __attribute__((always_inline)) {
+                    constexpr int g = decltype(gi)::value, LAST = SP::PARTS - 1;
+                    // In the last part the first SP::NB MFMAs go out before the barrier (they need only
                     // operands already read), so that the matrix pipe has work while the wavefronts
                     // meet; the operand reads of slice s+1 follow the barrier.
-                    constexpr int NB = (g == 3 && NM >= 4) ? 2 : 0;
                     static_for<NM>([&](auto ci) __attribute__((always_inline)) {
                         constexpr int c = decltype(ci)::value;
-                        constexpr int mi = c / NI, ni = c % NI, cb = g & 1, nb = (g + 1) & 1;
-                        if constexpr (g == 3 && c == NB) {
+                        constexpr int a = SP::a_of(c), b = SP::b_of(c), cb = SP::set_of(g), nb = SP::set_of(g + 1);
+                        if constexpr (g == LAST && c == SP::NB) {
                             // slice s+1 must have landed everywhere: this wavefront's direct loads of it
                             // were issued one iteration ago (only this iteration's may stay in flight),
                             // and every wavefront must be done reading slice s before its stage is reused
@@ -358,30 +356,22 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
                             __builtin_amdgcn_s_barrier();
                             __builtin_amdgcn_sched_barrier(0);
                         }
-                        acc[mi][ni] = In<T>::mfma(fb[cb][ni], fa[cb][mi], acc[mi][ni]);
-                        // operands for the next group (kk = g+1 of this slice, or kk = 0 of slice s+1) go to the
-                        // other register set, so they are requested as early as the group allows, RPM per
-                        // MFMA, in the order the next group's MFMAs (A index major) first use them:
-                        // A0, B0 .. B(NI-1), A1 .. A(MI-1)
-                        constexpr int r0 = c < NB ? 0 : (c - NB) * RPM < NOPS ? (c - NB) * RPM : NOPS;
-                        constexpr int r1 = c < NB ? 0 : (c - NB + 1) * RPM < NOPS ? (c - NB + 1) * RPM : NOPS;
-                        static_for<r1 - r0>([&](auto ri) __attribute__((always_inline)) {
-                            constexpr int r = r0 + decltype(ri)::value;
-                            const char *st = g < 3 ? cur : nx1;
-                            constexpr int kk = g < 3 ? g + 1 : 0;
-                            if constexpr (r == 0) fa[nb][0] = read_frag<T, A_TR, TM>(st, wm * WTM, kk);
-                            else if constexpr (r <= NI) fb[nb][r - 1] = read_frag<T, B_TR, TN>(st + A_BYTES, wn * WTN + (r - 1) * 32, kk);
-                            else fa[nb][r - NI] = read_frag<T, A_TR, TM>(st, wm * WTM + (r - NI) * 32, kk);
-                        });
-                        if constexpr (g < 3 && WITH_DMA) {
+                        SP::template mfma<T, a, b, false>(acc, fa[cb][a], fb[cb][b]);
+                        // operands for the next part (of this slice, or the first of slice s+1)
+                        const char *const st = g < LAST ? cur : nx1;
+                        constexpr int kk = g < LAST ? g + 1 : 0;
+                        SP::template reads<g, c>(
+                            [&](auto i) __attribute__((always_inline)) { fa[nb][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk); },
+                            [&](auto i) __attribute__((always_inline)) { fb[nb][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
+                        if constexpr (g < LAST && WITH_DMA) {
                             constexpr int gc = g * NM + c;
-                            constexpr int j0 = gc * NDMA_ITER / (3 * NM), j1 = (gc + 1) * NDMA_ITER / (3 * NM);
+                            constexpr int j0 = gc * NDMA_ITER / (LAST * NM), j1 = (gc + 1) * NDMA_ITER / (LAST * NM);
                             static_for<j1 - j0>([&](auto ji) __attribute__((always_inline)) {
                                 constexpr int j = j0 + decltype(ji)::value;
                                 if constexpr (j < NDMA_A) da.issue(s2.a, lda, nx2, j);
                                 else db.issue(s2.b, ldb, nx2 + A_BYTES, j - NDMA_A);
                             });
-                        } else if constexpr (g == 3 && c == 0 && WITH_DMA) {
+                        } else if constexpr (g == LAST && c == 0 && WITH_DMA) {
                             nxt_off = offset_of(s + 1 + AHEAD);   // list lookup for the next iteration
                         }
                         __builtin_amdgcn_sched_barrier(0);
@@ -454,8 +444,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
             constexpr int MODE = decltype(mode_c)::value;
             constexpr bool TL = TAIL && OP != DW && MODE != kTailNone;
             // global column of register quad (ni, q) of this lane; false if it lies outside the output
-            auto quad_col = [&](int ni, int q, int64_t &gcol) __attribute__((always_inline)) -> bool {
-                const int cl = wn * WTN + ni * 32 + q * 8 + (lane >> 5) * 4;          // column within the tile
+            auto global_col = [&](int ni, int q, int64_t &gcol) __attribute__((always_inline)) -> bool {
+                const int cl = wn * WTN + ni * 32 + quad_col<S16>(q);                 // column within the tile
                 if constexpr (OP == DX) {
                     const int g = cl >> 6;
                     int c0 = out_col0[0];
@@ -481,7 +471,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
             for (int nb = 0; nb < NI; nb += NB) {
-                const int row = mi * 32 + (lane & 31);
                 f32x4 bias_v[NB * 4];
                 e16x4 gate_v[NB * 4];
                 if constexpr (TL) {
@@ -489,7 +478,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
 #pragma unroll
                         for (int i = 0; i < NB * 4; ++i) {
                             int64_t gcol;
-                            const bool ok = quad_col(nb + (i >> 2), i & 3, gcol);
+                            const bool ok = global_col(nb + (i >> 2), i & 3, gcol);
                             bias_v[i] = ok ? *(const_f4)(uintptr_t)(tl.bias + gcol) : f32x4{0.f, 0.f, 0.f, 0.f};
                         }
                     }
@@ -497,8 +486,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
 #pragma unroll
                         for (int i = 0; i < NB * 4; ++i) {
                             int64_t gcol;
-                            const bool ok = quad_col(nb + (i >> 2), i & 3, gcol);
-                            const int64_t elem = (out_row0 + wm * WTM + row) * (ldc / ESZ) + gcol;
+                            const bool ok = global_col(nb + (i >> 2), i & 3, gcol);
+                            const int64_t elem = (out_row0 + wm * WTM + mi * 32 + quad_row<S16>(i & 3)) * (ldc / ESZ) + gcol;
                             gate_v[i] = ok ? *reinterpret_cast<const e16x4 *>(tl.aux + elem * (int64_t)sizeof(E16)) : e16x4{};
                         }
                     }
@@ -507,9 +496,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
                 for (int ni = nb; ni < nb + NB; ++ni)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const int col = ni * 32 + q * 8 + (lane >> 5) * 4;
-                        float v[4] = {acc[mi][ni][4 * q] * scale, acc[mi][ni][4 * q + 1] * scale,
-                                      acc[mi][ni][4 * q + 2] * scale, acc[mi][ni][4 * q + 3] * scale};
+                        const int row = mi * 32 + quad_row<S16>(q), col = ni * 32 + quad_col<S16>(q);
+                        const f32q a = acc[mi][ni].quad(q);
+                        float v[4] = {a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
                         if constexpr (TL) {
                             // (lanes outside the output compute on zeros; their values are not stored)
                             if (has_bias) {

@@ -30,9 +30,9 @@
 // stalls a wavefront that has nothing else to do, not the one feeding the matrix pipe
 // (measured: 134 -> 119 us for the dense 4096^3 forward).
 //
-// The matrix-core instruction is v_mfma_f32_32x32x16_{f16,bf16}: lane l supplies row (l%32) of
-// one operand and column (l%32) of the other, each as 8 consecutive reduction indices starting
-// at 8*(l/32).
+// The matrix-core instruction is v_mfma_f32_32x32x16_{f16,bf16} or, in the kernels where it measured faster (see
+// read_frag), v_mfma_f32_16x16x32: lane l supplies row l%32 (l%16) of one operand and that column of the other, each as
+// 8 consecutive reduction indices starting at 8*(l/32) (8*(l/16)).  Either gives the same bits.
 //   - Every operand goes HBM -> LDS directly (global_load_lds_dwordx4): no registers, no LDS
 //     store instructions, and the LDS pipe stays free for the reads (an LDS store of 1 KiB was
 //     measured at 13 clocks, a read at 5.6).
@@ -50,9 +50,9 @@
 // The MFMAs are issued with the operands swapped (B's columns as the instruction's rows), so
 // that an accumulator register quad holds four consecutive output columns for the epilogue.
 //
-// On this chip the loop is limited by power, not by issue slots: the shader clock, read in the
-// loop, is ~2.0 GHz with the MFMAs alone, ~1.55 GHz once the operand reads from LDS are added
-// and ~1.4 GHz with the loads as well, at 84 % MFMA duty (1214 clocks per slice against 1024).
+// On this chip the loop is limited by power, not by issue slots: the shader clock over a launch at 4096^3 with nothing dropped
+// is 1.8 GHz with the 32 x 32 instruction and 1.9 to 2.0 GHz with the 16 x 16 one (counted: 207 and 206 thousand clocks in
+// 116 and 106 us of eq. 2), which needs less power for the same work.
 #include "gemm_host.h"
 #include <atomic>
 #include <math.h>

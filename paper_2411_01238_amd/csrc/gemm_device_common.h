@@ -502,7 +502,8 @@ template <int MI, int NI, bool S16, bool TR> struct SlicePlan {
     static constexpr int AF = MI * 32 / ROWS, BF = NI * 32 / ROWS, NM = AF * BF, NOPS = AF + BF;
     static constexpr bool SINGLE = S16 && !TR && NM == 32 && (AF == 8 || BF == 8), LONG_A = AF == 8;
     static constexpr int SETS = SINGLE ? 1 : 2;
-    static constexpr int NB = SINGLE ? 12 : NM >= 4 ? 2 : 0;
+    static constexpr int SPREAD = 24, NB2 = 8;
+    static constexpr int NB = SINGLE ? 12 : S16 ? NM * NB2 / 32 : NM >= 4 ? 2 : 0;
     static constexpr int RPM_MIN = ceil_div(NOPS, NM - NB), RPM = 2 > RPM_MIN ? 2 : RPM_MIN;       // reads per MFMA (!S16)
     static constexpr int long_of(int c) { return c / 16 * 4 + c % 4; }
     static constexpr int short_of(int c) { return c % 16 / 4; }
@@ -514,7 +515,8 @@ template <int MI, int NI, bool S16, bool TR> struct SlicePlan {
     {
         const int c0 = g == PARTS - 1 ? NB : 0;
         if (c < c0) return 0;
-        const int r = S16 ? ceil_div((c - c0) * NOPS, NM - c0) : (c - c0) * RPM;
+        const int over = g == PARTS - 1 ? NM - NB : NM * SPREAD / 32;
+        const int r = S16 ? ceil_div((c - c0) * NOPS, over) : (c - c0) * RPM;
         return r < NOPS ? r : NOPS;
     }
     // calls read_a(i) / read_b(i) for the operands that are read after MFMA C of part G

@@ -286,6 +286,7 @@ __global__ __launch_bounds__(kMaskThreads) void mask_kernel(MaskParams P)
 // entries with a larger count, ties by index: deterministic), and for very small grids the
 // draw itself is done here, which saves a launch.
 constexpr int kSmallN = 1024;
+constexpr int64_t kFusedDrawBlocks = 4096;
 
 // ptr[0..n] := exclusive prefix sums of cnt[0..n), by one wavefront (all 64 lanes call it).
 __device__ __forceinline__ void wave_scan(const int32_t *cnt, int32_t *ptr, int n)
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(kMaskThreads) void mask_small_kernel(MaskParams P)
             uint64_t word = src_bits[g];
             if (valid < 64) word &= (uint64_t(1) << valid) - 1;
             s_bits[g] = word;
-            if (first_wg) P.bits[g] = word;
+            if (first_wg && P.given_bits) P.bits[g] = word;
         }
     }
     __syncthreads();
@@ -394,35 +395,46 @@ __global__ __launch_bounds__(kMaskThreads) void mask_small_kernel(MaskParams P)
 
     // -- phase 2: pointers (one wavefront each) and schedules.  rank = number of entries with a larger
     //    count, ties by index: with the key count * 1024 + (1023 - index) that is the number of larger
-    //    keys, one compare and one add per entry.  Rows are ranked by the lower half of the workgroup
-    //    and columns by the upper half at the same time; the keys are read four at a time --
+    //    keys --
     for (int j = threadIdx.x; j < P.KB; j += kMaskThreads) s_ckey[j] = s_ccnt[j] * kSmallN + (kSmallN - 1 - j);
     __syncthreads();
     if (wave == kMaskWaves - 1) wave_scan(s_rcnt, s_row_ptr, P.MB);
     if (wave == kMaskWaves - 2) wave_scan(s_ccnt, s_col_ptr, P.KB);
-    auto rank_of = [](const int32_t *key, int n, int mine) {
-        int rank = 0;
-        const int4 *q = reinterpret_cast<const int4 *>(key);
+    if (gridDim.x == 1) {
+        // one workgroup (a small grid): a thread per row in the lower half and per column in the upper half at the same
+        // time, the keys read four at a time (32 x 32 blocks: 9.1 us a launch, with a wavefront per row 9.5)
+        auto rank_of = [](const int32_t *key, int n, int mine) {
+            int rank = 0;
+            const int4 *q = reinterpret_cast<const int4 *>(key);
 #pragma unroll 4
-        for (int o = 0; o < (n + 3) / 4; ++o) {
-            const int4 v = q[o];
-            rank += (v.x > mine) + (v.y > mine) + (v.z > mine) + (v.w > mine);
-        }
-        return rank;
-    };
-    // (with several workgroups the rows and columns to rank are dealt out over all of them: ranking is quadratic,
-    // 512 rows took one workgroup 5 us)
-    constexpr int kHalf = kMaskThreads / 2;
-    const int rank_stride = (int)gridDim.x * kHalf;
-    if (threadIdx.x < kHalf) {
-        for (int i = (int)blockIdx.x * kHalf + threadIdx.x; i < P.MB; i += rank_stride) {
-            const int rank = rank_of(s_rkey, P.MB, s_rkey[i]);
-            P.row_order[rank] = i;
+            for (int o = 0; o < (n + 3) / 4; ++o) {
+                const int4 v = q[o];
+                rank += (v.x > mine) + (v.y > mine) + (v.z > mine) + (v.w > mine);
+            }
+            return rank;
+        };
+        constexpr int kHalf = kMaskThreads / 2;
+        if (threadIdx.x < kHalf) {
+            for (int i = threadIdx.x; i < P.MB; i += kHalf) P.row_order[rank_of(s_rkey, P.MB, s_rkey[i])] = i;
+        } else {
+            for (int j = threadIdx.x - kHalf; j < P.KB; j += kHalf) P.col_order[rank_of(s_ckey, P.KB, s_ckey[j])] = j;
         }
     } else {
-        for (int j = (int)blockIdx.x * kHalf + threadIdx.x - kHalf; j < P.KB; j += rank_stride) {
-            const int rank = rank_of(s_ckey, P.KB, s_ckey[j]);
-            P.col_order[rank] = j;
+        // several: a wavefront per row or column, 64 keys per ballot, dealt out over the wavefronts of the launch that do
+        // not scan (ranking is quadratic: with a thread per row all rows fell to one workgroup, 5 us for 512, 20 for 1024)
+        constexpr int kRankers = kMaskWaves - 2;
+        auto rank_of = [&](const int32_t *key, int n, int mine) {
+            int rank = 0;
+            for (int base = 0; base < n; base += 64) rank += (int)__popcll(__ballot(key[base + lane] > mine));
+            return rank;
+        };
+        if (wave < kRankers) {
+            for (int i = (int)blockIdx.x * kRankers + wave; i < P.MB + P.KB; i += (int)gridDim.x * kRankers) {
+                const bool row = i < P.MB;
+                const int j = row ? i : i - P.MB;
+                const int rank = row ? rank_of(s_rkey, P.MB, s_rkey[j]) : rank_of(s_ckey, P.KB, s_ckey[j]);
+                if (lane == 0) (row ? P.row_order : P.col_order)[rank] = j;
+            }
         }
     }
     // the largest counts, for the header (workgroup 0 writes it)
@@ -550,7 +562,10 @@ int launch_mask(void *mask, size_t mask_bytes, int64_t M, int64_t K, int BM, int
     // Small grids (and that is all five workloads') are drawn by the workgroups that build the lists: one launch.
     // The lists are shared out over several workgroups when there are many of them (about 32 list pieces, i.e. block
     // rows, block columns and groups of 8 block rows, per workgroup).
-    const bool fused_draw = small && !given_bits;
+    // Every one of them draws the whole grid then, 0.64 ns per block: on larger grids a draw spread over the chip, in a
+    // launch of its own (4 to 5 us with its boundary), is the shorter way.  Both steps, launches issued back to back, us:
+    // 512 x 32 blocks 23.8 -> 13.0, 1024 x 64 62.5 -> 18.0, 256 x 64 21.3 -> 12.0.
+    const bool fused_draw = small && !given_bits && L.MB * L.KB <= kFusedDrawBlocks;
     const int64_t pieces = L.MB + L.KB + (L.MB + 7) / 8;
     const unsigned n_wg = !small || words <= 64 ? 1u : (unsigned)(pieces / 32 < 1 ? 1 : pieces / 32 > 64 ? 64 : pieces / 32);
     if (!given_bits && !fused_draw) {

@@ -437,6 +437,20 @@ int sdrop_fwd_dense(const void *X, const void *W, const void *bias, void *Y, int
                     int dtype, void *stream, const sdrop_epilogue_t *epi, int *done);
 
 /*
+ * The products of the backward of a block  H -> act(H W0^T + b0) -> dropout -> . W  in pairs, in one launch each where the
+ * shapes allow it (128 x 128 blocks, N and N0 multiples of 256), else one after the other.  Contiguous matrices of type
+ * `dtype`; ws, ws_bytes: sdrop_workspace_bytes(SDROP_OP_BWD_DW, ...) of the second product.  Same bits as the two calls.
+ *   sdrop_bwd_gated     dZ = sdrop_bwd_dx_ex(dY, W) with the gate matrix (SDROP_GATE_*) as its only tail, dropout scale;
+ *                       dW = sdrop_bwd_dw(X, dY)
+ *   sdrop_producer_bwd  dH = sdrop_fwd_ex(dZ, W0), dW0 = sdrop_bwd_dw_ex(dZ, H), both at scale 1;  dZ [M,K], W0 [K,N0],
+ *                       H [M,N0]
+ */
+int sdrop_bwd_gated(const void *dY, const void *W, const void *X, const void *gate, int gate_mode, const void *mask, void *dZ, void *dW,
+                    int64_t M, int64_t K, int64_t N, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream);
+int sdrop_producer_bwd(const void *dZ, const void *W0, const void *H, const void *mask, void *dH, void *dW0,
+                       int64_t M, int64_t K, int64_t N0, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream);
+
+/*
  * The gradient of that bias: db[n] = sum over all rows m of dY[m, n], accumulated in fp32, rounded once to `dtype`.
  *   dY[M,N]   rows ld_dy elements apart (0 = N; else >= N, a multiple of 8); N a multiple of 8
  *   db        N values of type `dtype`, 16-byte aligned

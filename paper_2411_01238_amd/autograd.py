@@ -118,16 +118,25 @@ class _SparseActBlock(torch.autograd.Function):
         dy = dy.contiguous()
         need_h, need_w0, need_b0, need_w = ctx.needs_input_grad[:4]
         dz = dh = dw0 = db0 = dw = None
-        if need_h or need_w0 or (need_b0 and ctx.has_bias):
-            dz = sdrop.sdrop_bwd_dx_ex(dy, w, m, relu_mask=gate, gate_mode=ctx.gate_id)
-        if need_h:
-            dh = sdrop.sdrop_fwd_ex(dz, w0, m, scale_mode=sdrop.SCALE_ONE)
-        if need_w0:
-            dw0 = sdrop.sdrop_bwd_dw_ex(dz, h, m, scale_mode=sdrop.SCALE_ONE)
+        need_z = need_h or need_w0 or (need_b0 and ctx.has_bias)
+        # products that do not depend on each other share a launch where both are wanted (contiguous matrices: row-strided
+        # operands go through the calls that take leading dimensions)
+        if need_z and need_w and all(t.is_contiguous() for t in (w, x, gate)):
+            dz, dw = sdrop.sdrop_bwd_gated(dy, w, x, gate, ctx.gate_id, m)
+        else:
+            if need_z:
+                dz = sdrop.sdrop_bwd_dx_ex(dy, w, m, relu_mask=gate, gate_mode=ctx.gate_id)
+            if need_w:
+                dw = sdrop.sdrop_bwd_dw(x, dy, m)
+        if need_h and need_w0 and h.is_contiguous() and w0.is_contiguous():
+            dh, dw0 = sdrop.sdrop_producer_bwd(dz, w0, h, m)
+        else:
+            if need_h:
+                dh = sdrop.sdrop_fwd_ex(dz, w0, m, scale_mode=sdrop.SCALE_ONE)
+            if need_w0:
+                dw0 = sdrop.sdrop_bwd_dw_ex(dz, h, m, scale_mode=sdrop.SCALE_ONE)
         if need_b0 and ctx.has_bias:
             db0 = sdrop.sdrop_bias_grad(dz, m)
-        if need_w:
-            dw = sdrop.sdrop_bwd_dw(x, dy, m)
         return dh, dw0, db0, dw, None, None, None, None, None, None
 
 

@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libsdrop.so")
 # (source, object, defines): the GEMM kernels are one source, compiled per operand type and group of kernels.
 # The longest units come first.
 UNITS = [("sdrop_gemm_inst.hip", "sdrop_gemm_%s_%d.o" % (t.lower(), part), ["-DSDROP_T=" + t, "-DSDROP_PART=%d" % part])
-         for part in (1, 0, 3, 2, 4) for t in ("F16", "BF16")]
+         for part in (1, 0, 3, 2, 5, 4) for t in ("F16", "BF16")]
 UNITS += [(src, os.path.splitext(src)[0] + ".o", []) for src in ("sdrop_gemm.hip", "sdrop_mask.hip", "sdrop_bias_grad.hip")]
 
 HIPCC_FLAGS = [

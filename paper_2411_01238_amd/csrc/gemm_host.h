@@ -64,12 +64,19 @@ template <class T> int fwd_seeded_typed(bool o32, const GemmParams &P, hipStream
 // The forward product with nothing dropped, without a mask object (128-row tiles, 16-bit output).
 // Returns -1 when the device does not grant the LDS the launch needs.
 template <class T> int fwd_dense_typed(const GemmParams &P, hipStream_t stream);
+// The products of a block's backward in pairs (128 x 128 blocks, whole tile columns, 16-bit outputs; dw_f32: dW's launch writes
+// fp32 planes): eq. (2) with a gate in its tail beside eq. (3), and the two gradients of the layer in front of the dropout.
+// Return -1 when the device does not grant the LDS the launch needs.
+template <class T> int bwd_gated_typed(bool dw_f32, const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream);
+template <class T> int fwd_dw_typed(bool dw_f32, const GemmParams &Pf, const GemmParams &Pdw, hipStream_t stream);
 #define SDROP_EXTERN(T)                                                                \
     extern template int dispatch_typed<FWD, T>(bool, GemmParams &, hipStream_t);       \
     extern template int dispatch_typed<DX, T>(bool, GemmParams &, hipStream_t);        \
     extern template int dispatch_typed<DW, T>(bool, GemmParams &, hipStream_t);        \
     extern template int fwd_seeded_typed<T>(bool, const GemmParams &, hipStream_t);    \
     extern template int fwd_dense_typed<T>(const GemmParams &, hipStream_t);           \
+    extern template int bwd_gated_typed<T>(bool, const GemmParams &, const GemmParams &, hipStream_t); \
+    extern template int fwd_dw_typed<T>(bool, const GemmParams &, const GemmParams &, hipStream_t);    \
     extern template int bwd_fused_typed<T>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t)
 SDROP_EXTERN(F16);
 SDROP_EXTERN(BF16);

@@ -487,6 +487,52 @@ int launch_bwd_fused_tn(int TN, const GemmParams &Pdx, const GemmParams &Pdw, hi
     return launch_bwd_fused<T, OutDX, OutDW, 128>(Pdx, Pdw, stream);
 }
 
+template <class T, class OutDW, int TAIL, int TN_DW>
+int launch_bwd_gated(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream)
+{
+    using OutDX = typename In<T>::out16;
+    constexpr int LDS_DX = persistent_lds(128, 128), LDS_DW = persistent_lds(128, TN_DW);
+    constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
+    auto k = bwd_gated_kernel<T, OutDX, OutDW, TAIL, TN_DW>;
+    static int ok = -1;     // per instantiation: does the device grant that much LDS?
+    if (ok < 0) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        ok = (e == hipSuccess);
+        if (!ok) (void)hipGetLastError();
+    }
+    if (!ok) return -1;
+    const int ncu = cu_count();
+    const int64_t positions = (int64_t)Pdx.MB * Pdx.KB;
+    const int g_dx = (int)(positions < ncu ? positions : ncu);
+    const int g_dw = Pdw.total_tiles < ncu ? Pdw.total_tiles : ncu;
+    hipLaunchKernelGGL(k, dim3((unsigned)(g_dx + g_dw)), dim3(512), P_LDS, stream, Pdx, Pdw, g_dx);
+    return hip_status(hipGetLastError());
+}
+
+template <class T, class OutDW, int TN_F, int TN_DW>
+int launch_fwd_dw(const GemmParams &Pf, const GemmParams &Pdw, hipStream_t stream)
+{
+    using OutF = typename In<T>::out16;
+    constexpr int LDS_F = persistent_lds(128, TN_F), LDS_DW = persistent_lds(128, TN_DW);
+    constexpr int P_LDS = LDS_F > LDS_DW ? LDS_F : LDS_DW;
+    auto k = fwd_dw_kernel<T, OutF, OutDW, TN_F, TN_DW>;
+    static int ok = -1;     // per instantiation: does the device grant that much LDS?
+    if (ok < 0) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
+        ok = (e == hipSuccess);
+        if (!ok) (void)hipGetLastError();
+    }
+    if (!ok) return -1;
+    GemmParams F = Pf;
+    F.n_tiles = (int)(F.N / TN_F);
+    F.splits = 1;
+    F.total_tiles = F.MB * F.n_tiles;
+    const int ncu = cu_count();
+    const int g_f = F.total_tiles < ncu ? F.total_tiles : ncu, g_dw = Pdw.total_tiles < ncu ? Pdw.total_tiles : ncu;
+    hipLaunchKernelGGL(k, dim3((unsigned)(g_f + g_dw)), dim3(512), P_LDS, stream, F, Pdw, g_f);
+    return hip_status(hipGetLastError());
+}
+
 template <class T, class OutDX, class OutDW, int TN_DX>
 int launch_bwd_fused_tile64(const GemmParams &Pdx, const GemmParams &Pdw, int n_dx, int n_dw, hipStream_t stream)
 {
@@ -541,6 +587,32 @@ template <class T> int fwd_dense_typed(const GemmParams &P, hipStream_t stream)
     }
     if (P.bias16) return narrow ? launch_fwd_dense<T, 128, false, true>(P, stream) : launch_fwd_dense<T, 256, false, true>(P, stream);
     return narrow ? launch_fwd_dense<T, 128, false, false>(P, stream) : launch_fwd_dense<T, 256, false, false>(P, stream);
+}
+
+template <class T> int bwd_gated_typed(bool dw_f32, const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t stream)
+{
+    using O16 = typename In<T>::out16;
+    auto go = [&](auto mode) -> int {
+        constexpr int MODE = decltype(mode)::value;
+        if (Pdw.dw_narrow) return launch_bwd_gated<T, O16, MODE, 128>(Pdx, Pdw, stream);
+        return dw_f32 ? launch_bwd_gated<T, float, MODE, 256>(Pdx, Pdw, stream) : launch_bwd_gated<T, O16, MODE, 256>(Pdx, Pdw, stream);
+    };
+    switch (tail_mode(Pdx)) {
+    case kTailReluGate: return go(std::integral_constant<int, kTailReluGate>{});
+    case kTailGeluErfGate: return go(std::integral_constant<int, kTailGeluErfGate>{});
+    default: return go(std::integral_constant<int, kTailGeneric>{});
+    }
+}
+
+template <class T> int fwd_dw_typed(bool dw_f32, const GemmParams &Pf, const GemmParams &Pdw, hipStream_t stream)
+{
+    using O16 = typename In<T>::out16;
+    auto go = [&](auto tn) -> int {
+        constexpr int TN = decltype(tn)::value;
+        if (Pdw.dw_narrow) return launch_fwd_dw<T, O16, TN, 128>(Pf, Pdw, stream);
+        return dw_f32 ? launch_fwd_dw<T, float, TN, 256>(Pf, Pdw, stream) : launch_fwd_dw<T, O16, TN, 256>(Pf, Pdw, stream);
+    };
+    return fwd_narrow(Pf) ? go(std::integral_constant<int, 128>{}) : go(std::integral_constant<int, 256>{});
 }
 
 template <class T> int bwd_fused_typed(int form, int TN, bool o32, bool dw_f32, const GemmParams &Pdx, const GemmParams &Pdw,

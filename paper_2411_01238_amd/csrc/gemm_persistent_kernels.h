@@ -1183,6 +1183,27 @@ __global__ __launch_bounds__(512) void bwd_fused_kernel(GemmParams Pdx, GemmPara
         gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone, false, false, W_NK>(Pdw, (int)gridDim.x - g_dx, (int)blockIdx.x - g_dx);
 }
 
+// The same with an element-wise tail on eq. (2) (the gate of the activation in front of the dropout), on single-block tiles.
+template <class T, class OutDX, class OutDW, int TAIL, int TN_DW>
+__global__ __launch_bounds__(512) void bwd_gated_kernel(GemmParams Pdx, GemmParams Pdw, int g_dx)
+{
+    if ((int)blockIdx.x < g_dx)
+        gemm_persistent_dx_body<T, OutDX, 128, 128, 2, 2, TAIL>(Pdx, g_dx, (int)blockIdx.x);
+    else
+        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone>(Pdw, (int)gridDim.x - g_dx, (int)blockIdx.x - g_dx);
+}
+
+// The two gradients of the layer in front of the dropout, dH = dZ W0 (eq. 1's product) and dW0 = dZ^T H (eq. 3's), which
+// share dZ and the mask and do not depend on each other: forward workgroups, then dW ones, as above.
+template <class T, class OutF, class OutDW, int TN_F, int TN_DW>
+__global__ __launch_bounds__(512) void fwd_dw_kernel(GemmParams Pf, GemmParams Pdw, int g_f)
+{
+    if ((int)blockIdx.x < g_f)
+        gemm_persistent_body<FWD, T, OutF, 128, TN_F, TN_F == 256 ? 1 : 2, TN_F == 256 ? 4 : 2, kTailNone>(Pf, g_f, (int)blockIdx.x);
+    else
+        gemm_persistent_body<DW, T, OutDW, 128, TN_DW, TN_DW == 256 ? 1 : 2, TN_DW == 256 ? 4 : 2, kTailNone>(Pdw, (int)gridDim.x - g_f, (int)blockIdx.x - g_f);
+}
+
 // The same where dX runs one workgroup per tile (tiles of two kept blocks that are too few per CU
 // for the persistent kernel): workgroups [0, n_dx) are those tiles, in the order of the separate
 // launch, the rest the persistent dW kernel.  (W_NK: dX reads a transposed copy of the weight, dW is written as [N,K].)

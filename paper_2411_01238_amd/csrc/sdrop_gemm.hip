@@ -778,6 +778,101 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
     return run<DW>(x, dy, mask, dw, M, K, N, BM, BK, p, dtype, out_dtype, ws, ws_bytes, stream, ld ? &e : nullptr);
 }
 
+// Two products of a block's backward in one launch where that is one of the paired kernels' shapes, else in turn: the same
+// calls, the same bits.  A product that leaves the chip partly idle at its end (its heaviest list, its last round) then
+// shares it with the other one, and a launch boundary goes.  128 x 128 blocks, whole 256-wide tile columns, 16-bit outputs,
+// contiguous matrices.  In turn -> one launch, us (bf16; eq. 2 with a GELU's gate and eq. 3 / dH and dW0): 4096^2 x 1024, half
+// dropped 72.9 -> 62.5 / 57.7 -> 50.3; 16384 x 4096 x 1024 at p = 0.1 341 -> 313 / 210 -> 206; 65536 x 2048 x 512 at 0.3 350 ->
+// 328 / 181 -> 174; 4096^3, half dropped 159 -> 153 / 121 -> 117; 1024^3 25.5 -> 16.0 / 19.4 -> 12.0; 256 x 512 x 256 16.5 -> 11.4 /
+// 13.5 -> 8.3; 16384 x 1024 x 512, nothing dropped 73.2 -> 71.8 / 53.0 -> 52.0.  A block of 4096 x 4096 x 1024 with 1024
+// features in front and a GELU as a whole: 229 -> 215.  Not where dW on its own runs its parts on narrow tiles (which this
+// launch does not hold) and its lists are long: 32768 x 256^2 at 0.2 42.3 -> 42.8 with a ReLU's gate, 36.1 -> 40.7
+// (8192 x 1024 x 256, the line: 39.9 -> 38.9 / 31.5 -> 24.8).
+bool pair_applies(GemmParams &Pdw)
+{
+    if (!g_bwd_fused || Pdw.BM != 128 || Pdw.BK != 128 || Pdw.N % 256 != 0) return false;
+    set_dw_plan(Pdw);
+    const bool alone_narrow = Pdw.dw_narrow && Pdw.splits > 1;
+    set_dw_plan(Pdw, true);
+    return !(alone_narrow && Pdw.M > 8192);
+}
+
+// eq. (2) gated by `gate` (SDROP_GATE_*) and eq. (3)
+int run_bwd_gated(const void *dy, const void *w, const void *x, const void *gate, int gate_mode, const void *mask, void *dz, void *dw,
+                  int64_t M, int64_t K, int64_t N, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream)
+{
+    int rc = check_gemm_args(dy, w, mask, dz, M, K, N, BM, BK, p, dtype, dtype);
+    if (rc == SDROP_OK) rc = check_gemm_args(x, dy, mask, dw, M, K, N, BM, BK, p, dtype, dtype);
+    if (rc != SDROP_OK) return rc;
+    if (!gate || gate_mode < SDROP_GATE_RELU || gate_mode > SDROP_GATE_GELU_ERF) return SDROP_EINVAL;
+    if (reinterpret_cast<uintptr_t>(gate) % 16) return SDROP_EALIGN;
+    const size_t need = ws_planes_bytes(SDROP_OP_BWD_DW, M, K, N, BM, BK);
+    if (ws_bytes < need || (need && (!ws || reinterpret_cast<uintptr_t>(ws) % 16))) return SDROP_EWORKSPACE;
+    sdrop_mask_layout_t L;
+    sdrop_mask_layout(M, K, BM, BK, &L);
+    if (!tile_count_ok(N, L)) return SDROP_ESHAPE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    GemmParams Pdw = base_params(DW, x, dy, mask, dw, M, K, N, BM, BK, p, dtype, L);
+    if (pair_applies(Pdw)) {
+        GemmParams Pdx = base_params(DX, dy, w, mask, dz, M, K, N, BM, BK, p, dtype, L);
+        Pdx.aux = static_cast<const char *>(gate);
+        Pdx.gate_mode = gate_mode;
+        const DxPlan plan = dx_plan(Pdx);
+        if (plan.persistent && plan.TN == 128) {
+            Pdw.n_tiles = (int)(N / (Pdw.dw_narrow ? 128 : 256));
+            Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
+            const float scale = Pdw.scale;
+            const bool split = Pdw.splits > 1;
+            if (split) { Pdw.C = static_cast<char *>(ws); Pdw.ldc = N * 4; Pdw.scale = 1.0f; }
+            const int rf = dtype == SDROP_F16 ? bwd_gated_typed<F16>(split, Pdx, Pdw, st) : bwd_gated_typed<BF16>(split, Pdx, Pdw, st);
+            if (rf != -1) {
+                if (rf != SDROP_OK || !split) return rf;
+                return launch_reduce(ws, dw, K * N, Pdw.splits, scale, dtype, dtype, st, N, N, Pdw);
+            }
+        }
+    }
+    sdrop_epilogue_t e = {};
+    e.scale_mode = SDROP_SCALE_DROPOUT; e.act = SDROP_ACT_NONE; e.gate_mode = gate_mode; e.w_layout = SDROP_W_KN;
+    e.relu_mask = gate;
+    rc = run<DX>(dy, w, mask, dz, M, K, N, BM, BK, p, dtype, dtype, nullptr, 0, stream, &e);
+    if (rc != SDROP_OK) return rc;
+    return run<DW>(x, dy, mask, dw, M, K, N, BM, BK, p, dtype, dtype, ws, ws_bytes, stream);
+}
+
+// dH = dZ W0 and dW0 = dZ^T H at scale 1, dZ [M, K] block-sparse in the mask, W0 [K, N0], H [M, N0]
+int run_producer_bwd(const void *dz, const void *w0, const void *h, const void *mask, void *dh, void *dw0,
+                     int64_t M, int64_t K, int64_t N0, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream)
+{
+    int rc = check_gemm_args(dz, w0, mask, dh, M, K, N0, BM, BK, p, dtype, dtype);
+    if (rc == SDROP_OK) rc = check_gemm_args(dz, h, mask, dw0, M, K, N0, BM, BK, p, dtype, dtype);
+    if (rc != SDROP_OK) return rc;
+    const size_t need = ws_planes_bytes(SDROP_OP_BWD_DW, M, K, N0, BM, BK);
+    if (ws_bytes < need || (need && (!ws || reinterpret_cast<uintptr_t>(ws) % 16))) return SDROP_EWORKSPACE;
+    sdrop_mask_layout_t L;
+    sdrop_mask_layout(M, K, BM, BK, &L);
+    if (!tile_count_ok(N0, L)) return SDROP_ESHAPE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    GemmParams Pdw = base_params(DW, dz, h, mask, dw0, M, K, N0, BM, BK, p, dtype, L);
+    if (pair_applies(Pdw)) {
+        GemmParams Pf = base_params(FWD, dz, w0, mask, dh, M, K, N0, BM, BK, p, dtype, L);
+        Pf.scale = Pdw.scale = 1.0f;
+        Pdw.n_tiles = (int)(N0 / (Pdw.dw_narrow ? 128 : 256));
+        Pdw.total_tiles = Pdw.KB * Pdw.n_tiles * Pdw.splits;
+        const bool split = Pdw.splits > 1;
+        if (split) { Pdw.C = static_cast<char *>(ws); Pdw.ldc = N0 * 4; }
+        const int rf = dtype == SDROP_F16 ? fwd_dw_typed<F16>(split, Pf, Pdw, st) : fwd_dw_typed<BF16>(split, Pf, Pdw, st);
+        if (rf != -1) {
+            if (rf != SDROP_OK || !split) return rf;
+            return launch_reduce(ws, dw0, K * N0, Pdw.splits, 1.0f, dtype, dtype, st, N0, N0, Pdw);
+        }
+    }
+    sdrop_epilogue_t e = {};
+    e.scale_mode = SDROP_SCALE_ONE; e.act = SDROP_ACT_NONE; e.gate_mode = SDROP_GATE_RELU; e.w_layout = SDROP_W_KN;
+    rc = run<FWD>(dz, w0, mask, dh, M, K, N0, BM, BK, p, dtype, dtype, nullptr, 0, stream, &e);
+    if (rc != SDROP_OK) return rc;
+    return run<DW>(dz, h, mask, dw0, M, K, N0, BM, BK, p, dtype, dtype, ws, ws_bytes, stream, &e);
+}
+
 }  // namespace
 
 int check_gemm_args(const void *a, const void *b, const void *mask, void *out,
@@ -1019,6 +1114,18 @@ int sdrop_bwd_dw_ex(const void *X, const void *dY, const void *mask, void *dW,
                     const sdrop_epilogue_t *epi)
 {
     return sdrop::run<sdrop::DW>(X, dY, mask, dW, M, K, N, BM, BK, p, dtype, out_dtype, ws, ws_bytes, stream, epi);
+}
+
+int sdrop_bwd_gated(const void *dY, const void *W, const void *X, const void *gate, int gate_mode, const void *mask, void *dZ, void *dW,
+                    int64_t M, int64_t K, int64_t N, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream)
+{
+    return sdrop::run_bwd_gated(dY, W, X, gate, gate_mode, mask, dZ, dW, M, K, N, BM, BK, p, dtype, ws, ws_bytes, stream);
+}
+
+int sdrop_producer_bwd(const void *dZ, const void *W0, const void *H, const void *mask, void *dH, void *dW0,
+                       int64_t M, int64_t K, int64_t N0, int BM, int BK, double p, int dtype, void *ws, size_t ws_bytes, void *stream)
+{
+    return sdrop::run_producer_bwd(dZ, W0, H, mask, dH, dW0, M, K, N0, BM, BK, p, dtype, ws, ws_bytes, stream);
 }
 
 int sdrop_producer(const void *H, const void *W0, const float *bias, const void *mask, void *X, void *Z,

@@ -12,6 +12,9 @@ template int dispatch_typed<DW, SDROP_T>(bool, GemmParams &, hipStream_t);
 template int fwd_seeded_typed<SDROP_T>(bool, const GemmParams &, hipStream_t);
 #elif SDROP_PART == 4
 template int fwd_dense_typed<SDROP_T>(const GemmParams &, hipStream_t);
+#elif SDROP_PART == 5
+template int bwd_gated_typed<SDROP_T>(bool, const GemmParams &, const GemmParams &, hipStream_t);
+template int fwd_dw_typed<SDROP_T>(bool, const GemmParams &, const GemmParams &, hipStream_t);
 #else
 template int bwd_fused_typed<SDROP_T>(int, int, bool, bool, const GemmParams &, const GemmParams &, int, hipStream_t);
 #endif

@@ -26,7 +26,7 @@ EXPORTS = ("sdrop_strerror", "sdrop_last_hip_error", "sdrop_status", "sdrop_set_
            "sdrop_mask", "sdrop_mask_split", "sdrop_mask_from_bits", "sdrop_mask_bits", "sdrop_workspace_bytes",
            "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_fwd_seeded_bias", "sdrop_fwd_dense", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
            "sdrop_bwd", "sdrop_bwd_ex", "sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex", "sdrop_workspace_bytes_ex",
-           "sdrop_producer", "sdrop_producer_ex",
+           "sdrop_producer", "sdrop_producer_ex", "sdrop_bwd_gated", "sdrop_producer_bwd",
            "sdrop_bias_grad_workspace_bytes", "sdrop_bias_grad", "sdrop_col_sum_workspace_bytes", "sdrop_col_sum")
 
 SCALE_DROPOUT, SCALE_ONE = 0, 1
@@ -123,6 +123,10 @@ def lib():
         L.sdrop_producer_ex.restype = ci
         L.sdrop_producer.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, ci, ci, vp]
         L.sdrop_producer.restype = ci
+        L.sdrop_bwd_gated.argtypes = [vp, vp, vp, vp, ci, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, vp, sz, vp]
+        L.sdrop_bwd_gated.restype = ci
+        L.sdrop_producer_bwd.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, vp, sz, vp]
+        L.sdrop_producer_bwd.restype = ci
         L.sdrop_bias_grad_workspace_bytes.argtypes = [i64, i64, ci, ci]
         L.sdrop_bias_grad_workspace_bytes.restype = sz
         L.sdrop_bias_grad.argtypes = [vp, vp, vp, i64, i64, ci, ci, ci, i64, vp, sz, vp]
@@ -626,6 +630,50 @@ def sdrop_producer(H, W0, bias, mask, act=ACT_NONE, out_dtype=None, out=None, pr
         rc = lib().sdrop_producer_ex(*args, ldh, ldw, ldo)
     _check(rc, "sdrop_producer")
     return out if preact is None else (out, preact)
+
+
+def _block_pair(name, a, b, c, mask, n, gate=None, gate_mode=GATE_RELU):
+    """The common part of the two calls below: a, b, c contiguous matrices of one 16-bit type; returns the two outputs."""
+    M, K = mask.M, mask.K
+    dtype = a.dtype
+    if dtype not in (torch.float16, torch.bfloat16):
+        raise SdropError(EDTYPE, name)
+    if any(t.dtype != dtype for t in (b, c) + (() if gate is None else (gate,))):
+        raise ValueError("operands must have the same dtype")
+    if gate is not None and tuple(gate.shape) != (M, K):
+        raise ValueError("gate must have the output's shape")
+    need = workspace_bytes(OP_BWD_DW, M, K, n, mask.BM, mask.BK, dtype, dtype)
+    ws = torch.empty(need, dtype=torch.uint8, device=a.device) if need else None
+    ws_ptr = ws.data_ptr() if ws is not None else None
+    o1 = torch.empty((M, K) if gate is not None else (M, n), dtype=dtype, device=a.device)
+    o2 = torch.empty((K, n), dtype=dtype, device=a.device)
+    head = (_dev(a, "a"), _dev(b, "b"), _dev(c, "c"))
+    if gate is not None:
+        head += (_dev(gate, "gate"), int(gate_mode))
+    rc = getattr(lib(), name)(*head, _dev(mask.buf, "mask"), o1.data_ptr(), o2.data_ptr(), M, K, n, mask.BM, mask.BK, mask.p,
+                              _DTYPES[dtype], ws_ptr, need, _stream())
+    _check(rc, name)
+    return o1, o2
+
+
+def sdrop_bwd_gated(dY, W, X, gate, gate_mode, mask):
+    """sdrop_bwd_dx_ex(dY, W, mask, relu_mask=gate, gate_mode=gate_mode) and sdrop_bwd_dw(X, dY, mask) in one call (one launch
+    where the shapes allow it), for contiguous matrices: returns (dZ, dW)."""
+    M, N = dY.shape
+    K, N2 = W.shape
+    if N2 != N or tuple(X.shape) != (M, K) or (M, K) != (mask.M, mask.K):
+        raise SdropError(ESHAPE, "sdrop_bwd_gated")
+    return _block_pair("sdrop_bwd_gated", dY, W, X, mask, N, gate, gate_mode)
+
+
+def sdrop_producer_bwd(dZ, W0, H, mask):
+    """sdrop_fwd_ex(dZ, W0, mask) and sdrop_bwd_dw_ex(dZ, H, mask), both at scale 1, in one call (one launch where the shapes
+    allow it), for contiguous matrices: returns (dH, dW0)."""
+    M, K = dZ.shape
+    K2, N0 = W0.shape
+    if K2 != K or tuple(H.shape) != (M, N0) or (M, K) != (mask.M, mask.K):
+        raise SdropError(ESHAPE, "sdrop_producer_bwd")
+    return _block_pair("sdrop_producer_bwd", dZ, W0, H, mask, N0)
 
 
 def bias_grad_workspace_bytes(M, K, BM, BK):

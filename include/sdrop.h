@@ -489,6 +489,11 @@ int sdrop_producer(const void *H, const void *W0, const float *bias, const void 
 int sdrop_producer_ex(const void *H, const void *W0, const float *bias, const void *mask, void *X, void *Z,
                       int64_t M, int64_t N0, int64_t K, int BM, int BK, double p, int act,
                       int dtype, int out_dtype, void *stream, int64_t ld_h, int64_t ld_w0, int64_t ld_out);
+/* sdrop_producer_ex with the dropped blocks of the second output Z (not null) written as zeros too. */
+int sdrop_producer_zeroed(const void *H, const void *W0, const float *bias, const void *mask, void *X, void *Z,
+                          int64_t M, int64_t N0, int64_t K, int BM, int BK, double p, int act,
+                          int dtype, int out_dtype, void *stream, int64_t ld_h, int64_t ld_w0, int64_t ld_out);
+
 
 /*
  * Gradient of that layer's bias (the block of Section 4.3's closing remark, as above):

@@ -101,8 +101,8 @@ class _SparseActBlock(torch.autograd.Function):
             x = sdrop.sdrop_producer(h, w0, b0, m, act=act_id)
             gate = x                    # [X > 0] is [Z > 0] on the kept blocks
         else:
-            # (cleared, 7 us at 4096 x 4096: the gate reads kept blocks only, which the producer writes, but the tensor is saved,
-            # and whoever looks at saved tensors sees all of it)
+            # (zero in the dropped blocks, which the gate does not read: the tensor is saved, and whoever looks at saved tensors
+            # sees all of it)
             x, gate = sdrop.sdrop_producer(h, w0, b0, m, act=act_id, preact=True)
         y = sdrop.sdrop_fwd(x, w, m)
         ctx.save_for_backward(h, w0, w, x, gate)

@@ -46,6 +46,7 @@ struct GemmParams {
     bool dw_narrow;     // host side: eq. (3) on 128 x 128 tiles (see DwPlan)
     // (behind the fields that every kernel reads, whose places in the argument block the kernels without these keep)
     int32_t folds;      // DW on 128 x 128 tiles: parts of the list that one workgroup sums one after the other (see DwPlan)
+    bool zero_c2;       // DX with a second output: its dropped blocks are written as zeros too
     const char *bias16; // FWD only: one value of the operands' type per output column (no other tail with it), or null
 };
 

@@ -980,7 +980,11 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
         auto zero_step = [&]() __attribute__((always_inline)) -> bool {
             if (zblock) {
                 const int c = (zprog * NW + wave) * 64 + lane;
-                store_out(zblock + (c / row_chunks) * ldc + (c % row_chunks) * 16, make_uint4(0, 0, 0, 0));
+                char *const z = zblock + (c / row_chunks) * ldc + (c % row_chunks) * 16;
+                store_out(z, make_uint4(0, 0, 0, 0));
+                if constexpr (TAIL != kTailNone) {
+                    if (P.zero_c2) store_out(z + (P.C2 - P.C), make_uint4(0, 0, 0, 0));
+                }
                 if (++zprog == per_wave) zblock = nullptr;
                 return true;
             }

@@ -105,8 +105,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
         const int row_chunks = P.BK * (int)sizeof(OutT) / 16;
         auto zero_block = [&](int zi, int zj) __attribute__((always_inline)) {
             char *z = P.C + (int64_t)zi * P.BM * ldc + (int64_t)zj * P.BK * sizeof(OutT);
-            for (int c = threadIdx.x; c < TM * row_chunks; c += NT)
-                store_out(z + (c / row_chunks) * ldc + (c % row_chunks) * 16, make_uint4(0, 0, 0, 0));
+            for (int c = threadIdx.x; c < TM * row_chunks; c += NT) {
+                char *const zc = z + (c / row_chunks) * ldc + (c % row_chunks) * 16;
+                store_out(zc, make_uint4(0, 0, 0, 0));
+                if constexpr (TAIL) {
+                    if (P.zero_c2) store_out(zc + (P.C2 - P.C), make_uint4(0, 0, 0, 0));
+                }
+            }
         };
         int i, blocks_valid;                          // block row; kept blocks in this tile (<= 0: nothing to compute)
         int jg[NGRP_MAX] = {0, 0, 0, 0};

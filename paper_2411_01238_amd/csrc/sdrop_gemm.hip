@@ -382,7 +382,7 @@ GemmParams base_params(int op, const void *a, const void *b, const void *mask, v
     P.total_tiles = 0;
     P.scale = (p < 1.0) ? (float)(1.0 / (1.0 - p)) : 0.0f;
     P.bias = nullptr; P.bias16 = nullptr; P.aux = nullptr; P.act = SDROP_ACT_NONE;
-    P.gate_mode = SDROP_GATE_RELU; P.C2 = nullptr;
+    P.gate_mode = SDROP_GATE_RELU; P.C2 = nullptr; P.zero_c2 = false;
     P.p = p;
     P.key0 = P.key1 = P.ctr2 = P.ctr3 = 0;
     P.threshold = 0;
@@ -417,7 +417,7 @@ template <int OP>
 int run(const void *a, const void *b, const void *mask, void *out,
         int64_t M, int64_t K, int64_t N, int BM, int BK, double p,
         int dtype, int out_dtype, void *ws, size_t ws_bytes, void *stream,
-        const sdrop_epilogue_t *epi = nullptr, void *out2 = nullptr, const void *bias16 = nullptr)
+        const sdrop_epilogue_t *epi = nullptr, void *out2 = nullptr, const void *bias16 = nullptr, bool zero_out2 = false)
 {
     const int rc = check_gemm_args(a, b, mask, out, M, K, N, BM, BK, p, dtype, out_dtype);
     if (rc != SDROP_OK) return rc;
@@ -500,6 +500,7 @@ int run(const void *a, const void *b, const void *mask, void *out,
         P.gate_mode = epi->gate_mode;
     }
     if (out2) P.C2 = static_cast<char *>(out2);
+    P.zero_c2 = out2 && zero_out2;
     P.bias16 = static_cast<const char *>(bias16);
     if constexpr (OP == DW) {
         set_dw_plan(P);
@@ -1142,6 +1143,23 @@ int sdrop_producer(const void *H, const void *W0, const float *bias, const void 
     epi.w_layout = SDROP_W_KN;
     epi.kept_fraction = 0.0;
     return sdrop::run<sdrop::DX>(H, W0, mask, X, M, K, N0, BM, BK, p, dtype, out_dtype, nullptr, 0, stream, &epi, Z);
+}
+
+int sdrop_producer_zeroed(const void *H, const void *W0, const float *bias, const void *mask, void *X, void *Z,
+                          int64_t M, int64_t N0, int64_t K, int BM, int BK, double p, int act,
+                          int dtype, int out_dtype, void *stream, int64_t ld_h, int64_t ld_w0, int64_t ld_out)
+{
+    if (!Z) return SDROP_EINVAL;
+    sdrop_epilogue_t epi;
+    epi.scale_mode = SDROP_SCALE_ONE;
+    epi.act = act;
+    epi.bias = bias;
+    epi.relu_mask = nullptr;
+    epi.ld_a = ld_h; epi.ld_b = ld_w0; epi.ld_out = ld_out;
+    epi.gate_mode = SDROP_GATE_RELU;
+    epi.w_layout = SDROP_W_KN;
+    epi.kept_fraction = 0.0;
+    return sdrop::run<sdrop::DX>(H, W0, mask, X, M, K, N0, BM, BK, p, dtype, out_dtype, nullptr, 0, stream, &epi, Z, nullptr, true);
 }
 
 int sdrop_producer_ex(const void *H, const void *W0, const float *bias, const void *mask, void *X, void *Z,

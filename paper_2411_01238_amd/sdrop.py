@@ -26,7 +26,7 @@ EXPORTS = ("sdrop_strerror", "sdrop_last_hip_error", "sdrop_status", "sdrop_set_
            "sdrop_mask", "sdrop_mask_split", "sdrop_mask_from_bits", "sdrop_mask_bits", "sdrop_workspace_bytes",
            "sdrop_fwd", "sdrop_fwd_seeded", "sdrop_fwd_seeded_ex", "sdrop_fwd_seeded_bias", "sdrop_fwd_dense", "sdrop_bwd_dx", "sdrop_bwd_dw", "sdrop_bwd_dw_static",
            "sdrop_bwd", "sdrop_bwd_ex", "sdrop_fwd_ex", "sdrop_bwd_dx_ex", "sdrop_bwd_dw_ex", "sdrop_workspace_bytes_ex",
-           "sdrop_producer", "sdrop_producer_ex", "sdrop_bwd_gated", "sdrop_producer_bwd",
+           "sdrop_producer", "sdrop_producer_ex", "sdrop_producer_zeroed", "sdrop_bwd_gated", "sdrop_producer_bwd",
            "sdrop_bias_grad_workspace_bytes", "sdrop_bias_grad", "sdrop_col_sum_workspace_bytes", "sdrop_col_sum")
 
 SCALE_DROPOUT, SCALE_ONE = 0, 1
@@ -121,6 +121,8 @@ def lib():
         L.sdrop_workspace_bytes_ex.restype = sz
         L.sdrop_producer_ex.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, ci, ci, vp, i64, i64, i64]
         L.sdrop_producer_ex.restype = ci
+        L.sdrop_producer_zeroed.argtypes = L.sdrop_producer_ex.argtypes
+        L.sdrop_producer_zeroed.restype = ci
         L.sdrop_producer.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, ci, ci, vp]
         L.sdrop_producer.restype = ci
         L.sdrop_bwd_gated.argtypes = [vp, vp, vp, vp, ci, vp, vp, vp, i64, i64, i64, ci, ci, dbl, ci, vp, sz, vp]
@@ -612,8 +614,10 @@ def sdrop_producer(H, W0, bias, mask, act=ACT_NONE, out_dtype=None, out=None, pr
         raise SdropError(EDTYPE, "sdrop_producer")
     if bias is not None and (bias.dtype != torch.float32 or tuple(bias.shape) != (K,)):
         raise ValueError("bias must be fp32 with one value per output column")
-    if preact is True:
-        preact = torch.zeros((M, K), dtype=out_dtype, device=H.device)
+    new_preact = preact is True
+    if new_preact:
+        # (the kernel that writes the kept blocks writes the zeros as well: a pass over the whole matrix took 7 us at 4096 x 4096)
+        preact = torch.empty((M, K), dtype=out_dtype, device=H.device)
     if preact is not None and (tuple(preact.shape) != (M, K) or preact.dtype != out_dtype):
         raise ValueError("preact has the wrong shape or dtype")
     (ph, ldh), (pw, ldw), (po, ldo) = _mat(H, "H"), _mat(W0, "W0"), _mat(out, "out")
@@ -624,7 +628,9 @@ def sdrop_producer(H, W0, bias, mask, act=ACT_NONE, out_dtype=None, out=None, pr
             raise ValueError("preact must have the output's leading dimension")
     args = (ph, pw, _dev(bias, "bias") if bias is not None else None, _dev(mask.buf, "mask"), po, pz,
             M, N0, K, mask.BM, mask.BK, mask.p, int(act), _DTYPES[dtype], _DTYPES[out_dtype], _stream())
-    if (ldh, ldw, ldo) == (N0, N0, K):
+    if new_preact:
+        rc = lib().sdrop_producer_zeroed(*args, ldh, ldw, ldo)
+    elif (ldh, ldw, ldo) == (N0, N0, K):
         rc = lib().sdrop_producer(*args)
     else:
         rc = lib().sdrop_producer_ex(*args, ldh, ldw, ldo)

@@ -435,22 +435,37 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
 // sustains 1.90 PFLOP/s against 1.70 (a loop of either on all CUs, random bf16; the chip holds a higher clock), but a
 // half slice of it is twice the operands at a time.  Measured, 32 -> 16, us: both operands read by rows (eq. 2, eq. 1 with an
 // [N,K] weight), 4096^3: p = 0 117 -> 107 and 112 -> 103, p = 0.5 (single blocks) 89 -> 85; eq. 1 with a [K,N] weight on
-// 256-wide tiles 69 -> 66 at p = 0.5, 64-row tiles (8192 x 1024^2) 19.2 -> 18.6; but eq. 3, whose operands both need
-// transposing reads, 64 -> 68 and 114 -> 120, eq. 1 on 128-wide tiles 9.67 -> 9.86 (1024^3), 29.5 -> 29.8 (4096^2 x 1024), and
+// 256-wide tiles 63 -> 60 at p = 0.5 and 112 -> 106 at p = 0, 64-row tiles (8192 x 1024^2) 19.2 -> 18.6; but eq. 3, whose
+// operands both need transposing reads, 65 -> 72 and 113 -> 119, eq. 1 on 128-wide tiles the same within 1 % (1024^3, 2048^3,
+// 8192 x 1024^2) and 11.9 -> 12.5 (4096 x 1024 x 72), and
 // 64-row tiles with a workgroup per tile 6.9 -> 7.1 (256^3), 28.3 -> 28.8 (dX of 8192 x 1024 x 1000).
 
 // MFMA operand for the 32 (S16: 16) rows or columns starting at `base` of an LDS operand tile,
 // reduction indices [16 kk, 16 kk + 16) (S16: [32 kk, 32 kk + 32)): lane l gets index base + l%32, reduction 8*(l/32)..+8
-// (S16: base + l%16, 8*(l/16)..+8).
+// (S16: base + l%16, 8*(l/16)..+8), as read_frag reads it.
 // TR = false: tile [rows][64], one ds_read_b128.  TR = true: tile [64][ROWS] as in HBM, two
 // transposing reads (ds_read_b64_tr_b16): within a group of 16 lanes, lane q loads 4 elements
 // of row q/4 at columns 4*(q%4).. and receives column q of that 4 x 16 patch.
-template <class T, bool TR, int ROWS, bool S16>
-__device__ __forceinline__ typename In<T>::vec read_frag(const char *lds, int base, int kk)
+// An operand in registers; a transposing read delivers half of it.
+template <class T, bool TR> struct Frag {
+    typename In<T>::vec v;
+    __device__ __forceinline__ typename In<T>::vec get() const { return v; }
+};
+template <class T> struct Frag<T, true> {
+    s16x4 lo, hi;
+    __device__ __forceinline__ typename In<T>::vec get() const
+    {
+        return __builtin_bit_cast(typename In<T>::vec, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+// HALF: 0 or 1, one of an operand's two transposing reads; 2: the whole operand
+template <class T, bool TR, int ROWS, bool S16, int HALF = 2>
+__device__ __forceinline__ void read_frag(Frag<T, TR> &f, const char *lds, int base, int kk)
 {
     const int l = threadIdx.x & 63;
     if constexpr (!TR) {
-        return *reinterpret_cast<const typename In<T>::vec *>(
+        static_assert(HALF == 2, "one read");
+        f.v = *reinterpret_cast<const typename In<T>::vec *>(
             lds + (S16 ? lds_off(base + (l & 15), kk * 4 + (l >> 4)) : lds_off(base + (l & 31), kk * 2 + (l >> 5))));
     } else {
         static_assert(!S16 || ROWS >= 128, "see swz_t");
@@ -458,10 +473,8 @@ __device__ __forceinline__ typename In<T>::vec read_frag(const char *lds, int ba
         const int k = S16 ? kk * 32 + (l >> 4) * 8 + ((l & 15) >> 2) : kk * 16 + (l >> 5) * 8 + ((l & 15) >> 2);
         const int col = base + (S16 ? 0 : ((l >> 4) & 1) * 16) + (l & 3) * 4;
         const char *p = lds + k * ROW_BYTES + ((((col >> 3) ^ swz_t<ROWS>(k))) << 4) + ((col * 2) & 15);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * ROW_BYTES));
-        const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_bit_cast(typename In<T>::vec, v);
+        if constexpr (HALF != 1) f.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+        if constexpr (HALF != 0) f.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * ROW_BYTES));
     }
 }
 
@@ -498,10 +511,10 @@ template <bool S16> __device__ __forceinline__ int quad_col(int q)
 //     code.  With transposing reads, two per operand, the reads of a part are too many for its last 20 MFMAs.
 //   else: a second set, read in the order in which the next part's MFMAs first use it (A0, B0 .. , A1 ..).
 // NB: MFMAs of a slice's last part that precede its barrier; the next slice's operands are read behind it.
-template <int MI, int NI, bool S16, bool TR> struct SlicePlan {
+template <int MI, int NI, bool S16, bool A_TR, bool B_TR> struct SlicePlan {
     static constexpr int PARTS = S16 ? 2 : 4, DEPTH = S16 ? 32 : 16, ROWS = S16 ? 16 : 32;
     static constexpr int AF = MI * 32 / ROWS, BF = NI * 32 / ROWS, NM = AF * BF, NOPS = AF + BF;
-    static constexpr bool SINGLE = S16 && !TR && NM == 32 && (AF == 8 || BF == 8), LONG_A = AF == 8;
+    static constexpr bool SINGLE = S16 && !A_TR && !B_TR && NM == 32 && (AF == 8 || BF == 8), LONG_A = AF == 8;
     static constexpr int SETS = SINGLE ? 1 : 2;
     // (two S16 sets: the reads of the first part end at three quarters of it, a quarter of a part of MFMAs goes out before the
     // barrier, so that it does not wait for reads just requested: 114 -> 107 us for the 4096^3 forward)
@@ -512,35 +525,40 @@ template <int MI, int NI, bool S16, bool TR> struct SlicePlan {
     static constexpr int a_of(int c) { return !SINGLE ? c / BF : LONG_A ? long_of(c) : short_of(c); }
     static constexpr int b_of(int c) { return !SINGLE ? c % BF : LONG_A ? short_of(c) : long_of(c); }
     static constexpr int set_of(int g) { return SINGLE ? 0 : g & 1; }
-    // reads, of the NOPS, that precede MFMA c of part g
+    // S16: the reads of a transposed operand one by one.  Two of them and their address between two MFMAs of 16 clocks hold the
+    // second one up: eq. 1, both reads together -> one by one, us: 4096^3 at p = 0 114.5 -> 112.2, at p = 0.5 64.1 -> 63.5,
+    // 65536 x 4096 x 1024 at p = 0.3 352 -> 347, 16384 x 3072 x 768 (128 x 64 blocks) 72.1 -> 71.2
+    static constexpr int UA = S16 && A_TR ? 2 : 1, UB = S16 && B_TR ? 2 : 1, UNITS = AF * UA + BF * UB;
+    // reads, of the UNITS, that precede MFMA c of part g
     static constexpr int reads_before(int g, int c)
     {
         const int c0 = g == PARTS - 1 ? NB : 0;
         if (c < c0) return 0;
         const int over = g == PARTS - 1 ? NM - NB : NM * 3 / 4;
-        const int r = S16 ? ceil_div((c - c0) * NOPS, over) : (c - c0) * RPM;
-        return r < NOPS ? r : NOPS;
+        const int r = S16 ? ceil_div((c - c0) * UNITS, over) : (c - c0) * RPM;
+        return r < UNITS ? r : UNITS;
     }
-    // calls read_a(i) / read_b(i) for the operands that are read after MFMA C of part G
+    // calls read_a(i, half) / read_b(i, half) for what is read after MFMA C of part G (half: see read_frag)
     template <int G, int C, class FA, class FB> __device__ __forceinline__ static void reads(FA &&read_a, FB &&read_b)
     {
         if constexpr (SINGLE) {
             constexpr int l = C >= 28 ? C - 24 : C >= 12 && C < 16 ? C - 12 : -1, s = C >= 16 && C % 4 == 3 ? (C - 16) / 4 : -1;
             if constexpr (s >= 0) {
-                if constexpr (LONG_A) read_b(std::integral_constant<int, s>{});
-                else read_a(std::integral_constant<int, s>{});
+                if constexpr (LONG_A) read_b(std::integral_constant<int, s>{}, std::integral_constant<int, 2>{});
+                else read_a(std::integral_constant<int, s>{}, std::integral_constant<int, 2>{});
             }
             if constexpr (l >= 0) {
-                if constexpr (LONG_A) read_a(std::integral_constant<int, l>{});
-                else read_b(std::integral_constant<int, l>{});
+                if constexpr (LONG_A) read_a(std::integral_constant<int, l>{}, std::integral_constant<int, 2>{});
+                else read_b(std::integral_constant<int, l>{}, std::integral_constant<int, 2>{});
             }
         } else {
             constexpr int r0 = reads_before(G, C), r1 = reads_before(G, C + 1);
             static_for<r1 - r0>([&](auto ri) __attribute__((always_inline)) {
-                constexpr int r = r0 + decltype(ri)::value;
-                if constexpr (r == 0) read_a(std::integral_constant<int, 0>{});
-                else if constexpr (r <= BF) read_b(std::integral_constant<int, r - 1>{});
-                else read_a(std::integral_constant<int, r - BF>{});
+                // A0, B0 .. B(BF-1), A1 ..
+                constexpr int r = r0 + decltype(ri)::value, rb = r - UA, ra = rb - BF * UB;
+                if constexpr (r < UA) read_a(std::integral_constant<int, 0>{}, std::integral_constant<int, UA == 2 ? r : 2>{});
+                else if constexpr (rb < BF * UB) read_b(std::integral_constant<int, rb / UB>{}, std::integral_constant<int, UB == 2 ? rb % 2 : 2>{});
+                else read_a(std::integral_constant<int, 1 + ra / UA>{}, std::integral_constant<int, UA == 2 ? ra % 2 : 2>{});
             });
         }
     }

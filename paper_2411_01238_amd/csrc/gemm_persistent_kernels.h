@@ -13,14 +13,15 @@ namespace {
 template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int WN, bool S16> struct Compute {
     static constexpr int WTM = TM / WM, WTN = TN / WN, MI = WTM / 32, NI = WTN / 32;
     static constexpr int A_BYTES = TM * TK * 2;
-    using SP = SlicePlan<MI, NI, S16, A_TR || B_TR>;
+    using SP = SlicePlan<MI, NI, S16, A_TR, B_TR>;
     static constexpr int ESZ = (int)sizeof(OutT);
     static constexpr int STAGING = 32 * 128;         // output staging per wavefront: 32 rows of 128 bytes
     static constexpr int NIP = 128 / (32 * ESZ);     // 32-column accumulator blocks per 128-byte row
     static constexpr int NJ = NI / NIP;              // 128-byte column groups of the wavefront's sub-tile
     static_assert(NI % NIP == 0, "a wavefront's columns must fill whole 128-byte rows");
 
-    typename In<T>::vec fa[SP::SETS][SP::AF], fb[SP::SETS][SP::BF];
+    Frag<T, A_TR> fa[SP::SETS][SP::AF];
+    Frag<T, B_TR> fb[SP::SETS][SP::BF];
     Block<S16> acc[MI][NI];
     int wm, wn;
 
@@ -54,9 +55,9 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
     __device__ __forceinline__ void first(const char *st)
     {
 #pragma unroll
-        for (int i = 0; i < SP::AF; ++i) fa[0][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, 0);
+        for (int i = 0; i < SP::AF; ++i) read_frag<T, A_TR, TM, S16>(fa[0][i], st, wm * WTM + i * SP::ROWS, 0);
 #pragma unroll
-        for (int i = 0; i < SP::BF; ++i) fb[0][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, 0);
+        for (int i = 0; i < SP::BF; ++i) read_frag<T, B_TR, TN, S16>(fb[0][i], st + A_BYTES, wn * WTN + i * SP::ROWS, 0);
     }
     // One slice, part by part (SlicePlan).  On entry the first part's operands are in flight; during every part the
     // next one's are read.  After the first MFMAs of the last part comes the slice's barrier (every wavefront is done
@@ -76,12 +77,12 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                     __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                SP::template mfma<T, a, b, SWAP>(acc, fa[cb][a], fb[cb][b]);
+                SP::template mfma<T, a, b, SWAP>(acc, fa[cb][a].get(), fb[cb][b].get());
                 const char *const st = g < LAST ? cur : nx1;
                 constexpr int kk = g < LAST ? g + 1 : 0;
                 SP::template reads<g, c>(
-                    [&](auto i) __attribute__((always_inline)) { fa[nb][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk); },
-                    [&](auto i) __attribute__((always_inline)) { fb[nb][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
+                    [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, A_TR, TM, S16, decltype(h)::value>(fa[nb][i], st, wm * WTM + i * SP::ROWS, kk); },
+                    [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, B_TR, TN, S16, decltype(h)::value>(fb[nb][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
                 __builtin_amdgcn_sched_barrier(0);
             });
         });

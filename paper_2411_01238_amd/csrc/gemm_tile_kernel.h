@@ -295,18 +295,19 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
             __builtin_amdgcn_s_barrier();
         }
 
-        using SP = SlicePlan<MI, NI, S16, A_TR || B_TR>;
-        typename In<T>::vec fa[SP::SETS][SP::AF], fb[SP::SETS][SP::BF];
+        using SP = SlicePlan<MI, NI, S16, A_TR, B_TR>;
+        Frag<T, A_TR> fa[SP::SETS][SP::AF];
+        Frag<T, B_TR> fb[SP::SETS][SP::BF];
         auto read_frags = [&](int buf, const char *st, int kk) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < SP::AF; ++i) fa[buf][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk);
+            for (int i = 0; i < SP::AF; ++i) read_frag<T, A_TR, TM, S16>(fa[buf][i], st, wm * WTM + i * SP::ROWS, kk);
 #pragma unroll
-            for (int i = 0; i < SP::BF; ++i) fb[buf][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk);
+            for (int i = 0; i < SP::BF; ++i) read_frag<T, B_TR, TN, S16>(fb[buf][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk);
         };
         auto mfmas = [&](int buf) __attribute__((always_inline)) {
             static_for<SP::NM>([&](auto ci) __attribute__((always_inline)) {
                 constexpr int c = decltype(ci)::value, a = SP::a_of(c), b = SP::b_of(c);
-                SP::template mfma<T, a, b, false>(acc, fa[buf][a], fb[buf][b]);
+                SP::template mfma<T, a, b, false>(acc, fa[buf][a].get(), fb[buf][b].get());
             });
         };
         constexpr int NM = SP::NM;
@@ -361,13 +362,13 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
                             __builtin_amdgcn_s_barrier();
                             __builtin_amdgcn_sched_barrier(0);
                         }
-                        SP::template mfma<T, a, b, false>(acc, fa[cb][a], fb[cb][b]);
+                        SP::template mfma<T, a, b, false>(acc, fa[cb][a].get(), fb[cb][b].get());
                         // operands for the next part (of this slice, or the first of slice s+1)
                         const char *const st = g < LAST ? cur : nx1;
                         constexpr int kk = g < LAST ? g + 1 : 0;
                         SP::template reads<g, c>(
-                            [&](auto i) __attribute__((always_inline)) { fa[nb][i] = read_frag<T, A_TR, TM, S16>(st, wm * WTM + i * SP::ROWS, kk); },
-                            [&](auto i) __attribute__((always_inline)) { fb[nb][i] = read_frag<T, B_TR, TN, S16>(st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
+                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, A_TR, TM, S16, decltype(h)::value>(fa[nb][i], st, wm * WTM + i * SP::ROWS, kk); },
+                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, B_TR, TN, S16, decltype(h)::value>(fb[nb][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
                         if constexpr (g < LAST && WITH_DMA) {
                             constexpr int gc = g * NM + c;
                             constexpr int j0 = gc * NDMA_ITER / (LAST * NM), j1 = (gc + 1) * NDMA_ITER / (LAST * NM);

@@ -20,7 +20,7 @@
 // 64-row tiles, several workgroups per CU).  The paper names the lack of software pipelining as
 // the reason its kernels lose to dense at zero sparsity (Section 5.1); here, while the MFMAs of
 // slice t run, slice t+1 is complete in LDS and slice t+2 is on its way.  One barrier per slice,
-// placed after the first MFMAs of the slice's last quarter so that the matrix pipe has work
+// placed after the first MFMAs of the slice's last part (SlicePlan) so that the matrix pipe has work
 // while the wavefronts meet.  Inside a slice every instruction has a fixed place (compile-time
 // loops and scheduling fences), because one computing wavefront per SIMD has no other wavefront
 // to hide its issue slots.

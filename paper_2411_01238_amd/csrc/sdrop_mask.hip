@@ -2,12 +2,12 @@
 // Sections 3.2 and 3.4), plus the small host-side pieces of the C ABI that are
 // not GEMMs (layout, error text).
 //
-// Two launches.  (1) The draw: one wavefront per 64 blocks of a block row (lane <-> block
+// Two launches (one for grids of up to kFusedDrawBlocks blocks, whose list workgroups draw them).  (1) The draw: one wavefront per 64 blocks of a block row (lane <-> block
 // column), spread over the whole chip because ten Philox rounds per block are integer-multiply
 // bound; the 64-lane ballot of the keep decisions IS the packed 64-bit mask word of
-// Section 3.4.  (2) The lists: one 1024-thread workgroup turns the words into every index
-// list.  The largest mask here has 16384 blocks, so this part is latency, not throughput,
-// and a single workgroup needs no cross-workgroup scan: a wavefront owns a block row,
+// Section 3.4.  (2) The lists: 1024-thread workgroups, one or (more than 64 words) several that
+// each derive counts and pointers of the whole grid and share the lists out, turn the words into every index
+// list.  This part is latency, not throughput, and so needs no cross-workgroup scan: a wavefront owns a block row,
 // popcount(word & lanes-below) is the position of a kept block inside its row's list, row
 // totals become row_ptr by a workgroup prefix scan, and the column lists (what eq. 3 walks)
 // are built the same way with lane <-> block row.

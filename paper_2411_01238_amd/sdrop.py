@@ -455,6 +455,11 @@ def sdrop_fwd_seeded(X, W, BM, BK, p, seed, rng_stream=0, mask=None, out_dtype=N
     return out, m
 
 
+def fwd_dense_has_kernel(X, W, w_layout=W_KN):
+    """Whether sdrop_fwd_dense is worth calling: False only for shapes that it has no kernel for."""
+    return X.shape[0] % 128 == 0 and (w_layout == W_KN or W.shape[0] % 256 == 0)
+
+
 def sdrop_fwd_dense(X, W, BM, BK, w_layout=W_KN, bias=None):
     """eq. (1) with nothing dropped, without a mask object: Y of X's type, the bits of sdrop_fwd_seeded with p = 0; None
     where the library has no such kernel for the shape (call sdrop_fwd_seeded then)."""

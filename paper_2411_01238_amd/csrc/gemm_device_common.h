@@ -230,6 +230,14 @@ __device__ __forceinline__ uint4 gate16(uint4 out, uint4 gate)
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 // Byte offset of 16-byte chunk c (0..7) of row r in an LDS operand tile.
 __device__ __forceinline__ int lds_off(int r, int c) { return r * 128 + (((c ^ swz(r)) & 7) << 4); }
+// The same for an operand that is stored through registers.  The transposed stores go to rows 4 or 8 apart, of which swz()
+// tells two: rotate its value left by one and flip with bits 4,5 of r.  Reads of 32 rows are as free of conflicts as above.
+__device__ __forceinline__ int swz_reg(int r)
+{
+    const int m = (r >> 1) & 7;
+    return (((m & 3) << 1) | (m >> 2)) ^ ((r >> 3) & 6);
+}
+__device__ __forceinline__ int lds_off_reg(int r, int c) { return r * 128 + (((c ^ swz_reg(r)) & 7) << 4); }
 
 // One global_load_lds_dwordx4: every lane moves 16 bytes from sbase + voff (uniform 64-bit base
 // plus 32-bit lane offset) to LDS byte address lds_base + 16*lane.  Written as inline assembly on
@@ -409,7 +417,7 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
 #pragma unroll
             for (int q = PART * PER; q < (PART + 1) * PER; ++q) {
                 const int c = threadIdx.x + q * kThreads;
-                *reinterpret_cast<uint4 *>(lds + lds_off(c >> 3, c & 7)) =
+                *reinterpret_cast<uint4 *>(lds + lds_off_reg(c >> 3, c & 7)) =
                     make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
             }
         } else {
@@ -424,7 +432,7 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     o[j] = __builtin_amdgcn_perm(d[DW_PER_ROW * (2 * j + 1) + n / 2], d[DW_PER_ROW * (2 * j) + n / 2], sel);
-                *reinterpret_cast<uint4 *>(lds + lds_off(ng * NW + n, kc)) = make_uint4(o[0], o[1], o[2], o[3]);
+                *reinterpret_cast<uint4 *>(lds + lds_off_reg(ng * NW + n, kc)) = make_uint4(o[0], o[1], o[2], o[3]);
             }
         }
     }
@@ -458,17 +466,18 @@ template <class T> struct Frag<T, true> {
         return __builtin_bit_cast(typename In<T>::vec, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     }
 };
-// HALF: 0 or 1, one of an operand's two transposing reads; 2: the whole operand
-template <class T, bool TR, int ROWS, bool S16, int HALF = 2>
+// HALF: 0 or 1, one of an operand's two transposing reads; 2: the whole operand.  REG: stored through registers (lds_off_reg).
+template <class T, bool TR, int ROWS, bool S16, int HALF = 2, bool REG = false>
 __device__ __forceinline__ void read_frag(Frag<T, TR> &f, const char *lds, int base, int kk)
 {
     const int l = threadIdx.x & 63;
     if constexpr (!TR) {
-        static_assert(HALF == 2, "one read");
+        static_assert(HALF == 2 && !(REG && S16), "one read; 32 rows of it");
         f.v = *reinterpret_cast<const typename In<T>::vec *>(
-            lds + (S16 ? lds_off(base + (l & 15), kk * 4 + (l >> 4)) : lds_off(base + (l & 31), kk * 2 + (l >> 5))));
+            lds + (REG ? lds_off_reg(base + (l & 31), kk * 2 + (l >> 5))
+                       : S16 ? lds_off(base + (l & 15), kk * 4 + (l >> 4)) : lds_off(base + (l & 31), kk * 2 + (l >> 5))));
     } else {
-        static_assert(!S16 || ROWS >= 128, "see swz_t");
+        static_assert(!REG && (!S16 || ROWS >= 128), "see swz_t");
         constexpr int ROW_BYTES = 2 * ROWS;
         const int k = S16 ? kk * 32 + (l >> 4) * 8 + ((l & 15) >> 2) : kk * 16 + (l >> 5) * 8 + ((l & 15) >> 2);
         const int col = base + (S16 ? 0 : ((l >> 4) & 1) * 16) + (l & 3) * 4;

@@ -300,9 +300,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
         Frag<T, B_TR> fb[SP::SETS][SP::BF];
         auto read_frags = [&](int buf, const char *st, int kk) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < SP::AF; ++i) read_frag<T, A_TR, TM, S16>(fa[buf][i], st, wm * WTM + i * SP::ROWS, kk);
+            for (int i = 0; i < SP::AF; ++i) read_frag<T, A_TR, TM, S16, 2, !A_DMA>(fa[buf][i], st, wm * WTM + i * SP::ROWS, kk);
 #pragma unroll
-            for (int i = 0; i < SP::BF; ++i) read_frag<T, B_TR, TN, S16>(fb[buf][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk);
+            for (int i = 0; i < SP::BF; ++i) read_frag<T, B_TR, TN, S16, 2, !B_DMA>(fb[buf][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk);
         };
         auto mfmas = [&](int buf) __attribute__((always_inline)) {
             static_for<SP::NM>([&](auto ci) __attribute__((always_inline)) {
@@ -367,8 +367,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
                         const char *const st = g < LAST ? cur : nx1;
                         constexpr int kk = g < LAST ? g + 1 : 0;
                         SP::template reads<g, c>(
-                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, A_TR, TM, S16, decltype(h)::value>(fa[nb][i], st, wm * WTM + i * SP::ROWS, kk); },
-                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, B_TR, TN, S16, decltype(h)::value>(fb[nb][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
+                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, A_TR, TM, S16, decltype(h)::value, !A_DMA>(fa[nb][i], st, wm * WTM + i * SP::ROWS, kk); },
+                            [&](auto i, auto h) __attribute__((always_inline)) { read_frag<T, B_TR, TN, S16, decltype(h)::value, !B_DMA>(fb[nb][i], st + A_BYTES, wn * WTN + i * SP::ROWS, kk); });
                         if constexpr (g < LAST && WITH_DMA) {
                             constexpr int gc = g * NM + c;
                             constexpr int j0 = gc * NDMA_ITER / (LAST * NM), j1 = (gc + 1) * NDMA_ITER / (LAST * NM);

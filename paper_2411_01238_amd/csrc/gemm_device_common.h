@@ -347,7 +347,11 @@ template <int ROWS, int NW> struct DmaT {
 // !KMAJ: HBM tile [64][ROWS] (ROWS contiguous).  Thread t owns reduction rows
 //        8*(t/32)..+8 and columns NW*(t%32)..+NW, NW = ROWS/32, and turns them
 //        into NW LDS rows of one 16-byte chunk each.
-// RAGGED: chunks beyond `lim` valid elements of the contiguous dimension read as zero.
+// RAGGED: only `lim` elements of the contiguous dimension are valid, and chunks beyond them are not read.  KMAJ, where that
+//         dimension is the reduction: they are stored as zeros.  (Zeroed where they are loaded they wait for every load at
+//         once, one after the other where the compiler will have it so.  eq. 1 with a GELU, us: 256 x 7680 x 400 172 / 247
+//         (gathered / one by one) -> 107, 1152 x 2496 x 1440 with 64-row blocks 61 / 78 -> 39; eq. 2 at p = 0.1, 4096^2 x 4104
+//         300 -> 177.)  !KMAJ: they are columns of the output that nothing is stored for, and hold whatever.
 template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
     static constexpr int NW = ROWS / 32;                       // !KMAJ: columns per thread
     static constexpr int NCH = KMAJ ? ROWS * 8 / kThreads : 1; // KMAJ: chunks per thread
@@ -359,16 +363,11 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
     static_assert(ROWS % 32 == 0 && (KMAJ ? NCH >= 1 : (NW == 2 || NW == 4 || NW == 8)), "unsupported tile edge");
     static_assert(!KMAJ || NGRP == 1 || (GROUP_ROWS % 32 == 0), "row groups must cover whole passes");
     uint32_t d[ND];
+    bool ok;            // RAGGED: are this thread's chunks valid?
 
-    template <class V> __device__ __forceinline__ static V ld(const char *p, const char *safe, bool ok)
+    template <class V> __device__ __forceinline__ V ld(const char *p, const char *safe) const
     {
-        if constexpr (RAGGED) {
-            V v = *reinterpret_cast<const V *>(ok ? p : safe);   // `safe` is the (valid) start of the row
-            V z = {};
-            return ok ? v : z;
-        } else {
-            return *reinterpret_cast<const V *>(p);
-        }
+        return *reinterpret_cast<const V *>(RAGGED && !ok ? safe : p);   // `safe` is the (valid) start of the row
     }
 
     // base[g]: start of row group g (uniform).  lim = valid elements along the contiguous
@@ -379,29 +378,29 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
         if constexpr (KMAJ) {
             const int cc = threadIdx.x & 7;
             const uint32_t voff = (uint32_t)(threadIdx.x >> 3) * (uint32_t)ld_bytes + cc * 16;
-            const bool ok = cc * 8 < lim;
+            ok = cc * 8 < lim;
 #pragma unroll
             for (int q = 0; q < NCH; ++q) {
                 const int g = (q * 32) / GROUP_ROWS;           // rows of pass q: 32q .. 32q+31
                 const char *sbase = base[g] + (int64_t)(32 * q - g * GROUP_ROWS) * ld_bytes;
-                const uint4 v = ld<uint4>(sbase + voff, sbase, ok);
+                const uint4 v = ld<uint4>(sbase + voff, sbase);
                 d[4 * q] = v.x; d[4 * q + 1] = v.y; d[4 * q + 2] = v.z; d[4 * q + 3] = v.w;
             }
         } else {
             const int ng = threadIdx.x & 31, kc = threadIdx.x >> 5;
             const uint32_t voff = (uint32_t)(kc * 8) * (uint32_t)ld_bytes + ng * (NW * 2);
-            const bool ok = ng * NW < lim;
+            ok = ng * NW < lim;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const char *sbase = base[0] + (int64_t)i * ld_bytes;
                 if constexpr (NW == 8) {
-                    const uint4 v = ld<uint4>(sbase + voff, sbase, ok);
+                    const uint4 v = ld<uint4>(sbase + voff, sbase);
                     d[4 * i] = v.x; d[4 * i + 1] = v.y; d[4 * i + 2] = v.z; d[4 * i + 3] = v.w;
                 } else if constexpr (NW == 4) {
-                    const uint2 v = ld<uint2>(sbase + voff, sbase, ok);
+                    const uint2 v = ld<uint2>(sbase + voff, sbase);
                     d[2 * i] = v.x; d[2 * i + 1] = v.y;
                 } else {
-                    d[i] = ld<uint32_t>(sbase + voff, sbase, ok);
+                    d[i] = ld<uint32_t>(sbase + voff, sbase);
                 }
             }
         }
@@ -417,8 +416,8 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
 #pragma unroll
             for (int q = PART * PER; q < (PART + 1) * PER; ++q) {
                 const int c = threadIdx.x + q * kThreads;
-                *reinterpret_cast<uint4 *>(lds + lds_off_reg(c >> 3, c & 7)) =
-                    make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+                const uint4 v = make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+                *reinterpret_cast<uint4 *>(lds + lds_off_reg(c >> 3, c & 7)) = RAGGED && !ok ? make_uint4(0, 0, 0, 0) : v;
             }
         } else {
             // d[(NW/2)*i + w] holds columns 2w (low half) and 2w+1 (high half) of reduction row i.

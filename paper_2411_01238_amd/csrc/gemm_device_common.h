@@ -239,6 +239,14 @@ __device__ __forceinline__ int swz_reg(int r)
 }
 __device__ __forceinline__ int lds_off_reg(int r, int c) { return r * 128 + (((c ^ swz_reg(r)) & 7) << 4); }
 
+// A uniform value in scalar registers of its own.  As a part of the eight arguments that one load brings in, the compiler
+// keeps or spills it with all of them.
+__device__ __forceinline__ int64_t own_scalar(int64_t v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 // One global_load_lds_dwordx4: every lane moves 16 bytes from sbase + voff (uniform 64-bit base
 // plus 32-bit lane offset) to LDS byte address lds_base + 16*lane.  Written as inline assembly on
 // purpose: the compiler then does not know that LDS is written behind its back, and does not make
@@ -503,13 +511,11 @@ template <> struct Block<true> {
     __device__ __forceinline__ f32q quad(int q) const { return v[q]; }
     __device__ __forceinline__ void set(int q, f32q x) { v[q] = x; }
 };
-template <bool S16> __device__ __forceinline__ int quad_row(int q) { return S16 ? (q >> 1) * 16 + (int)(threadIdx.x & 15) : (int)(threadIdx.x & 31); }
-template <bool S16> __device__ __forceinline__ int quad_col(int q)
+template <bool S16> __device__ __forceinline__ int quad_row(int q, int l = threadIdx.x & 63) { return S16 ? (q >> 1) * 16 + (l & 15) : l & 31; }
+template <bool S16> __device__ __forceinline__ int quad_col(int q, int l = threadIdx.x & 63)
 {
-    const int l = threadIdx.x & 63;
     return S16 ? (q & 1) * 16 + (l >> 4) * 4 : 8 * q + 4 * (l >> 5);
 }
-
 // A wavefront's MI x NI blocks of 32 x 32, a slice of 64 reduction indices: the slice in PARTS parts of one instruction's
 // depth, AF + BF operands and AF x BF = NM MFMAs each, in which order, and after which of them the next part's operands are
 // read.

@@ -149,6 +149,22 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
         for (int it = 0; it < 4; ++it)
             g[it] = *reinterpret_cast<const uint4 *>(tl.aux + (out - tl.c0) + (int64_t)(it * 8 + rrow) * ldc + rch * 16);
     }
+    // The gate values of one piece in the accumulator's layout, 8 bytes per lane and quad (16-bit elements whatever the output
+    // is); `out` is the piece's place in the output.  All of a piece are requested together: requested where a quad needs its
+    // own they are eight trips to memory in a row, unless the compiler happens to gather them.  (All pieces of the sub-tile up
+    // front were slower, eq. 2 under a GELU's gate with fp32 results: 6912 x 4224 x 256 49.8 us against 46.5, 59264 x 1152 x 768
+    // 155 against 146.)
+    typedef __attribute__((__vector_size__(4 * sizeof(typename In<T>::out16)))) typename In<T>::out16 gate4v;
+    __device__ __forceinline__ void gate_load_acc(const char *out, gate4v (&g)[NIP * 4], int64_t ldc, const Tail &tl, int lane)
+    {
+        const char *const base = tl.aux + (out - tl.c0) / ESZ * 2;
+        const uint32_t ld = (uint32_t)(ldc / ESZ * 2), lane_off = quad_row<S16>(0, lane) * ld + quad_col<S16>(0, lane) * 2;
+#pragma unroll
+        for (int i = 0; i < NIP * 4; ++i) {
+            const int drow = S16 ? (i >> 1 & 1) * 16 : 0, dcol = (i >> 2) * 32 + (S16 ? (i & 1) * 16 : (i & 3) * 8);     // quad i & 3 against quad 0
+            g[i] = *reinterpret_cast<const gate4v *>(base + drow * (int64_t)ld + dcol * 2 + lane_off);
+        }
+    }
     // MODE: which tail this instance is compiled for (TailMode; the host picks the kernel by it).  The
     // generic form carries every activation and every gate's derivative in each of its 16 to 32
     // unrolled steps, ~200 KB of code of which a tile runs a few KB scattered over all of it: a ReLU
@@ -183,6 +199,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                 for (int q = 0; q < AHEAD && q < NP; ++q) gate_load(MI0 + q / NJW, NJ0 + q % NJW, gate_q[q], ldc, tl, dst);
             }
         }
+        gate4v gate_a[NIP * 4];
 #pragma unroll
         for (int pc = 0; pc < NP; ++pc) {
             {
@@ -194,6 +211,12 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                 int64_t gcol0 = 0;
                 char *const out = dst(mi, nj, gcol0);
                 if (!out) continue;                        // uniform
+                if constexpr (TAIL) {
+                    if (gate_acc) {
+                        gate_load_acc(out, gate_a, ldc, tl, lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
                 const int vch = RAGN ? (int)((ncols - gcol0) * ESZ / 16) : 8;      // valid 16-byte chunks of the piece's rows
                 if (RAGN && vch <= 0) continue;            // uniform
 #pragma unroll
@@ -201,7 +224,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const f32q a = acc[mi][nj * NIP + nl].quad(q);
-                        const int wrow = quad_row<S16>(q), wcol = nl * 32 + quad_col<S16>(q);      // place of the quad in the piece
+                        const int wrow = quad_row<S16>(q, lane), wcol = nl * 32 + quad_col<S16>(q, lane);      // place of the quad in the piece
                         float v[4] = {a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale};
                         if constexpr (MODE == kTailBias16) {
                             // the product rounded, then the sum: what adding the bias to a finished Y gives, bit for bit.  (The
@@ -225,11 +248,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                                 act4(tl.act, v);
                             }
                             if (gate_acc) {
-                                // the gate matrix has 16-bit elements, read here in the accumulator's layout
-                                using E = typename In<T>::out16;
-                                typedef __attribute__((__vector_size__(4 * sizeof(E)))) E e4;
-                                const int64_t elem = (out - tl.c0) / ESZ + wrow * (ldc / ESZ) + wcol;
-                                const e4 x = *reinterpret_cast<const e4 *>(tl.aux + elem * (int64_t)sizeof(E));
+                                const gate4v x = gate_a[nl * 4 + q];
                                 const float xf[4] = {static_cast<float>(x[0]), static_cast<float>(x[1]), static_cast<float>(x[2]), static_cast<float>(x[3])};
                                 gate4(gate_mode, v, xf);
                             }
@@ -292,7 +311,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const f32q a = acc[pj * NIP + nl][r].quad(q);
-                        const int wrow = quad_row<S16>(q), wcol = nl * 32 + quad_col<S16>(q);
+                        const int wrow = quad_row<S16>(q, lane), wcol = nl * 32 + quad_col<S16>(q, lane);
                         const float v0 = a[0] * scale, v1 = a[1] * scale, v2 = a[2] * scale, v3 = a[3] * scale;
                         if constexpr (ESZ == 4) {
                             const int slot = (wcol >> 2) ^ (wrow & 7);
@@ -425,6 +444,8 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
     // A kernel handed a mask built for another problem writes nothing.  The header is tested after
     // the first look-ups have been issued (they are addressed by the tile number alone and stay
     // inside the mask object whatever it holds), so that it costs no round trip of its own.
+    // (see read_frag; with an element-wise tail the second operand set spills)
+    constexpr bool S16 = OP == FWD && TN == 256 && (TAIL == kTailNone || TAIL == kTailBias16);
     const MaskHeader *H = P.mv.hdr;
     auto mask_ok = [&]() __attribute__((always_inline)) -> bool {
         return mask_header_ok(H, P.M, P.K, P.BM, P.BK, true, P.p_call, P.status);
@@ -641,8 +662,6 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
         ord2 = uni(ord2_v);
     }
 
-    // (see read_frag; with an element-wise tail the second operand set spills)
-    constexpr bool S16 = OP == FWD && TN == 256 && (TAIL == kTailNone || TAIL == kTailBias16);
     Compute<T, OutT, A_TR, B_TR, TM, TN, WM, WN, S16> cw;
     cw.wm = wm; cw.wn = wn;
     cw.ncols = P.N;
@@ -801,6 +820,9 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
     constexpr int STAGES = 3, AHEAD = 2;
     constexpr int ESZ = (int)sizeof(OutT);
     constexpr int STAGING = 32 * 128;
+    constexpr bool S16 = true;                        // (see read_frag)
+    // tails that may come with a second output (the producing layer's, which have no gate)
+    constexpr bool SECOND = TAIL == kTailLight || TAIL == kTailGeluErf || TAIL == kTailGeneric;
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char *const staging = smem + STAGES * STAGE_BYTES;
@@ -966,6 +988,8 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
         const int wpr = H->words_per_row;
         const int row_chunks = P.BK * ESZ / 16;                      // 16-byte pieces per row of a block
         const int per_wave = TM * row_chunks / (NW * 64);           // store instructions per wavefront and block
+        // where the second output's zeros go, from the first one's place (0: nowhere); not an argument load per step
+        const int64_t c2_zeros = SECOND && P.zero_c2 ? own_scalar(P.C2 - P.C) : 0;
         int zpos = 0;                    // next position to test
         int zprog = 0;                   // store instructions already issued for the block in hand
         char *zblock = nullptr;          // the dropped block in hand, or null
@@ -983,8 +1007,8 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
                 const int c = (zprog * NW + wave) * 64 + lane;
                 char *const z = zblock + (c / row_chunks) * ldc + (c % row_chunks) * 16;
                 store_out(z, make_uint4(0, 0, 0, 0));
-                if constexpr (TAIL != kTailNone) {
-                    if (P.zero_c2) store_out(z + (P.C2 - P.C), make_uint4(0, 0, 0, 0));
+                if constexpr (SECOND) {
+                    if (c2_zeros) store_out(z + c2_zeros, make_uint4(0, 0, 0, 0));
                 }
                 if (++zprog == per_wave) zblock = nullptr;
                 return true;
@@ -1047,7 +1071,8 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
         }
         return g;
     };
-    Compute<T, OutT, false, W_NK, TM, TN, WM, WN, true> cw;
+    using Cw = Compute<T, OutT, false, W_NK, TM, TN, WM, WN, S16>;
+    Cw cw;
     cw.wm = wm; cw.wn = wn;
     int st0 = 0, st1 = 1, st2 = 2;
     bool started = false;
@@ -1127,14 +1152,21 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
                 cw.first(stage_ptr(0));
             }
             char *const c_rows = P.C + ((int64_t)row * P.BM + wm * WTM) * ldc;
-            auto dst = [&](int mi, int nj, int64_t &gcol0) __attribute__((always_inline)) -> char * {
-                const int col_t = wn * WTN + nj * (128 / ESZ);         // first column of the piece, in the tile
+            // First column of each of the wavefront's column groups (negative: not to be written), worked out ahead of the slices.
+            // Where a tail's epilogue looked them up piece by piece, the entries lay in scratch memory, a round trip each behind
+            // all stores before it: producer with a GELU and both outputs, 4096^2 x 1024 half dropped 41.1 -> 37.8 us, 8064 x 1664 x 256
+            // 33.1 -> 29.8; eq. 2 under the GELU's gate (with the piece's gate values together, see gate_load_acc), 43392 x 4736 x 256
+            // 344 -> 291, 8064 x 1664 x 256 36.4 -> 32.6.
+            int gcols[Cw::NJ];
+#pragma unroll
+            for (int nj = 0; nj < Cw::NJ; ++nj) {
+                const int col_t = wn * WTN + nj * (128 / ESZ);         // in the tile
                 const int g = col_t >> 6;
-                if (g >= chunks_valid) return nullptr;
-                const int col = sel4(gc, a + (g >> cshift));
-                const int64_t col0 = (int64_t)col * P.BK + (g & cmask) * 64 + (col_t & 63);
-                gcol0 = col0;
-                return c_rows + (int64_t)(mi * 32) * ldc + col0 * ESZ;
+                gcols[nj] = g < chunks_valid ? uni(sel4(gc, a + (g >> cshift)) * P.BK + (g & cmask) * 64 + (col_t & 63)) : -1;
+            }
+            auto dst = [&](int mi, int nj, int64_t &gcol0) __attribute__((always_inline)) -> char * {
+                gcol0 = gcols[nj];
+                return gcol0 < 0 ? nullptr : c_rows + (int64_t)(mi * 32) * ldc + gcol0 * ESZ;
             };
             for (int s = 0; s < nsteps; ++s) {
                 cw.slice(stage_ptr(st0), stage_ptr(st1));
@@ -1144,7 +1176,7 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
             __builtin_amdgcn_s_waitcnt(waitcnt_vm_only(0));
 #pragma unroll
             for (int b = 0; b < 4; ++b) { ngr[b] = uni(nxt.r[b]); ngc[b] = uni(nxt.c[b]); }
-            if constexpr (TAIL != kTailNone) {
+            if constexpr (SECOND) {
                 if (P.C2) {
                     // the producing layer's value before the activation, to the second output
                     const Tail tz = make_tail_preact(P);

@@ -10,7 +10,8 @@ namespace {
 
 // The computing side of a persistent kernel: one wavefront's accumulators and operand registers,
 // the MFMA schedule of one slice, and the epilogue.
-template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int WN, bool S16> struct Compute {
+// HOIST: a 64-bit address per row of the epilogue's stores instead of a uniform one plus a lane offset (see store).
+template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int WN, bool S16, bool HOIST = false> struct Compute {
     static constexpr int WTM = TM / WM, WTN = TN / WN, MI = WTM / 32, NI = WTN / 32;
     static constexpr int A_BYTES = TM * TK * 2;
     using SP = SlicePlan<MI, NI, S16, A_TR, B_TR>;
@@ -147,7 +148,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
         if (!out) return;                                  // uniform
 #pragma unroll
         for (int it = 0; it < 4; ++it)
-            g[it] = *reinterpret_cast<const uint4 *>(tl.aux + (out - tl.c0) + (int64_t)(it * 8 + rrow) * ldc + rch * 16);
+            g[it] = *reinterpret_cast<const uint4 *>(tl.aux + (out - tl.c0) + (int64_t)(it * 8) * ldc + (rrow * (uint32_t)ldc + rch * 16));
     }
     // The gate values of one piece in the accumulator's layout, 8 bytes per lane and quad (16-bit elements whatever the output
     // is); `out` is the piece's place in the output.  All of a piece are requested together: requested where a quad needs its
@@ -180,6 +181,12 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
         constexpr bool TAIL = MODE != kTailNone;
         const int lane = threadIdx.x & 63;
         const int rrow = lane >> 3, rch = lane & 7;
+        // a lane's 16 bytes of eight rows; the rest of a store's address is uniform.  With 64-bit lane addresses, eight registers
+        // kept across all tiles, the kernels of 128 accumulators spill them, and each reload between the stores waits for all
+        // stores before it (16 x 16 instructions; us: eq. 1 on a ragged N, 8192 x 1024 x 1000 21.6 -> 19.5, 5888 x 384 x 760
+        // 13.4 -> 12.2; eq. 2, 24448 x 5376 x 128 68 -> 61).  HOIST: the pair list's 16-bit kernel, which holds both epilogues, spills
+        // 13 registers this way and 2 the other (sdrop_bwd, 16384 x 4096 x 512 half dropped 99.5 against 108, 4096^3 151 against 156).
+        const uint32_t lane_off = rrow * (uint32_t)ldc + rch * 16;
         // 16-bit outputs under a ReLU gate are gated after rounding, on whole rows; everything else in the accumulator's layout
         const bool gate_rows = MODE == kTailReluGate ? ESZ == 2
                              : MODE == kTailGeneric ? (ESZ == 2 && tl.aux != nullptr && tl.gate_mode == SDROP_GATE_RELU) : false;
@@ -286,7 +293,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                             if (gate_rows) v = gate16<T>(v, gate_q[pc][it]);
                         }
                     }
-                    if (!RAGN || rch < vch) store_out(out + (int64_t)row * ldc + rch * 16, v);
+                    if (!RAGN || rch < vch) store_out(HOIST ? out + (int64_t)row * ldc + rch * 16 : out + (int64_t)(it * 8) * ldc + lane_off, v);
                 }
             }
         }
@@ -300,6 +307,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
         static_assert(MI % NIP == 0, "a wavefront's rows must fill whole 128-byte rows of the transposed tile");
         const int lane = threadIdx.x & 63;
         const int rrow = lane >> 3, rch = lane & 7;
+        const uint32_t lane_off = rrow * (uint32_t)ldc + rch * 16;
 #pragma unroll
         for (int r = 0; r < NI; ++r)
 #pragma unroll
@@ -336,7 +344,7 @@ template <class T, class OutT, bool A_TR, bool B_TR, int TM, int TN, int WM, int
                     const int row = it * 8 + rrow;
                     const uint4 x = rv[it];
                     const uint4 v = (ESZ == 4 || !(row & 1)) ? x : make_uint4(x.z, x.w, x.x, x.y);
-                    store_out(out + (int64_t)row * ldc + rch * 16, v);
+                    store_out(HOIST ? out + (int64_t)row * ldc + rch * 16 : out + (int64_t)(it * 8) * ldc + lane_off, v);
                 }
             }
     }
@@ -1071,7 +1079,7 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
         }
         return g;
     };
-    using Cw = Compute<T, OutT, false, W_NK, TM, TN, WM, WN, S16>;
+    using Cw = Compute<T, OutT, false, W_NK, TM, TN, WM, WN, S16, PAIRS>;
     Cw cw;
     cw.wm = wm; cw.wn = wn;
     int st0 = 0, st1 = 1, st2 = 2;

@@ -301,13 +301,14 @@ template <int ROWS, int NGRP, int NW> struct DmaK {
 
 // Slot swizzle of an LDS tile kept as it lies in HBM when the reduction index is the strided
 // one: [64 reduction rows][ROWS contiguous].  The transposing read of 32 lanes touches, for operands of 32
-// columns, 4 consecutive rows x 64 bytes; for operands of 16 columns, rows k .. k+3 and k+8 .. k+11 x 32 bytes.
-// XORing the 64-byte slot index with (row & 3) and the 32-byte half with bit 3 of the row keeps either on different
-// banks (without bit 3 the second costs two conflict cycles per read, counted).  128-byte rows, two of which share a round
-// of the banks, are read as 32 columns only: the 64-byte slot with bit 1 of the row.
-template <int ROWS> __device__ __forceinline__ int swz_t(int k)
+// columns, 4 consecutive rows x 64 bytes; for operands of 16 columns (S16), rows k .. k+3 and k+8 .. k+11 x 32 bytes.
+// XORing the 64-byte slot index with (row & 3) (with (row>>1)&1 for 128-byte rows) keeps the former on different banks, and the
+// 32-byte half with bit 3 of the row as well the latter (without it two conflict cycles per read, counted).  Bit 3 only where
+// it is needed: the loads then fetch a row in runs of 32 bytes instead of 64, which costs time where rows are not whole cache
+// lines (eq. 1 on 128-wide tiles, 384 x 7680 x 200 51.7 -> 53.9 us, 512 x 5376 x 232 31.7 -> 33.0).
+template <int ROWS, bool S16> __device__ __forceinline__ int swz_t(int k)
 {
-    return ROWS >= 128 ? ((k & 3) << 2) | (((k >> 3) & 1) << 1) : (((k >> 1) & 1) << 2);
+    return ROWS >= 128 ? ((k & 3) << 2) | (S16 ? ((k >> 3) & 1) << 1 : 0) : (((k >> 1) & 1) << 2);
 }
 
 // HBM -> LDS without registers for an operand tile [64][ROWS] (ROWS contiguous, rows ld_bytes
@@ -315,12 +316,12 @@ template <int ROWS> __device__ __forceinline__ int swz_t(int k)
 // it and fetches the chunk whose swizzled slot that is.  Row k = RPI*I + kl with I = w + NW*i: of the
 // bits that swz_t() sees only bit 3 depends on i, and only for 256-wide tiles, where it is i's lowest: two lane
 // offsets, for even and odd passes (the same one otherwise).
-template <int ROWS, int NW> struct DmaT {
+template <int ROWS, int NW, bool S16> struct DmaT {
     static constexpr int ROW_BYTES = 2 * ROWS, RPI = 1024 / ROW_BYTES;       // rows per instruction
     static constexpr int PER_WAVE = ROWS / (8 * NW);
     static_assert(ROWS % (8 * NW) == 0, "every wavefront issues whole instructions");
     static_assert(ROWS == 64 || ROWS == 128 || ROWS == 256, "unsupported tile edge");
-    static constexpr int ODD = ROWS == 256 ? 2 : 0;          // what an odd pass adds (XOR) to the chunk
+    static constexpr int ODD = S16 && ROWS == 256 ? 2 : 0;          // what an odd pass adds (XOR) to the chunk
     static_assert(NW == 4, "the passes' row bits");
     uint32_t voff[2];
     int wave, chunk;                                         // chunk: the 16-byte chunk of the row this lane fetches in even passes
@@ -331,7 +332,7 @@ template <int ROWS, int NW> struct DmaT {
         const int kl = (lane * 16) / ROW_BYTES;              // row within the instruction
         const int cpos = ((lane * 16) % ROW_BYTES) >> 4;     // 16-byte slot within the row
         const int k0 = RPI * wave + kl;
-        chunk = cpos ^ swz_t<ROWS>(k0);
+        chunk = cpos ^ swz_t<ROWS, S16>(k0);
         voff[0] = (uint32_t)kl * (uint32_t)ld_bytes + (chunk << 4);
         voff[1] = (uint32_t)kl * (uint32_t)ld_bytes + ((chunk ^ ODD) << 4);
     }
@@ -488,7 +489,7 @@ __device__ __forceinline__ void read_frag(Frag<T, TR> &f, const char *lds, int b
         constexpr int ROW_BYTES = 2 * ROWS;
         const int k = S16 ? kk * 32 + (l >> 4) * 8 + ((l & 15) >> 2) : kk * 16 + (l >> 5) * 8 + ((l & 15) >> 2);
         const int col = base + (S16 ? 0 : ((l >> 4) & 1) * 16) + (l & 3) * 4;
-        const char *p = lds + k * ROW_BYTES + ((((col >> 3) ^ swz_t<ROWS>(k))) << 4) + ((col * 2) & 15);
+        const char *p = lds + k * ROW_BYTES + ((((col >> 3) ^ swz_t<ROWS, S16>(k))) << 4) + ((col * 2) & 15);
         if constexpr (HALF != 1) f.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
         if constexpr (HALF != 0) f.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * ROW_BYTES));
     }

@@ -494,8 +494,8 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
 
     if (loader) {
         // ---------------- loaders: the stream of slices ----------------
-        using DmaA = typename std::conditional<A_KMAJ, DmaK<TM, 1, NW>, DmaT<TM, NW>>::type;
-        using DmaB = typename std::conditional<W_NK && OP == FWD, DmaK<TN, 1, NW>, DmaT<TN, NW>>::type;
+        using DmaA = typename std::conditional<A_KMAJ, DmaK<TM, 1, NW>, DmaT<TM, NW, S16>>::type;
+        using DmaB = typename std::conditional<W_NK && OP == FWD, DmaK<TN, 1, NW>, DmaT<TN, NW, S16>>::type;
         DmaA da;
         DmaB db;
         da.init(lda, wave);
@@ -828,7 +828,9 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
     constexpr int STAGES = 3, AHEAD = 2;
     constexpr int ESZ = (int)sizeof(OutT);
     constexpr int STAGING = 32 * 128;
-    constexpr bool S16 = true;                        // (see read_frag)
+    // (see read_frag.  Not with an [N,K] weight's transposing reads, 128 x 512^2 7.8 -> 7.3 us, 4096^3 92.0 -> 91.7, nor for fp32 pairs,
+    // where the registers spill: sdrop_bwd, 4096^2 x 512 at p = 0.3 51.3 -> 48.1)
+    constexpr bool S16 = !W_NK && !(PAIRS && ESZ == 4);
     // tails that may come with a second output (the producing layer's, which have no gate)
     constexpr bool SECOND = TAIL == kTailLight || TAIL == kTailGeluErf || TAIL == kTailGeneric;
 
@@ -871,7 +873,7 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
 
     if (loader) {
         DmaK<TM, 1, NW> da;
-        typename std::conditional<W_NK, DmaT<TN, NW>, DmaK<TN, DXG, NW>>::type db;
+        typename std::conditional<W_NK, DmaT<TN, NW, S16>, DmaK<TN, DXG, NW>>::type db;
         da.init(lda, wave);
         db.init(ldb, wave);
         constexpr int NDMA_A = TM / (8 * NW), NDMA_B = TN / (8 * NW), NDMA = NDMA_A + NDMA_B;

@@ -258,8 +258,8 @@ __device__ __forceinline__ void gemm_tile_body(const GemmParams &P, const int bi
         auto a_lim = [&](const Src &x) __attribute__((always_inline)) { return OP == DX ? x.lim : (OP == FWD ? TK : TM); };
 
         // direct-load engines (lane offsets computed once)
-        using DmaA = typename std::conditional<A_KMAJ, DmaK<TM, 1, NW>, DmaT<TM, NW>>::type;
-        using DmaB = typename std::conditional<B_KMAJ, DmaK<TN, DXG, NW>, DmaT<TN, NW>>::type;
+        using DmaA = typename std::conditional<A_KMAJ, DmaK<TM, 1, NW>, DmaT<TM, NW, S16>>::type;
+        using DmaB = typename std::conditional<B_KMAJ, DmaK<TN, DXG, NW>, DmaT<TN, NW, S16>>::type;
         DmaA da;
         DmaB db;
         if constexpr (A_DMA) da.init(lda, wave);

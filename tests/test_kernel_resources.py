@@ -15,8 +15,6 @@ MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 # Mangled name -> bytes of scratch memory that these may use, with the reason.
 ALLOWED = [
-    # the pair list's fp32 form
-    (r"gemm_persistent_dx_kernelI.*fLi128ELi256ELi2ELi2ELi0ELb0ELb1ELb0E|bwd_fused_kernelI.*ffLi256ELb1E", 72),
     # the pair list's 16-bit form holds two epilogues (rows and transposed): one or two registers, outside its loops
     (r"gemm_persistent_dx_kernelI.*Li128ELi256ELi2ELi2ELi0ELb0ELb1ELb0E|bwd_fused_kernelI.*Li256ELb1ELb0ELi(128|256)E", 16),
     # eq. (1) under a gate on 128 x 256 tiles: gate values beside 128 accumulators, 16-bit results only

@@ -281,13 +281,11 @@ template <int ROWS, int NGRP, int NW> struct DmaK {
         chunk = (lane & 7) ^ swz(r0);
         voff = row_off + (chunk << 4);
     }
-    // pass i of this wavefront.  nch < 8: the slice is the ragged last one of the reduction and holds
-    // only nch valid 16-byte chunks per row; lanes whose chunk lies beyond fetch nothing and clear
+    // pass i of this wavefront, whose first row lies at `sbase`.  nch < 8: the slice is the ragged last one of the reduction and
+    // holds only nch valid 16-byte chunks per row; lanes whose chunk lies beyond fetch nothing and clear
     // their 16 bytes of LDS instead (the caller waits for those LDS writes before it publishes the slice).
-    __device__ __forceinline__ void issue(const char *const (&base)[NGRP], int64_t ld_bytes, char *lds, int i, int nch = 8) const
+    __device__ __forceinline__ void pass(const char *sbase, char *lds, int i, int nch) const
     {
-        const int g = (PASS_ROWS * i) / GROUP_ROWS;       // uniform: pass i covers rows PASS_ROWS*i ..
-        const char *sbase = base[g] + (int64_t)(PASS_ROWS * i - g * GROUP_ROWS) * ld_bytes;
         char *const dst = lds + (wave + NW * i) * 1024;
         if (nch == 8) {
             dma16(sbase, voff, dst);
@@ -295,6 +293,24 @@ template <int ROWS, int NGRP, int NW> struct DmaK {
             const int lane = threadIdx.x & 63;
             if (chunk < nch) dma16(sbase, voff, dst);
             else *reinterpret_cast<uint4 *>(dst + lane * 16) = make_uint4(0, 0, 0, 0);
+        }
+    }
+    __device__ __forceinline__ void issue(const char *const (&base)[NGRP], int64_t ld_bytes, char *lds, int i, int nch = 8) const
+    {
+        const int g = (PASS_ROWS * i) / GROUP_ROWS;       // uniform: pass i covers rows PASS_ROWS*i ..
+        pass(base[g] + (int64_t)(PASS_ROWS * i - g * GROUP_ROWS) * ld_bytes, lds, i, nch);
+    }
+    // All passes, by a pointer that moves on.  A row offset kept for each is two scalar registers a pass, and a loader that runs
+    // out of them fetches some from vector lanes for every slice, a workgroup's whole time where few of them wait for memory
+    // (64-row tiles with a 16-bit bias, 384 x 3840 x 256 26.8 -> 24.0 us, 256 x 7936 x 256 35.4 -> 31.7).
+    __device__ __forceinline__ void issue_all(const char *const (&base)[NGRP], int64_t ld_bytes, char *lds, int nch = 8) const
+    {
+        const char *p = nullptr;
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            if (PASS_ROWS * i % GROUP_ROWS == 0) p = base[PASS_ROWS * i / GROUP_ROWS];
+            else p += PASS_ROWS * ld_bytes;
+            pass(p, lds, i, nch);
         }
     }
 };
@@ -333,18 +349,34 @@ template <int ROWS, int NW, bool S16> struct DmaT {
         const int cpos = ((lane * 16) % ROW_BYTES) >> 4;     // 16-byte slot within the row
         const int k0 = RPI * wave + kl;
         chunk = cpos ^ swz_t<ROWS, S16>(k0);
-        voff[0] = (uint32_t)kl * (uint32_t)ld_bytes + (chunk << 4);
-        voff[1] = (uint32_t)kl * (uint32_t)ld_bytes + ((chunk ^ ODD) << 4);
+        voff[0] = (uint32_t)k0 * (uint32_t)ld_bytes + (chunk << 4);
+        voff[1] = (uint32_t)k0 * (uint32_t)ld_bytes + ((chunk ^ ODD) << 4);
     }
-    // nch < ROWS / 8: the tile hangs over the end of the rows (the last tile column of a ragged N)
-    // and only its first nch >= 1 chunks per row exist: the other lanes fetch nothing, and their
+    // pass i, whose first row (of all wavefronts) lies at `sbase`.
+    // PART: the tile hangs over the end of the rows (the last tile column of a ragged N)
+    // and only its first nch chunks per row exist: the other lanes fetch nothing, and their
     // LDS columns keep whatever they held (columns beyond N, which no one stores).
-    __device__ __forceinline__ void issue(const char *const (&base)[1], int64_t ld_bytes, char *lds, int i, int nch = ROWS / 8) const
+    template <bool PART> __device__ __forceinline__ void pass(const char *sbase, char *lds, int i, int nch) const
     {
-        const int I = wave + NW * i;
+        char *const dst = lds + (wave + NW * i) * 1024;
         const uint32_t vo = voff[ODD && (i & 1)];
-        if (nch == ROWS / 8) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, vo, lds + I * 1024);
-        else if ((ODD && (i & 1) ? chunk ^ ODD : chunk) < nch) dma16(base[0] + (int64_t)(RPI * I) * ld_bytes, vo, lds + I * 1024);
+        if (!PART || nch == ROWS / 8) dma16(sbase, vo, dst);
+        else if ((ODD && (i & 1) ? chunk ^ ODD : chunk) < nch) dma16(sbase, vo, dst);
+    }
+    __device__ __forceinline__ void issue(const char *const (&base)[1], int64_t ld_bytes, char *lds, int i) const
+    {
+        pass<false>(base[0] + (int64_t)(RPI * NW * i) * ld_bytes, lds, i, ROWS / 8);
+    }
+    // (see DmaK::issue_all)
+    template <bool PART = false>
+    __device__ __forceinline__ void issue_all(const char *const (&base)[1], int64_t ld_bytes, char *lds, int nch = ROWS / 8) const
+    {
+        const char *p = base[0];
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            if (i > 0) p += (RPI * NW) * ld_bytes;
+            pass<PART>(p, lds, i, nch);
+        }
     }
 };
 

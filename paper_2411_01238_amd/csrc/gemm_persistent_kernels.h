@@ -496,6 +496,7 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
         // ---------------- loaders: the stream of slices ----------------
         using DmaA = typename std::conditional<A_KMAJ, DmaK<TM, 1, NW>, DmaT<TM, NW, S16>>::type;
         using DmaB = typename std::conditional<W_NK && OP == FWD, DmaK<TN, 1, NW>, DmaT<TN, NW, S16>>::type;
+        const int64_t lda = own_scalar(P.lda), ldb = own_scalar(P.ldb);
         DmaA da;
         DmaB db;
         da.init(lda, wave);
@@ -596,14 +597,17 @@ __device__ __forceinline__ void gemm_persistent_body(const GemmParams &P, const 
             const char *const sa[1] = {a_tile + off * (OP == FWD ? 2 : lda)};
             const char *const sb[1] = {(W_NK && OP == FWD) ? b_tile + off * 2 : b_tile + off * ldb};
             char *stp = stage_ptr(st);
-#pragma unroll
-            for (int j = 0; j < NDMA_A; ++j) da.issue(sa, lda, stp, j);
+            da.issue_all(sa, lda, stp);
             if constexpr (RAGN) {
-#pragma unroll
-                for (int j = 0; j < NDMA_B; ++j) db.issue(sb, ldb, stp + A_BYTES, j, b_chunks);
+                // Whether the column is whole is asked once for the slice or, on eq. 3's 128 x 256 tiles, by every pass.  Every pass ->
+                // once, us: eq. 1, 8192 x 1024 x 1000 21.9 -> 21.8, 128 x 7360 x 2040 (64-row blocks) 54.5 -> 39.7 (with the pointers); eq. 3 on
+                // 64-row tiles, 16384 x 3072 x 1000 141 -> 121, on 128 x 128 tiles, 4096 x 1024 x 72 14.8 -> 13.9; but on 128 x 256 ones
+                // 8192 x 1024 x 1000 33.7 -> 35.1, 17280 x 640 x 672 28.9 -> 30.3, 8192 x 4096 x 1000 65.4 -> 65.2.
+                constexpr bool ONCE = !(OP == DW && TM == 128 && TN == 256);
+                if (ONCE && b_chunks == TN / 8) db.issue_all(sb, ldb, stp + A_BYTES);
+                else db.template issue_all<true>(sb, ldb, stp + A_BYTES, b_chunks);
             } else {
-#pragma unroll
-                for (int j = 0; j < NDMA_B; ++j) db.issue(sb, ldb, stp + A_BYTES, j);
+                db.issue_all(sb, ldb, stp + A_BYTES);
             }
             ++s;
             if ((s & sub_mask) == 0) {
@@ -872,6 +876,7 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
     struct Group { int u, n; int r[4], c[4]; };        // list entries [u GB, u GB + n)
 
     if (loader) {
+        const int64_t lda = own_scalar(P.lda), ldb = own_scalar(P.ldb);
         DmaK<TM, 1, NW> da;
         typename std::conditional<W_NK, DmaT<TN, NW, S16>, DmaK<TN, DXG, NW>>::type db;
         da.init(lda, wave);
@@ -959,25 +964,20 @@ __device__ __forceinline__ void gemm_persistent_dx_body(const GemmParams &P, con
             if constexpr (RAGN) {
                 if (last_chunks != 0 && s == nsteps - 1) {
                     whole = false;
-#pragma unroll
-                    for (int j = 0; j < NDMA_A; ++j) da.issue(sa, lda, stp, j, last_chunks);
-#pragma unroll
-                    for (int j = 0; j < NDMA_B; ++j) db.issue(sb, ldb, stp + A_BYTES, j, last_chunks);
+                    da.issue_all(sa, lda, stp, last_chunks);
+                    db.issue_all(sb, ldb, stp + A_BYTES, last_chunks);
                     // the cleared chunks are ordinary LDS writes: done before this wavefront goes on to
                     // the barrier that publishes the slice (which waits for the direct loads only)
                     __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0_only());
                 }
             }
             if (whole) {
-#pragma unroll
-                for (int j = 0; j < NDMA_A; ++j) da.issue(sa, lda, stp, j);
+                da.issue_all(sa, lda, stp);
                 if constexpr (W_NK) {
                     const char *const sk[1] = {bgrp[0] + (int64_t)s * TK * ldb};      // rows [64 s, 64 s + 64) of W[N,K]
-#pragma unroll
-                    for (int j = 0; j < NDMA_B; ++j) db.issue(sk, ldb, stp + A_BYTES, j);
+                    db.issue_all(sk, ldb, stp + A_BYTES);
                 } else {
-#pragma unroll
-                    for (int j = 0; j < NDMA_B; ++j) db.issue(sb, ldb, stp + A_BYTES, j);
+                    db.issue_all(sb, ldb, stp + A_BYTES);
                 }
             }
             ++s;

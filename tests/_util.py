@@ -122,3 +122,27 @@ def blocks_of_units(units):
         else:
             out.append((x, y))
     return out
+
+
+def kernel_names(fn):
+    """Mangled names of the kernels that fn enqueues, in order of their appearance in a captured graph."""
+    import os
+    import re
+    import tempfile
+    import warnings
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        fn()
+    torch.cuda.current_stream().wait_stream(side)
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    g.enable_debug_mode()
+    with torch.cuda.graph(g):
+        fn()
+    with tempfile.TemporaryDirectory() as d:
+        path = os.path.join(d, "graph.dot")
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")         # (a dump announces itself)
+            g.debug_dump(path)
+        return re.findall(r"_Z\w+", open(path).read())

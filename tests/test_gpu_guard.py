@@ -102,3 +102,65 @@ def test_no_entry_point_writes_outside_its_buffers(M, K, N, BM, BK, dtype, out32
     for name, b in bufs.items():
         assert b.intact(), "%s: bytes outside the buffer were written" % name
     assert torch.equal(Y, Y2) and torch.equal(dX, dX2) and torch.equal(dW, dW2)
+
+
+@pytest.mark.parametrize("M,K,N,BM,BK,dtype", SHAPES + [
+    (1024, 512, 256, 128, 128, torch.bfloat16),      # the paired launches with dW on narrow tiles
+    (8192, 256, 512, 128, 128, torch.float16),       # ... with dW in parts
+])
+def test_the_calls_of_inference_and_of_a_blocks_backward(M, K, N, BM, BK, dtype):
+    # sdrop_fwd_dense, sdrop_bwd_gated, sdrop_producer_bwd and sdrop_producer_zeroed by their C entry points, each output
+    # between guards: against the calls above
+    import ctypes
+    print("guard case, block", M, K, N, BM, BK, dtype, flush=True)
+    L, code, stream = sdrop.lib(), sdrop._DTYPES[dtype], sdrop._stream()
+    g = torch.Generator(device="cuda").manual_seed(2)
+    X, W, dY, gate = (torch.randn(s, generator=g, device="cuda", dtype=torch.float32).to(dtype) for s in ((M, K), (K, N), (M, N), (M, K)))
+    b16 = torch.randn(N, generator=g, device="cuda", dtype=torch.float32).to(dtype)
+    b32 = torch.randn(K, generator=g, device="cuda", dtype=torch.float32)
+    m = sdrop.sdrop_mask(M, K, BM, BK, 0.5, 3, 1)
+    bufs = {}
+
+    def out(name, *shape):
+        bufs[name] = Guarded(2 * shape[0] * shape[1])
+        return bufs[name].view(shape, dtype)
+
+    # the forward without a mask, both layouts of the weight
+    for layout in (sdrop.W_KN, sdrop.W_NK):
+        w = W if layout == sdrop.W_KN else W.t().contiguous()
+        y = out("Y of sdrop_fwd_dense, layout %d" % layout, M, N)
+        epi, done = sdrop.Epilogue(w_layout=layout), ctypes.c_int(-1)
+        assert L.sdrop_fwd_dense(X.data_ptr(), w.data_ptr(), b16.data_ptr(), y.data_ptr(), M, K, N, BM, BK, code, stream,
+                                 ctypes.byref(epi), ctypes.byref(done)) == sdrop.OK
+        assert done.value == int(M % 128 == 0 and (layout == sdrop.W_KN or N % 256 == 0))
+        if done.value:
+            assert torch.equal(y, sdrop.sdrop_fwd_seeded(X, w, BM, BK, 0.0, 0, w_layout=layout, bias=b16)[0])
+    # the block's products in pairs
+    need = sdrop.workspace_bytes(sdrop.OP_BWD_DW, M, K, N, BM, BK, dtype, dtype)
+    bufs["workspace"] = Guarded(max(need, 256))
+    ws = bufs["workspace"].body.data_ptr()
+    dz, dw, dh, dw0 = out("dZ", M, K), out("dW", K, N), out("dH", M, N), out("dW0", K, N)
+    for gate_mode in (sdrop.GATE_RELU, sdrop.GATE_GELU_ERF):
+        assert L.sdrop_bwd_gated(dY.data_ptr(), W.data_ptr(), X.data_ptr(), gate.data_ptr(), gate_mode, m.buf.data_ptr(), dz.data_ptr(),
+                                 dw.data_ptr(), M, K, N, BM, BK, 0.5, code, ws, need, stream) == sdrop.OK
+        assert torch.equal(dz, sdrop.sdrop_bwd_dx_ex(dY, W, m, relu_mask=gate, gate_mode=gate_mode))
+        assert torch.equal(dw, sdrop.sdrop_bwd_dw(X, dY, m))
+    assert L.sdrop_producer_bwd(dz.data_ptr(), W.data_ptr(), dY.data_ptr(), m.buf.data_ptr(), dh.data_ptr(), dw0.data_ptr(), M, K, N,
+                                BM, BK, 0.5, code, ws, need, stream) == sdrop.OK
+    assert torch.equal(dh, sdrop.sdrop_fwd_ex(dz, W, m, scale_mode=sdrop.SCALE_ONE))
+    assert torch.equal(dw0, sdrop.sdrop_bwd_dw_ex(dz, dY, m, scale_mode=sdrop.SCALE_ONE))
+    # the producer whose second output is zeroed: rows of a wider matrix, whose other columns are guards as well
+    for act in (sdrop.ACT_RELU, sdrop.ACT_GELU_ERF):
+        x, z = out("X, act %d" % act, M, K + 8), out("Z, act %d" % act, M, K + 8)
+        x.fill_(7.0)
+        z.fill_(7.0)
+        assert L.sdrop_producer_zeroed(dY.data_ptr(), W.data_ptr(), b32.data_ptr(), m.buf.data_ptr(), x.data_ptr(), z.data_ptr(), M, N, K,
+                                       BM, BK, 0.5, act, code, code, stream, N, N, K + 8) == sdrop.OK
+        zeros = torch.zeros((M, K), dtype=dtype, device="cuda")
+        x0, z0 = sdrop.sdrop_producer(dY, W, b32, m, act=act, preact=zeros)
+        assert torch.equal(x[:, :K], x0) and torch.equal(z[:, :K], z0)
+        assert bool((x[:, K:] == 7.0).all()) and bool((z[:, K:] == 7.0).all())
+    torch.cuda.synchronize()
+    assert sdrop.status() == 0
+    for name, b in bufs.items():
+        assert b.intact(), "%s: bytes outside the buffer were written" % name

@@ -108,3 +108,44 @@ def test_graph_of_the_sparse_block_replays_equal_eager(M, K, N, BM, BK, dtype, p
         torch.cuda.synchronize()
         for n, o in outs.items():
             assert torch.equal(o, ref[n]), n
+
+
+@pytest.mark.parametrize("M,K,N,BM,BK,dtype,p", [
+    (1024, 512, 256, 128, 128, "bf16", 0.3),      # paired launches, dW's parts summed in the accumulators
+    (8192, 256, 512, 128, 128, "f16", 0.3),       # paired launches and a summing pass
+    (512, 768, 328, 128, 64, "bf16", 0.4),        # the calls in turn
+])
+def test_graph_of_a_blocks_paired_backward_and_of_inference(M, K, N, BM, BK, dtype, p):
+    # the producer that zeroes its second output, the two paired calls and the forward without a mask, whose outputs the
+    # binding allocates (in the graph's own pool: the same memory at every replay)
+    print("graph pairs", M, K, N, BM, BK, dtype, p, flush=True)
+    X, W, dY = (t.cuda() for t in make_custom(M, K, N, dtype, seed=7))
+    b0 = torch.randn(K, generator=torch.Generator().manual_seed(1)).cuda()
+    m = sdrop.Mask(M, K, BM, BK, p)
+
+    def step():
+        sdrop.sdrop_mask(M, K, BM, BK, p, 4, 2, out=m)
+        x, z = sdrop.sdrop_producer(dY, W, b0, m, act=sdrop.ACT_GELU_ERF, preact=True)
+        dz, dw = sdrop.sdrop_bwd_gated(dY, W, x, z, sdrop.GATE_GELU_ERF, m)
+        dh, dw0 = sdrop.sdrop_producer_bwd(dz, W, dY, m)
+        return x, z, dz, dw, dh, dw0, sdrop.sdrop_fwd_dense(X, W, BM, BK)
+
+    ref = [o.clone() for o in step()]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        outs = step()
+    for _ in range(3):
+        for o in outs:
+            o.fill_(7.0)
+        m.buf.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for o, r in zip(outs, ref):
+            assert torch.equal(o, r)

@@ -46,14 +46,49 @@ def test_shapes_without_a_kernel_take_the_masked_call():
         sdrop.sdrop_fwd_dense(X[:96].contiguous().cuda(), W.cuda(), 64, 64)        # the block must divide the shape, as ever
 
 
-@pytest.mark.parametrize("M", [192, 256])
-def test_layer_in_inference(M):
-    layer = SparseDropLinear(128, 264, 0.5, 64, 64, bias=True, seed=1).eval()
+@pytest.fixture
+def routes(monkeypatch):
+    """The forward calls that a layer makes, by name (both give the same bits, so the result does not tell)."""
+    seen = []
+
+    def watch(name):
+        call = getattr(sdrop, name)
+
+        def watched(*a, **kw):
+            r = call(*a, **kw)
+            seen.append(name if r is not None else name + " without a kernel")
+            return r
+        monkeypatch.setattr(sdrop, name, watched)
+
+    watch("sdrop_fwd_dense")
+    watch("sdrop_fwd_seeded")
+    return seen
+
+
+@pytest.mark.parametrize("M,N,nk,route", [
+    (256, 264, False, "sdrop_fwd_dense"), (192, 264, False, "sdrop_fwd_seeded"),
+    (256, 256, True, "sdrop_fwd_dense"), (256, 264, True, "sdrop_fwd_seeded"),
+])
+def test_layer_in_inference(M, N, nk, route, routes):
+    layer = SparseDropLinear(128, N, 0.5, 64, 64, bias=True, seed=1, weight_layout="nk" if nk else "kn").eval()
     x = torch.randn(M, 128, device="cuda").to(torch.bfloat16)
     with_graph = layer(x)
-    assert with_graph.requires_grad
+    assert with_graph.requires_grad and routes == ["sdrop_fwd_seeded"]
     with torch.no_grad():
         y = layer(x)
     assert not y.requires_grad and torch.equal(y, with_graph)
     with torch.inference_mode():
         assert torch.equal(layer(x), y)
+    assert routes[1:] == [route, route]
+
+
+def test_a_training_layer_drops_blocks_without_a_graph_too(routes):
+    layer = SparseDropLinear(128, 264, 0.5, 64, 64, bias=False, seed=1)
+    x = torch.ones(256, 128, device="cuda", dtype=torch.bfloat16)
+    with torch.no_grad():
+        layer.weight.fill_(1.0)
+        y = layer(x)
+    assert routes == ["sdrop_fwd_seeded"]
+    keep = sdrop.sdrop_mask(256, 128, 64, 64, 0.5, 1, 0).bits().cpu().flatten().tolist()
+    kept = torch.tensor([bin(b & 3).count("1") for b in keep]).repeat_interleave(64)
+    assert torch.equal(y.float().cpu(), (kept * 128.0)[:, None].expand(-1, 264)) and 0 < kept.sum() < 2 * 256

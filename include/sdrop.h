@@ -69,8 +69,8 @@ enum { SDROP_OP_FWD = 0, SDROP_OP_BWD_DX = 1, SDROP_OP_BWD_DW = 2 };
  *       the shape allows it)
  *   SDROP_TUNE_DX_TILE_WIDTH  columns of sdrop_bwd_dx's output tiles: 0 (default) chosen per call
  *       from the expected number of kept blocks, 128 or 256 forced
- *   SDROP_TUNE_BWD_FUSED  1 (default): sdrop_bwd computes both gradients in one launch where the
- *       shapes allow it; 0: always as the two separate launches
+ *   SDROP_TUNE_BWD_FUSED  1 (default): sdrop_bwd, sdrop_bwd_gated and sdrop_producer_bwd compute their two
+ *       products in one launch where the shapes allow it; 0: always as the two separate launches
  *   SDROP_TUNE_FWD_SEEDED  1 (default): sdrop_fwd_seeded draws the mask inside the forward kernel where the
  *       block grid allows it; 0: always as sdrop_mask followed by sdrop_fwd
  *   SDROP_TUNE_DW64_PERSISTENT_SLICES  sdrop_bwd_dw with 64-row tiles (BK = 64) uses its persistent kernel
@@ -438,7 +438,8 @@ int sdrop_fwd_dense(const void *X, const void *W, const void *bias, void *Y, int
 
 /*
  * The products of the backward of a block  H -> act(H W0^T + b0) -> dropout -> . W  in pairs, in one launch each where the
- * shapes allow it (128 x 128 blocks, N and N0 multiples of 256), else one after the other.  Contiguous matrices of type
+ * shapes allow it (128 x 128 blocks, N and N0 multiples of 256; not where the weight's gradient on its own would run in
+ * parts on 128-wide tiles and M > 8192; not under SDROP_TUNE_BWD_FUSED = 0), else one after the other.  Contiguous matrices of type
  * `dtype`; ws, ws_bytes: sdrop_workspace_bytes(SDROP_OP_BWD_DW, ...) of the second product.  Same bits as the two calls.
  *   sdrop_bwd_gated     dZ = sdrop_bwd_dx_ex(dY, W) with the gate matrix (SDROP_GATE_*) as its only tail, dropout scale;
  *                       dW = sdrop_bwd_dw(X, dY)

@@ -480,8 +480,8 @@ template <bool KMAJ, int ROWS, bool RAGGED, int NGRP = 1> struct Slice {
 
 // The matrix instruction of a kernel: v_mfma_f32_32x32x16 or (S16) v_mfma_f32_16x16x32.  The sums are the same bits (a
 // reduction of 32 in one instruction adds up as two of 16 in turn do).  Beside the operand reads from LDS the 16 x 16 form
-// sustains 1.90 PFLOP/s against 1.70 (a loop of either on all CUs, random bf16; the chip holds a higher clock), but a
-// half slice of it is twice the operands at a time.  Measured, 32 -> 16, us: both operands read by rows (eq. 2, eq. 1 with an
+// sustains 1.80 - 1.85 PFLOP/s against 1.62 - 1.66 (a loop of either on all CUs with one read after an MFMA, random bf16, two
+// cards, profiles/probe_mfma_shapes.md: 1.88 - 1.92 GHz against 1.63 - 1.65), but a half slice of it is twice the operands at a time.  Measured, 32 -> 16, us: both operands read by rows (eq. 2, eq. 1 with an
 // [N,K] weight), 4096^3: p = 0 117 -> 107 and 112 -> 103, p = 0.5 (single blocks) 89 -> 85; eq. 1 with a [K,N] weight on
 // 256-wide tiles 63 -> 60 at p = 0.5 and 112 -> 106 at p = 0, 64-row tiles (8192 x 1024^2) 19.2 -> 18.6; but eq. 3, whose
 // operands both need transposing reads, 65 -> 72 and 113 -> 119, eq. 1 on 128-wide tiles the same within 1 % (1024^3, 2048^3,

@@ -586,7 +586,7 @@ int run_fwd_seeded(const void *x, const void *w, void *mask, size_t mask_bytes, 
 // eq. (1) with nothing dropped (p = 0, scale 1), as a layer in inference calls it: no mask object is drawn, written or
 // read.  All blocks being kept, the mask's block size means nothing to the product, so 64-row blocks run on 128-row tiles
 // as well (half the operand reads from LDS per product, one round of tiles instead of two; 8192 x 1024 x 1000 with a bias and
-// 64 x 64 blocks, a layer's call as a whole: 30.5 -> 25.8 us), and no launch draws a mask on the grids that the forward
+// 64 x 64 blocks, a layer's call as a whole: 28.3 -> 21.0 us), and no launch draws a mask on the grids that the forward
 // does not draw itself.  Returns -1 where there is no
 // such kernel (M not a multiple of 128; an [N,K] weight whose N is not a multiple of 256).
 int run_fwd_dense(const void *x, const void *w, const void *bias16, void *y, int64_t M, int64_t K, int64_t N, int BM, int BK,
@@ -786,9 +786,12 @@ int run_bwd(const void *dy, const void *w, const void *x, const void *mask, void
 // dropped 72.9 -> 62.5 / 57.7 -> 50.3; 16384 x 4096 x 1024 at p = 0.1 341 -> 313 / 210 -> 206; 65536 x 2048 x 512 at 0.3 350 ->
 // 328 / 181 -> 174; 4096^3, half dropped 159 -> 153 / 121 -> 117; 1024^3 25.5 -> 16.0 / 19.4 -> 12.0; 256 x 512 x 256 16.5 -> 11.4 /
 // 13.5 -> 8.3; 16384 x 1024 x 512, nothing dropped 73.2 -> 71.8 / 53.0 -> 52.0.  A block of 4096 x 4096 x 1024 with 1024
-// features in front and a GELU as a whole: 229 -> 215.  Not where dW on its own runs its parts on narrow tiles (which this
-// launch does not hold) and its lists are long: 32768 x 256^2 at 0.2 42.3 -> 42.8 with a ReLU's gate, 36.1 -> 40.7
-// (8192 x 1024 x 256, the line: 39.9 -> 38.9 / 31.5 -> 24.8).
+// features in front and a GELU as a whole: 229 -> 215 (kernels of that time).  Not where dW on its own runs its parts on narrow
+// tiles (which this launch does not hold) and its lists are long: 32768 x 256^2 at 0.2 42.3 -> 42.8 with a ReLU's gate, 36.1 -> 40.7
+// (8192 x 1024 x 256, the line: 39.9 -> 38.9 / 31.5 -> 24.8).  Swept with either form forced, 240 random shapes
+// (M to 65536, K to 6000, N to 4096, three calls each): one launch is 1.22 times the speed in turn (geometric mean of 600 calls)
+// where this rule takes it, 11 calls of six shapes below 0.985 (the worst 8576 x 3584 x 2304 at p = 0.1, whose dW fills a round by
+// itself: 0.90 - 0.93); in the 120 calls that it leaves in turn 0.85 - 1.42, 28 below 0.985, 24 of them beyond 30000 rows.
 bool pair_applies(GemmParams &Pdw)
 {
     if (!g_bwd_fused || Pdw.BM != 128 || Pdw.BK != 128 || Pdw.N % 256 != 0) return false;

@@ -20,19 +20,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_DENSE_TFLOPS = 2500.0     # MI355X published dense bf16/fp16 MFMA peak
-# What the matrix cores of this chip were measured to sustain under its power limit (profiles/probe_clock_mfma_lds_loads.md):
-# bf16 MFMAs issued back to back hold 1.56 GHz = 1640 TFLOP/s; with the operand reads from LDS that feed them, 1390
-MFMA_ONLY_CEILING_TFLOPS = 1640.0
-MFMA_WITH_LDS_READS_CEILING_TFLOPS = 1390.0
+# What the matrix cores of this chip were measured to sustain under its power limit with the operand reads from LDS that feed
+# them (profiles/probe_mfma_shapes.md, the larger of two cards): 16x16x32 bf16 MFMAs 1850 TFLOP/s at 1.92 GHz, 32x32x16 1660 at 1.65
+MFMA_16X16_WITH_LDS_READS_TFLOPS = 1850.0
+MFMA_32X32_WITH_LDS_READS_TFLOPS = 1660.0
 # Bytes per launch that crossed L2 -> fabric: rocprofv3 FETCH_SIZE / WRITE_SIZE of an earlier run of this
 # benchmark's launches, scaled by a known 1 GiB copy.  Constants from the tracked counter summaries named
 # here, NOT measured by this run (counters need the profiler).
 TRAFFIC_BYTES = {
-    ("square4096", 0.5): {"fwd": 235.6e6, "bwd": 581.2e6, "source": "profiles/bench_square4096_p0.5.md"},
-    ("mlp", 0.5): {"fwd": 58.2e6, "bwd": 127.9e6, "source": "profiles/bench_mlp_p0.5.md"},
+    ("square4096", 0.5): {"fwd": 235.6e6, "bwd": 576.6e6, "source": "profiles/bench_square4096_p0.5.md"},
+    ("mlp", 0.5): {"fwd": 58.2e6, "bwd": 127.6e6, "source": "profiles/bench_mlp_p0.5.md"},
     ("mlp", 0.1): {"fwd": 85.1e6, "bwd": 135.6e6, "source": "profiles/bench_mlp_p0.1.md"},
-    ("ffn_down", 0.1): {"fwd": 372.9e6, "bwd": 671.7e6, "source": "profiles/bench_ffn_down_p0.1.md"},
-    ("skinny", 0.3): {"fwd": 1781.5e6, "bwd": 4891.2e6, "source": "profiles/bench_skinny_p0.3.md"},
+    ("ffn_down", 0.1): {"fwd": 372.9e6, "bwd": 672.0e6, "source": "profiles/bench_ffn_down_p0.1.md"},
+    ("skinny", 0.3): {"fwd": 1780.6e6, "bwd": 4831.1e6, "source": "profiles/bench_skinny_p0.3.md"},
 }
 
 
@@ -285,9 +285,9 @@ def main():
                 "duration_is": "HIP events on the launch stream around each launch of the timed steps (includes the dispatch "
                                "latency between dependent launches); profiles/ holds the rocprofv3 kernel trace of the same command",
                 "frac_of_measured_mfma_ceiling": {
-                    "mfma_only_1640_tflops": round(achieved / MFMA_ONLY_CEILING_TFLOPS, 5),
-                    "mfma_with_lds_operand_reads_1390_tflops": round(achieved / MFMA_WITH_LDS_READS_CEILING_TFLOPS, 5),
-                    "source": "profiles/probe_clock_mfma_lds_loads.md"},
+                    "mfma_16x16x32_with_lds_operand_reads_1850_tflops": round(achieved / MFMA_16X16_WITH_LDS_READS_TFLOPS, 5),
+                    "mfma_32x32x16_with_lds_operand_reads_1660_tflops": round(achieved / MFMA_32X32_WITH_LDS_READS_TFLOPS, 5),
+                    "source": "profiles/probe_mfma_shapes.md"},
                 "avg_launch_ms": {k: round(v, 5) for k, v in kern.items()},
                 "separate_launch_ms": {k: round(v, 5) for k, v in kern_sep.items()}}
 

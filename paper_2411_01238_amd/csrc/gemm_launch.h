@@ -8,8 +8,19 @@
 namespace sdrop {
 namespace {
 
-// WM x WN: wavefront grid of the kernel without ragged edges; WMR x WNR (4 wavefronts): with.
+// Does the device grant these kernels that much LDS?  (Set and asked once for each instantiation of a launch.)
+template <class... K> bool lds_granted(int bytes, K... kernels)
+{
+    for (const void *k : {reinterpret_cast<const void *>(kernels)...}) {
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+    }
+    return true;
+}
 
+// WM x WN: wavefront grid of the kernel without ragged edges; WMR x WNR (4 wavefronts): with.
 
 template <int TMODE, int OP, class T, class OutT, int TM, int TN, int WM, int WN, int WMR, int WNR>
 int launch_t(const GemmParams &P, int grid, bool ragged, hipStream_t stream, bool persistent_ok);
@@ -64,16 +75,7 @@ int launch_t(const GemmParams &P, int grid, bool ragged, hipStream_t stream, boo
             constexpr int P_LDS = persistent_lds(TM, TN);
             auto k_whole = gemm_persistent_kernel<OP, T, OutT, TM, TN, WM, WN, TMODE, false>;
             auto k_edge = gemm_persistent_kernel<OP, T, OutT, TM, TN, WM, WN, TMODE, !TAIL>;    // (the same kernel when there is a tail)
-            static int pers_ok = -1;    // per instantiation: does the device grant that much LDS?
-            if (pers_ok < 0) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-                if (e == hipSuccess)
-                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-                pers_ok = (e == hipSuccess);
-                if (!pers_ok) (void)hipGetLastError();
-            }
+            static const bool pers_ok = lds_granted(P_LDS, k_whole, k_edge);    // per instantiation
             auto k_pers = ragged ? k_edge : k_whole;
             if (pers_ok) {
                 GemmParams Q = P;
@@ -98,14 +100,7 @@ int launch_fwd_seeded(const GemmParams &P, hipStream_t stream)
     constexpr int P_LDS = persistent_lds(TM, TN);
     auto k_whole = fwd_seeded_kernel<T, OutT, TM, TN, false, BIAS>;
     auto k_edge = fwd_seeded_kernel<T, OutT, TM, TN, true, BIAS>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k_whole, k_edge);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)((P.N + TN - 1) / TN);
@@ -125,14 +120,7 @@ int launch_fwd_plain(const GemmParams &P, hipStream_t stream)
     constexpr int P_LDS = persistent_lds(TM, TN), WM = TN == 256 ? 1 : 2, WN = 4 / WM;
     auto k_whole = gemm_persistent_kernel<FWD, T, OutT, TM, TN, WM, WN, BIAS ? kTailBias16 : kTailNone, false>;
     auto k_edge = gemm_persistent_kernel<FWD, T, OutT, TM, TN, WM, WN, BIAS ? kTailBias16 : kTailNone, true>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k_whole, k_edge);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)((P.N + TN - 1) / TN);
@@ -153,14 +141,7 @@ int launch_fwd_dense(const GemmParams &P, hipStream_t stream)
     constexpr int P_LDS = persistent_lds(128, TN);
     auto k_whole = fwd_dense_kernel<T, OutT, TN, false, W_NK, BIAS>;
     auto k_edge = fwd_dense_kernel<T, OutT, TN, !W_NK, W_NK, BIAS>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k_whole, k_edge);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)((P.N + TN - 1) / TN);
@@ -179,12 +160,7 @@ int launch_fwd_nk(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = persistent_lds(TM, TN);
     auto k = fwd_nk_kernel<T, OutT, TM, TN, SEEDED, BIAS>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)(P.N / TN);
@@ -201,12 +177,7 @@ int launch_dw_nk(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = persistent_lds(TM, TN);
     auto k = dw_nk_kernel<T, OutT, TM, TN>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)(P.N / TN);
@@ -224,14 +195,7 @@ int launch_dw_narrow(const GemmParams &P, hipStream_t stream)
     constexpr int P_LDS = persistent_lds(128, 128);
     auto k_whole = gemm_persistent_kernel<DW, T, OutT, 128, 128, 2, 2, kTailNone, false>;
     auto k_edge = gemm_persistent_kernel<DW, T, OutT, 128, 128, 2, 2, kTailNone, true>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_edge), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k_whole, k_edge);     // per instantiation
     if (!ok) return -1;
     GemmParams Q = P;
     Q.n_tiles = (int)((P.N + 127) / 128);
@@ -271,14 +235,7 @@ int launch_dx_persistent_t(const GemmParams &P, hipStream_t stream)
     // two forms: N a multiple of the 64-wide slice, or with a ragged last slice
     auto k_whole = gemm_persistent_dx_kernel<T, OutT, 128, TN, 2, 2, TAIL, false>;
     auto k_ragged = gemm_persistent_dx_kernel<T, OutT, 128, TN, 2, 2, TAIL, true>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_whole), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_ragged), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k_whole, k_ragged);   // per instantiation
     auto k = P.N % TK == 0 ? k_whole : k_ragged;
     if (!ok) return -1;
     const int64_t positions = (int64_t)P.MB * P.KB;
@@ -293,12 +250,7 @@ int launch_dx_pairs(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = persistent_lds(128, 256);
     auto k = gemm_persistent_dx_kernel<T, OutT, 128, 256, 2, 2, kTailNone, false, true>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     const int64_t positions = (int64_t)P.MB * P.KB;
     const int ncu = cu_count();
@@ -312,12 +264,7 @@ int launch_dx_nk(const GemmParams &P, hipStream_t stream)
 {
     constexpr int P_LDS = persistent_lds(128, 128);
     auto k = gemm_persistent_dx_kernel<T, OutT, 128, 128, 2, 2, kTailNone, false, false, true>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     const int64_t positions = (int64_t)P.MB * P.KB;
     const int ncu = cu_count();
@@ -436,12 +383,7 @@ int launch_bwd_fused(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t s
     constexpr int LDS_DX = persistent_lds(128, TN_DX), LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
     auto k = bwd_fused_kernel<T, OutDX, OutDW, TN_DX, PAIRS, W_NK, TN_DW>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     const int ncu = cu_count();
     const int64_t positions = (int64_t)Pdx.MB * Pdx.KB;
@@ -457,12 +399,7 @@ int launch_bwd_fused_tile(const GemmParams &Pdx, const GemmParams &Pdw, int n_dx
     constexpr int LDS_DX = 3 * (128 + 256) * TK * 2, LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
     auto k = bwd_fused_tile_kernel<T, OutDX, OutDW, TN_DW, W_NK>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     const int ncu = cu_count();
     const int g_dw = Pdw.total_tiles < ncu ? Pdw.total_tiles : ncu;
@@ -494,12 +431,7 @@ int launch_bwd_gated(const GemmParams &Pdx, const GemmParams &Pdw, hipStream_t s
     constexpr int LDS_DX = persistent_lds(128, 128), LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_DX > LDS_DW ? LDS_DX : LDS_DW;
     auto k = bwd_gated_kernel<T, OutDX, OutDW, TAIL, TN_DW>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     const int ncu = cu_count();
     const int64_t positions = (int64_t)Pdx.MB * Pdx.KB;
@@ -516,12 +448,7 @@ int launch_fwd_dw(const GemmParams &Pf, const GemmParams &Pdw, hipStream_t strea
     constexpr int LDS_F = persistent_lds(128, TN_F), LDS_DW = persistent_lds(128, TN_DW);
     constexpr int P_LDS = LDS_F > LDS_DW ? LDS_F : LDS_DW;
     auto k = fwd_dw_kernel<T, OutF, OutDW, TN_F, TN_DW>;
-    static int ok = -1;     // per instantiation: does the device grant that much LDS?
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     GemmParams F = Pf;
     F.n_tiles = (int)(F.N / TN_F);
@@ -539,12 +466,7 @@ int launch_bwd_fused_tile64(const GemmParams &Pdx, const GemmParams &Pdw, int n_
     constexpr int P_LDS = stages_for(64, 256) * (64 + 256) * TK * 2;      // the larger of the two bodies' needs
     static_assert(stages_for(64, TN_DX) * (64 + TN_DX) * TK * 2 <= P_LDS, "dX's stages must fit");
     auto k = bwd_fused_tile64_kernel<T, OutDX, OutDW, TN_DX>;
-    static int ok = -1;
-    if (ok < 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, P_LDS);
-        ok = (e == hipSuccess);
-        if (!ok) (void)hipGetLastError();
-    }
+    static const bool ok = lds_granted(P_LDS, k);     // per instantiation
     if (!ok) return -1;
     hipLaunchKernelGGL(k, dim3((unsigned)(n_dx + n_dw)), dim3(256), P_LDS, stream, Pdx, Pdw, n_dx);
     return hip_status(hipGetLastError());

@@ -258,6 +258,9 @@ int g_dx_persistent_groups_per_cu = 8;
 // 3 (16384 x 3072 x 768, 64-wide blocks, half dropped) 61 against 56; 5.6 (8192 x 8192 x 2048, 0.3
 // dropped) 215 against 190; 9.6 (65536 x 4096 x 1024, 0.7 dropped) 235 against 270; 22 (the same,
 // 0.3 dropped) 410 against 417.
+// (These figures and the pair list's below are of 32x32x16 kernels.  With every form forced on the present ones, 200 random
+// shapes of 128-row blocks: the plan takes the fastest within 2 % in 123; in 61 another is at least 5 % faster, up to 1.8
+// times: the pair list in 30 (26 at p <= 0.2), other widths or kernels in 31, of which 21 have 128 x 64 blocks.)
 int g_dx_tile_width = 0;    // 0: chosen per call; 128 or 256: forced (benchmarks and tests)
 // The pair list (see build_units): every unit is a 128 x 256 tile of two kept blocks, from the same block row or
 // the same block column, so no tile is cut and (almost) none is half empty: ceil(kept / 2) equal tiles, each
@@ -327,6 +330,9 @@ DxPlan dx_plan(const GemmParams &P, bool fused)
 //   16384 x 4096 x 256 53.5 -> 48.2 / 49.5 -> 45.2 / 41.3 -> 35.4;  112: 14336 x 1024 x 256 22.1 -> 18.8 / 23.4 -> 20.0 / 22.0 -> 18.5.
 // (At p = 0 the same shapes gave 1.00 to 1.30 of the wide form's speed in that run.)  Beyond half of the chip a second
 // round of narrow tiles loses to one of wide ones (160 wide tiles, all kept, K = 1024: 16.1 -> 20.6).
+// (Wide tiles are of 16x16x32 instructions since, narrow ones are not.  Either form forced on the present kernels, 150 random shapes,
+// narrow / wide: up to 96 wide tiles on 256 CUs 0.67 - 0.91 in all 74; 97 - 128 tiles 20 of 21 faster, one 1.03; 129 - 256 tiles, which
+// this rule leaves wide, 0.79 - 1.28, 33 of 55 faster by more than 2 % and 18 slower.)
 bool fwd_narrow(const GemmParams &P)
 {
     const int64_t wide = P.MB * ((P.N + 255) / 256), ncu = cu_count();
@@ -467,7 +473,8 @@ int run(const void *a, const void *b, const void *mask, void *out,
         // eq. 2's in-place form computes one kept block per tile.  Where the [K,N] plan would take 256-wide tiles of
         // one block row (many tiles per CU: 65536 x 4096 x 1024, 431 us through the transposed copy against 450 in
         // place), the copy is the cheaper way; where it takes single blocks or the pair list (4096^3: 74 us in place
-        // against 63 + 15), it is not.
+        // against 63 + 15), it is not.  (Of 120 random shapes with either way forced on the present kernels this takes the faster
+        // within 2 % in 84; in the 25 where it loses 5 % or more, up to a third, it copies and in place is the faster.)
         GemmParams Q = base_params(OP, a, b, mask, out, M, K, N, BM, BK, p, out_dtype, L);
         if (epi->kept_fraction > 0.0) { Q.p = 1.0 - (epi->kept_fraction < 1.0 ? epi->kept_fraction : 1.0); Q.kept_given = true; }
         const DxPlan plan = dx_plan(Q);
